@@ -223,51 +223,62 @@ __global__ void count_unreached_kernel(int n, const int *__restrict__ dist, int 
 // last visit).  A recorded walk is always long enough: it stopped at a vertex of an older
 // tree, which is still in T.  Three commit paths:
 //   - runs of short walks (at most kPathLds steps, kept in LDS) commit as one batch, one
-//     lane each, up to the first entry that reads a vertex an earlier entry of the batch
-//     writes (detected through two minimum-writer tables under independent hashes);
-//   - longer recorded walks (up to 255 steps) commit cooperatively with ballots (one ballot per
-//     64-step chunk finds the truncation point, one per chunk and branch vertex finds the
-//     vertex's last visit).  A walk that filled its 255-step record without reaching the
-//     tree it saw takes this path too: the tree has usually grown since, so the record
-//     mostly does reach it;
-//   - if no recorded vertex is in the tree, one lane turns the record into Next pointers (in
-//     the parent field of the record array) and continues the walk from its last vertex in
-//     a tight loop (the sequential algorithm for that start).
-// Everything a commit needs is prefetched into LDS while walking (the B_u flag word of
-// every recorded vertex, the chain value of the vertex a walk ends on), so the in-order
-// commit path does no dependent global loads in the common cases.
+//     lane each.  Nine walks in ten of a small-world graph are a single step, and a run of
+//     those needs no test at all: its end is in T for good, and nothing it adds is read by
+//     another.  Where the run holds longer walks, the vertices they read beside their start
+//     (inner vertices) are tested against the tree, and the batch commits up to the first
+//     walk that reads an inner vertex of an earlier one (two minimum-writer tables under
+//     independent hashes); the starts take part only if an inner vertex lies among the
+//     starts in flight, an interval since starts ascend;
+//   - longer recorded walks (up to kPath steps) commit cooperatively: a lane per step, the
+//     loop erasure by one ballot and one lane read per branch vertex.  A walk that filled its
+//     record without reaching the tree it saw takes this path too: the tree has usually
+//     grown since, so the record mostly does reach it;
+//   - if no recorded vertex is in the tree, one lane turns the record into Next pointers and
+//     continues the walk from its last vertex in a tight loop (the sequential algorithm for
+//     that start).
 //
-// Output per vertex x: rec[x] = {parent_T(x), nba(x) | marked(x) << 31} (see "Marked
-// vertices").  Launches are persistent: each block takes tree after tree from a queue.
+// What bounds it: the latency of a round (allocate, step, commit) times the rounds of a tree, and
+// on graphs within the bitmap instruction issue.  A commit round that planned every walk for
+// five recorded steps, with a tree test (a global load past the bitmap) per vertex, took half
+// of a tree's time; without those, with 128 entries and starts from the window's list, a pass went
+// from 1350 to 1036 ms (R-MAT scale 22, 8192 trees), 51.3 to 30.8 ms (R-MAT 19, 777 trees,
+// fewer trees than SIMDs), 8.58 to 5.36 ms (R-MAT 16 edge counts), 13.1 to 11.2 ms (R-MAT 16),
+// 316 to 243 ms (hyperbolic, 200k vertices) and 5.1 to 3.9 ms (32 x 32 grid).
+//
+// Output per vertex x: rec[x] = {parent_T(x), nba(x) | flags} (see "Marked vertices").
+// Launches are persistent: each block takes tree after tree from a queue.
 // ======================================================================================
 namespace {
 
-// reorder-buffer entries (LDS): with the tree bitmap in LDS the sampler's occupancy is bound by
-// LDS (64 entries); with the tree state in the records it is bound by registers, and 128 entries
-// let the lanes run further ahead of a long walk at the head
 template <bool LDS>
 constexpr int rob_cap() { return LDS ? kSamplerRobLds : kSamplerRobMax; }
-constexpr int kPathLds = 5;              // recorded steps kept in LDS per entry (x_1..x_5)
-constexpr int kPath = 255;               // recorded steps per speculative walk (x_1..x_255)
+constexpr int kPathLds = 4;    // recorded steps kept in LDS per entry (x_1..x_4)
+constexpr int kPath = 250;     // recorded steps per speculative walk (x_1..x_250)
 static_assert(kPath - kPathLds == kSamplerPathGlobal, "path split");
-// reorder-buffer entry states besides a finished walk's step count (>= 0):
+// reorder-buffer entry states (a byte) besides a finished walk's step count (<= kPath; 0: the
+// start was absorbed, nothing to commit):
 //   kWalking  - still walking
 //   kOverflow - recorded kPath steps without reaching the tree it saw
 //   kContinue - an overflowed walk none of whose recorded vertices is in the tree at commit
 //   kRewalk   - re-walk from the start (never expected; keeps the commit exact regardless)
-constexpr int kWalking = -1, kOverflow = -2, kContinue = -3, kRewalk = -4;
+constexpr int kWalking = 255, kOverflow = 254, kContinue = 253, kRewalk = 252;
+static_assert(kPath < kRewalk, "step counts and states share a byte");
+// starts are taken from a list of the free vertices of a window of this many vertices
+constexpr int kWin = 256;
+static_assert(kWin == 4 * kWave, "four vertices of the window per lane");
 
 // Membership of the tree being built.  Graphs of up to 131072 vertices keep an n-bit
-// bitmap in LDS (allocation words of 32 vertices).  Larger graphs use the vertex's own
-// record: its nba field holds kFree until the vertex joins the tree (the records are
-// cleared when the tree starts), so a membership test reads the line a walk that ends
-// there needs anyway, and joining is the record write itself (set() does nothing).
-// Records are read for membership with agent-scope loads (past the per-CU L1).
+// bitmap in LDS.  Larger graphs use the vertex's own record: its nba field holds kFree until
+// the vertex joins the tree (the records are cleared when the tree starts), so a membership
+// test reads the line a walk that ends there needs anyway, and joining is the record write
+// itself (set() does nothing).  All accesses of a tree's records come from one wavefront,
+// whose loads and stores the vector L1 keeps in order.
 constexpr int kFree = 0x3FFFFFFF;  // nba of a vertex not in the tree; vertex IDs are below it
 
 // the {nba | flags} word of a record another lane of the wave may have written
 __device__ __forceinline__ int load_nbx(const int *recw, int v) {
-    return __hip_atomic_load(recw + 2 * v + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(recw + 2 * v + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 template <bool LDS>
@@ -276,24 +287,28 @@ struct TreeState;
 template <>
 struct TreeState<true> {
     uint32_t *w;
-    static constexpr int kShift = 5;  // allocation word: 32 vertices
-    __device__ __forceinline__ uint32_t word(int i, int /*n*/) const { return w[i]; }
+    // the free vertices among the window's 4 lane .. 4 lane + 3, as 4 bits
+    __device__ __forceinline__ uint32_t free4(int base, int lane, int n) const {
+        const int v = base + 4 * lane;
+        return v < n ? (~w[v >> 5] >> (v & 31)) & 0xFu : 0u;
+    }
     __device__ __forceinline__ bool test(int v) const { return (w[v >> 5] >> (v & 31)) & 1u; }
     __device__ __forceinline__ void set(int v) const { atomicOr(w + (v >> 5), 1u << (v & 31)); }
 };
 
 template <>
 struct TreeState<false> {
-    int *recw;                        // int pairs {parent, nba | flags}
-    static constexpr int kShift = 3;  // allocation word: 8 vertices
+    int *recw;  // int pairs {parent, nba | flags}
     __device__ __forceinline__ int nbx(int v) const { return load_nbx(recw, v); }
-    __device__ __forceinline__ uint32_t word(int i, int n) const {
+    __device__ __forceinline__ uint32_t free4(int base, int lane, int n) const {
+        const int v = base + 4 * lane;
+        if (v >= n) return 0u;
+        int w[4];  // the records of a tree are padded to 32 vertices
+#pragma unroll
+        for (int b = 0; b < 4; ++b) w[b] = nbx(v + b);
         uint32_t m = 0u;
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const int v = (i << 3) + b;
-            if (v < n && nbx(v) != kFree) m |= 1u << b;
-        }
+        for (int b = 0; b < 4; ++b) m |= w[b] == kFree ? 1u << b : 0u;
         return m;
     }
     __device__ __forceinline__ bool test(int v) const { return nbx(v) != kFree; }
@@ -349,18 +364,11 @@ __device__ __forceinline__ void wave_sync() {
 __device__ __forceinline__ void consume(int a, int b, int c, int d) {
     asm volatile("" ::"v"(a), "v"(b), "v"(c), "v"(d));
 }
-// wait until all of this wavefront's global loads and stores have completed
-__device__ __forceinline__ void wait_global() {
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt/lgkmcnt unconstrained
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-}
-
 // Batch-commit conflict tables: two tables of minimum-writer lanes under independent
 // hashes; a read conflicts only if both of its slots hold a smaller lane, so collisions
-// rarely cut a batch short and a real conflict is never missed.  240 slots each rather than
-// 256 keep the sampler's LDS at R-MAT scale 16 within 8960 bytes, the size at which a CU
-// holds 18 blocks (16 above it).
-constexpr int kHashSlots = 240;
+// rarely cut a batch short and a real conflict is never missed.  A batch writes a handful of
+// inner vertices into them; together they hold the 256 walk words of a one-lane walk.
+constexpr int kHashSlots = 128;
 
 // inclusive prefix sum over the 64 lanes with DPP row shifts and row broadcasts
 __device__ __forceinline__ int wave_scan_dpp(int x) {
@@ -372,45 +380,21 @@ __device__ __forceinline__ int wave_scan_dpp(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31
     return x;
 }
-// Multiplicative hashes scaled to [0, kHashSlots).  Any hash keeps the commit exact: a
-// collision only ends a batch early.  With the tree bitmap in LDS (vertex IDs below 2^17) they
-// take bits 16..23 of a 24 x 24-bit product (odd multipliers near 2^24 times the golden ratio
-// and another irrational, so consecutive IDs spread over the table), then x 240 / 256: two
-// full-rate v_mul_u32_u24 instead of a quarter-rate 32-bit multiply and high multiply, as that
-// sampler is bound by instruction issue.  The large-graph sampler keeps the 32-bit hashes (the
-// other form costs it a register and one wave per SIMD).
+// Multiplicative hashes to [0, kHashSlots).  Any hash keeps the commit exact: a collision only
+// ends a batch early.  With the tree bitmap in LDS (vertex IDs below 2^17) they take bits
+// 16..22 of a 24 x 24-bit product (odd multipliers near 2^24 times the golden ratio and another
+// irrational, so consecutive IDs spread over the table): a full-rate v_mul_u32_u24.
 template <bool LDS>
 __device__ __forceinline__ int hash_slot(int v) {
-    if constexpr (LDS)
-        return (int)(__umul24((__umul24((unsigned)v, 0x9E3779u) >> 16) & 0xFFu, (unsigned)kHashSlots) >> 8);
-    else
-        return (int)__umulhi((unsigned)v * 2654435761u, kHashSlots);
+    if constexpr (LDS) return (int)(__umul24((unsigned)v, 0x9E3779u) >> 16) & (kHashSlots - 1);
+    else return (int)(((unsigned)v * 2654435761u) >> 25);
 }
 template <bool LDS>
 __device__ __forceinline__ int hash_slot2(int v) {
-    if constexpr (LDS)
-        return (int)(__umul24(((__umul24((unsigned)v, 0xC2B2AFu) + 0x5BD1E9u) >> 16) & 0xFFu, (unsigned)kHashSlots) >>
-                     8);
-    else
-        return (int)__umulhi((unsigned)v * 2246822519u + 3266489917u, kHashSlots);
+    if constexpr (LDS) return (int)((__umul24((unsigned)v, 0xC2B2AFu) + 0x5BD1E9u) >> 16) & (kHashSlots - 1);
+    else return (int)(((unsigned)v * 2246822519u + 3266489917u) >> 25);
 }
-
-// position of the k-th set bit of x (k < popc(x)), by halving
-__device__ __forceinline__ int select_bit(uint32_t x, int k) {
-    int pos = 0, c = __popc(x & 0xFFFFu);
-    if (k >= c) { k -= c; pos += 16; x >>= 16; }
-    c = __popc(x & 0xFFu);
-    if (k >= c) { k -= c; pos += 8; x >>= 8; }
-    c = __popc(x & 0xFu);
-    if (k >= c) { k -= c; pos += 4; x >>= 4; }
-    c = __popc(x & 0x3u);
-    if (k >= c) { k -= c; pos += 2; x >>= 2; }
-    return pos + (k >= (int)(x & 1u) ? 1 : 0);
-}
-__device__ __forceinline__ int select_bit64(uint64_t x, int k) {
-    const int c = __popc((uint32_t)x);
-    return k >= c ? 32 + select_bit((uint32_t)(x >> 32), k - c) : select_bit((uint32_t)x, k);
-}
+static_assert(kHashSlots == 128, "the hashes give seven bits");
 
 // Neighbour index (0 .. deg-1) of a walk step with word w from the row [r0, r1).  Unit
 // weights: floor(w deg / 2^32).  Weighted (Section "Generalizations"): the first j with
@@ -437,185 +421,208 @@ __device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, const doub
     }
 }
 
-// The sequential algorithm for one start s0 against the current tree, in two parts: a walk
-// that writes Next pointers (in the parent field) until it reaches the tree, then the retrace
-// of the loop erasure that writes the branch's records {parent, nba | marked << 31}.  The walk
-// resumes at step k0 from vertex x0 (k0 = 0, x0 = s0 for a whole walk; otherwise the Next
-// pointers of steps 0..k0-1 are already written).
+// ---- the one-lane walk: the sequential algorithm for one start against the current tree, in
+// two parts: a walk that writes Next pointers until it reaches the tree, then the retrace of the
+// loop erasure that writes the branch's records.  The walk resumes at step k0 from vertex x0
+// (k0 = 0, x0 = s0 for a whole walk; otherwise the Next pointers of steps 0..k0-1 are already
+// written).  Every lane calls both.
+//
+// Next pointers: the parent field of the records (it becomes the parent when the vertex joins).
+struct NextRec {
+    int *recw;
+    __device__ __forceinline__ void set(int x, int y) const { recw[2 * x] = y; }
+    __device__ __forceinline__ int get(int x) const { return recw[2 * x]; }
+};
 
-// Retrace from s0 to the tree vertex the walk reached.  One lane.
-template <bool LDS>
-__device__ void retrace_commit(const TreeState<LDS> &bits, int *recw, const int *__restrict__ bflag, int s0) {
-    int z = s0;
-    while (!bits.test(z)) {
-        bits.set(z);
-        z = recw[2 * z];
-    }
-    const int ya = z;
-    const int cva = cv_of(ya, load_nbx(recw, ya));
-    // nba: the nearest marked vertex strictly closer to ya on the branch, else cv(ya)
-    int run = s0;
-    z = s0;
-    while (z != ya) {
-        const int nz = recw[2 * z];
-        if (mark_bits(z, bflag[z], nz, bflag[nz])) {
-            for (int w2 = run; w2 != z; w2 = recw[2 * w2]) recw[2 * w2 + 1] = z;
-            run = z;
-        }
-        z = nz;
-    }
-    for (int w2 = run; w2 != ya; w2 = recw[2 * w2]) recw[2 * w2 + 1] = cva;
-    for (z = s0; z != ya; z = recw[2 * z]) {
-        const int nz = recw[2 * z];
-        recw[2 * z + 1] |= mark_bits(z, bflag[z], nz, bflag[nz]);
-    }
+__device__ __forceinline__ long long uniform_ll(long long k) {
+    const int lo = __builtin_amdgcn_readfirstlane((int)(unsigned long long)k);
+    const int hi = __builtin_amdgcn_readfirstlane((int)((unsigned long long)k >> 32));
+    return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// The walk on graphs held in LDS (the graph-in-LDS sampler).  Every lane calls it; lane 0 walks.  The
-// wave computes the walk's Philox words 256 at a time (lane i the block of steps 4(b0+i) ..
-// 4(b0+i)+3) into wbuf (LDS), so the walking lane reads a word per step instead of running a
-// ten-round Philox block on one lane every fourth step.  Returns the walk's total step count
-// on every lane.
-template <typename CT, bool WT>
-__device__ long long walk_next_wave(const TreeState<true> &bits, int *recw, const int *__restrict__ rp,
-                                    const CT *__restrict__ col, const double *__restrict__ cw,
-                                    const int *__restrict__ guide, uint32_t wkey, int x0, long long k0, uint32_t tlo,
-                                    uint32_t thi, uint32_t key0, uint32_t key1, uint32_t *wbuf) {
+// Lane 0 walks; the wave computes its Philox words 256 at a time (lane i the block of steps
+// 4 (b0 + i) .. + 3) into wbuf (LDS), so that a step reads a word instead of running a ten-round
+// block on one lane every fourth step.  Graphs past the LDS bitmap read the edge entries {y, row
+// of y, B_u flag of y}: the entry of step k gives everything step k + 1 needs, so step k + 1's
+// entry is loaded together with the tree test of y (before its answer is known) and a step waits
+// for one load, not two in a row; the Next pointer is stored after both loads are issued, so a
+// step does not wait for the store.  Graphs within it read the compact column and row arrays.
+// Returns the walk's total step count (on every lane).
+template <bool LDS, typename CT, bool WT, typename Next>
+__device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, const int *__restrict__ rp,
+                               const CT *__restrict__ col, const int4 *__restrict__ edge,
+                               const int4 *__restrict__ vrow, const double *__restrict__ cw,
+                               const int *__restrict__ guide, uint32_t wkey, int x0, long long k0, uint32_t tlo,
+                               uint32_t thi, uint32_t key0, uint32_t key1, uint32_t *wbuf) {
     const int lane = threadIdx.x;
     long long k = k0;  // wave-uniform between word blocks
-    int xw = x0, r0 = 0, r1 = 0;
+    int xw = x0;
+    int r0 = 0, r1 = 0;  // LDS bitmap: the row of xw
+    int4 e = make_int4(-1, 0, 0, 0);  // else: the entry of step k - 1, the step to take from xw
     if (lane == 0) {
-        r0 = rp[x0];
-        r1 = rp[x0 + 1];
+        if constexpr (LDS) {
+            r0 = rp[x0];
+            r1 = rp[x0 + 1];
+        } else {
+            const int4 v0 = vrow[x0];
+            r0 = v0.x;
+            r1 = v0.y;
+        }
     }
     for (;;) {
         const long long b0 = k >> 2;
         const uint4 ph = philox4x32_10(make_uint4((uint32_t)(b0 + lane), wkey, tlo, thi), key0, key1);
-        wbuf[4 * lane] = ph.x;
-        wbuf[4 * lane + 1] = ph.y;
-        wbuf[4 * lane + 2] = ph.z;
-        wbuf[4 * lane + 3] = ph.w;
+        reinterpret_cast<uint4 *>(wbuf)[lane] = ph;
         wave_sync();
         int fin = 0;
         if (lane == 0) {
-            const long long kend = (b0 + kWave) * 4;
-            while (k < kend) {
-                const uint32_t w = wbuf[(int)(k - b0 * 4)];
-                const int y = (int)col[r0 + step_index<WT>(w, r0, r1, cw, guide)];
-                const int ny0 = rp[y], ny1 = rp[y + 1];
-                ++k;
-                recw[2 * xw] = y;  // Next pointer; becomes the parent when xw joins T
-                if (bits.test(y)) {
+            const uint32_t *wk = wbuf + (int)(k - b0 * 4);
+            int left = 4 * kWave - (int)(k - b0 * 4);
+            uint32_t w = *wk;
+            if constexpr (LDS) {
+                for (;;) {
+                    ++wk;
+                    const int y = (int)col[r0 + step_index<WT>(w, r0, r1, cw, guide)];
+                    w = *wk;  // the next step's word (past the last one: never used)
+                    --left;
+                    r0 = rp[y];
+                    r1 = rp[y + 1];
+                    const bool in = bits.test(y);
+                    next.set(xw, y);
+                    if (in) {
+                        fin = 1;
+                        break;
+                    }
+                    xw = y;
+                    if (left == 0) break;
+                }
+            } else {
+                if (e.x < 0) {
+                    e = edge[r0 + step_index<WT>(w, r0, r1, cw, guide)];
+                    ++wk;
+                    --left;
+                    w = *wk;
+                }
+                while (left > 0) {
+                    ++wk;
+                    const int4 en = edge[e.y + step_index<WT>(w, e.y, e.z, cw, guide)];
+                    const int t = bits.nbx(e.x);
+                    w = *wk;
+                    next.set(xw, e.x);
+                    if (t != kFree) {
+                        fin = 1;
+                        break;
+                    }
+                    --left;
+                    xw = e.x;
+                    e = en;
+                }
+            }
+            k = (b0 + kWave) * 4 - left;
+        }
+        wave_sync();  // the words are read before they are overwritten
+        k = uniform_ll(k);
+        if (__builtin_amdgcn_readfirstlane(fin)) return k;
+    }
+}
+
+// Retrace of the loop erasure from s0 along the Next pointers to the tree, and the branch's
+// records.  Lane 0 follows the pointers (one dependent load per vertex), up to 256 vertices at a
+// time into buf (LDS); the wave then writes their records, a lane each, from the tree's end of
+// the piece.  nba of a vertex is the nearest marked one closer to the tree, so the vertices from
+// a piece's last marked one on wait for the next piece that has one (or for the tree): they are
+// written with a placeholder and completed by lane 0 then.
+template <bool LDS, typename Next>
+__device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw, const int *__restrict__ bflag, int u,
+                        int s0, int *buf) {
+    constexpr int kPiece = 2 * kHashSlots;
+    const int lane = threadIdx.x;
+    int z = s0, pend = -1;  // pend: first vertex whose nba is not known yet
+    for (;;) {
+        int cnt = 0, fin = 0;
+        if (lane == 0) {
+            for (;;) {
+                const int nz = next.get(z);  // loaded beside the tree test
+                if (bits.test(z)) {
                     fin = 1;
                     break;
                 }
-                xw = y;
-                r0 = ny0;
-                r1 = ny1;
+                if (cnt == kPiece) break;
+                buf[cnt++] = z;
+                z = nz;
             }
         }
-        wave_sync();  // the words are read before they are overwritten
-        fin = __shfl(fin, 0, kWave);
-        const int klo = __shfl((int)(unsigned long long)k, 0, kWave);
-        const int khi = __shfl((int)((unsigned long long)k >> 32), 0, kWave);
-        k = (long long)(((unsigned long long)(unsigned)khi << 32) | (unsigned)klo);
-        if (fin) return k;
-    }
-}
-
-// The walk and retrace by one lane.  Graphs past the LDS bitmap read the edge entries {y,
-// row of y, B_u flag of y}: the entry of step k gives everything step k + 1 needs, so step
-// k + 1's entry is loaded together with the tree test of y (before its answer is known) and
-// each step waits for one load, not two in a row.  Graphs within it read the compact column
-// and row arrays, which stay in the L1.  Returns the walk's total step count.
-template <bool LDS, typename CT, bool WT>
-__device__ long long rewalk_commit(const TreeState<LDS> &bits, int *recw, const int *__restrict__ rp,
-                                   const CT *__restrict__ col, const int4 *__restrict__ edge,
-                                   const int4 *__restrict__ vrow, const double *__restrict__ cw,
-                                   const int *__restrict__ guide, const int *__restrict__ bflag, int s0, uint32_t wkey,
-                                   int x0, long long k0, uint32_t tlo, uint32_t thi, uint32_t key0, uint32_t key1) {
-    int xw = x0;
-    long long k = k0;
-    uint4 ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), wkey, tlo, thi), key0, key1);
-    if constexpr (LDS) {
-        int r0 = rp[x0], r1 = rp[x0 + 1];
-        for (;;) {
-            if ((k & 3) == 0) ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), wkey, tlo, thi), key0, key1);
-            const int q = (int)(k & 3);
-            const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
-            const int y = (int)col[r0 + step_index<WT>(w, r0, r1, cw, guide)];
-            const int ny0 = rp[y], ny1 = rp[y + 1];
-            ++k;
-            recw[2 * xw] = y;  // Next pointer; becomes the parent when xw joins T
-            if (bits.test(y)) break;
-            xw = y;
-            r0 = ny0;
-            r1 = ny1;
+        wave_sync();
+        cnt = __builtin_amdgcn_readfirstlane(cnt);
+        fin = __builtin_amdgcn_readfirstlane(fin);
+        z = __builtin_amdgcn_readfirstlane(z);
+        int carry = fin ? cv_of(z, load_nbx(recw, z)) : -1;
+        const int first = cnt ? buf[0] : z;
+        int last = -1;  // the piece's last marked vertex
+        for (int c = (cnt - 1) >> 6; c >= 0; --c) {  // cnt = 0: no piece
+            const int i = c * kWave + lane;
+            const bool mine = i < cnt;
+            const int v = mine ? buf[i] : 0, nx = mine ? (i + 1 < cnt ? buf[i + 1] : z) : 0;
+            const int mb = mine ? mark_bits(v, bflag[v], nx, bflag[nx]) : 0;
+            const uint64_t m = __ballot((mb & kMarkBit) != 0);
+            const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
+            const int up = __shfl(v, above ? __builtin_ctzll(above) : 0, kWave);
+            const int nba = above ? up : carry;
+            if (mine) {
+                recw[2 * v] = nx;
+                recw[2 * v + 1] = (nba >= 0 ? nba : u) | mb;
+                bits.set(v);
+            }
+            if (m) {
+                if (last < 0) last = __builtin_amdgcn_readlane(v, 63 - __builtin_clzll(m));
+                carry = __builtin_amdgcn_readlane(v, __builtin_ctzll(m));
+            }
         }
-        retrace_commit<true>(bits, recw, bflag, s0);
-        return k;
-    } else {
-    int4 e;  // entry of step k: the step from xw
-    {
-        const int4 v0 = vrow[x0];
-        const int q = (int)(k & 3);
-        const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
-        e = edge[v0.x + step_index<WT>(w, v0.x, v0.y, cw, guide)];
+        wave_sync();
+        if (pend >= 0 && carry >= 0) {
+            if (lane == 0)
+                for (int w = pend; w != first; w = recw[2 * w]) {
+                    const int old = load_nbx(recw, w);
+                    recw[2 * w + 1] = carry | (old & ~kVertexMask);
+                }
+            pend = -1;
+            wave_sync();
+        }
+        if (fin) return;
+        if (last >= 0) pend = last;
+        else if (pend < 0) pend = first;
     }
-    for (;;) {
-        const int y = e.x;
-        ++k;
-        if ((k & 3) == 0) ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), wkey, tlo, thi), key0, key1);
-        const int q = (int)(k & 3);
-        const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
-        const int4 en = edge[e.y + step_index<WT>(w, e.y, e.z, cw, guide)];  // step k from y
-        recw[2 * xw] = y;  // Next pointer; becomes the parent when xw joins T
-        if (bits.test(y)) break;
-        xw = y;
-        e = en;
-    }
-    retrace_commit<false>(bits, recw, bflag, s0);
-    return k;
-    }
-}
-
-template <typename T>
-__device__ __forceinline__ T sel4(int c, T a0, T a1, T a2, T a3) {
-    return c == 0 ? a0 : (c == 1 ? a1 : (c == 2 ? a2 : a3));
 }
 
 }  // namespace
 
 template <bool LDS, typename CT, bool WT, bool GL = false, bool BV = false>
 __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
-    // Reorder buffer.  Vertex IDs take the column type (16 bits when n <= 65536), so that
-    // with the tree bitmap a block of R-MAT scale 16 fits 18 to a CU.  A recorded step
-    // keeps the vertex and the step's edge bits (below), not the vertex's B_u flag word.
+    // Reorder buffer.  Vertex IDs take the column type (16 bits when n <= 65536): 14 bytes an
+    // entry, so that with the tree bitmap a block of R-MAT scale 16 fits 18 to a CU at 128
+    // entries.  A recorded step keeps the vertex and the step's edge bits (below).
     constexpr int kRobMax = rob_cap<LDS>();
+    struct alignas(2 * sizeof(CT)) Ends { CT s, cv; };       // start; chain value of the walk's end
+    struct alignas(4 * sizeof(CT)) Steps { CT v[kPathLds]; };  // x_1 .. x_4
     extern __shared__ uint32_t lds_bits[];
-    __shared__ CT rob_s[kRobMax], rob_cv[kRobMax];
-    __shared__ short rob_k[kRobMax];
-    __shared__ unsigned short rob_pb[kRobMax];  // edge bits of steps 1..kPathLds, 2 bits each
-    __shared__ CT rob_p[kRobMax][kPathLds];
-    __shared__ int htab[2 * kHashSlots];
-    // tree state in the records: the free-vertex words of the last scanned window (a window of
-    // 64 allocation words is read once, not once per allocation round)
-    __shared__ uint32_t win_fb[LDS ? 1 : kWave];
-    __shared__ int win_base;  // first word of that window, -1 before the first read
-    int *const hslot = htab;                     // first conflict table
-    int *const hslot2 = htab + kHashSlots;       // second conflict table
-    int *const br = htab;  // a long walk's branch (vertex | edge bits << 30) shares the tables'
-                           // storage; the slots are cleared again afterwards
-    static_assert(kPath + 1 <= 2 * kHashSlots, "the branch buffer fits the conflict tables");
-    static_assert(4 * kWave <= 2 * kHashSlots, "a re-walk's Philox words fit the conflict tables");
-    static_assert(kPathLds * 2 <= 16, "edge bits fit rob_pb");
+    __shared__ Ends rob_e[kRobMax];
+    __shared__ Steps rob_p[kRobMax];
+    __shared__ uint8_t rob_k[kRobMax];
+    __shared__ uint8_t rob_pb[kRobMax];  // edge bits of steps 1..kPathLds, 2 bits each
+    __shared__ alignas(16) int htab[2 * kHashSlots + 4];  // a word past the end is read, not used
+    __shared__ uint8_t win[kWin];  // free vertices of the window, as offsets
+    int *const hslot = htab;                // first conflict table
+    int *const hslot2 = htab + kHashSlots;  // second conflict table; together the one-lane walk's
+                                            // words and pieces (then cleared again)
+    static_assert(kPath + 1 <= 2 * kHashSlots && 4 * kWave <= 2 * kHashSlots, "a record, and the words, fit the tables");
+    static_assert(kPathLds * 2 <= 8, "edge bits fit rob_pb");
 
     const int lane = threadIdx.x;
     int *__restrict__ gpath = a.path + (long long)blockIdx.x * kSamplerPathSlot;
 
     // GL (small graphs, single-graph launches): the row pointers, B_u flags and 16-bit columns
     // are copied into LDS after the tree bitmap, once per block, so that walk steps (above all
-    // the one-lane re-walk of long walks) read LDS instead of the L1/L2.
+    // the one-lane walks) read LDS instead of the L1/L2.
     const int *lrp = nullptr, *lbf = nullptr;
     const CT *lcol = nullptr;
     if constexpr (GL) {
@@ -637,6 +644,10 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
 
     for (;;) {
     // ---------------------------------------------------------------- next tile
+    // The barrier keeps the wave together here: without a convergent operation between the
+    // lane-0 branch at the end of a tile and the one below, the compiler may join the two and
+    // send the other lanes into the next tile alone.
+    wave_sync();
     int tile = 0;
     if (lane == 0) tile = atomicAdd(a.queue, 1);
     tile = __builtin_amdgcn_readfirstlane(tile);
@@ -663,8 +674,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     TreeState<LDS> bits;
     if constexpr (LDS) bits.w = lds_bits;
     else bits.recw = recw;
-    constexpr int kWShift = TreeState<LDS>::kShift, kW = 1 << kWShift;
-    const int nw = (n + kW - 1) >> kWShift;  // allocation words
+    const NextRec next{recw};
     const int *__restrict__ bflag = GL ? lbf : g.bflag;
     const int4 *__restrict__ vrow = g.vrow;
     const int4 *__restrict__ edge = g.edge;  // set when the tree state is in global memory
@@ -674,15 +684,12 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     const double *__restrict__ cw = g.cw;
     const int *__restrict__ guide = g.guide;
 
-    wait_global();  // the previous tree's record writes have landed
     if constexpr (LDS) {
         for (int i = lane; i < nwords; i += kWave) bits.w[i] = 0u;
     } else {
         for (int i = lane; i < n; i += kWave) rec[i] = make_int2(-1, kFree);
-        wait_global();
     }
     for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
-    if (lane == 0) __hip_atomic_store(&win_base, -1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
     wave_sync();
     if constexpr (BV) {  // several roots (one per block of the block-split graph)
         for (int i = lane; i < a.nroots; i += kWave) {
@@ -696,106 +703,101 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     }
     wave_sync();
 
-    int head = 0, tail = 0, cursor = 0;  // wave-uniform
-    int mode = 0;                        // 0 idle, 1 speculative walk
-    int my_e = 0, x = 0, s = 0, sk = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
+    int head = 0, tail = 0;               // wave-uniform
+    int wend = 0, wpos = 0, wcnt = 0;     // the window is [wend - kWin, wend); list position and length
+    int mode = 0;                         // 0 idle, 1 speculative walk
+    int my_e = 0, x = 0, s = 0, wkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
     uint4 ph = make_uint4(0, 0, 0, 0);
     long long steps = 0, draws = 0;
 
-    for (;;) {
-        // ---------------------------------------------------------------- allocate
-        // The idle lane of rank r takes the r-th not-in-tree vertex at or after `cursor`
-        // (ascending start order).  A window of 64 bitmap words is scanned at once: every
-        // lane finds its own start by a binary search over the lanes' prefix counts and a
-        // select of the bit within that word, with no per-bit loop.
-        const uint64_t idle = __ballot(mode == 0);
-        const int want = min(__popcll(idle), rob - (tail - head));
-        const int rank = __popcll(idle & lanemask_lt());
-        int got = 0, mys = 0;
-        while (got < want && cursor < n) {
-            // With the tree state in the records, the window's words are read once and kept in
-            // LDS while the cursor stays inside it.  A vertex that joined the tree since the
-            // read still shows as free: it is allocated, and its walk finds it in the tree after
-            // one step and ends without a commit (as the sequential algorithm skips it).
-            int wbase = cursor >> kWShift;
-            uint32_t fb = 0u;
-            if constexpr (LDS) {
-                if (wbase + lane < nw) fb = ~bits.word(wbase + lane, n);
-            } else {
-                // win_base is written by lane 0 and read by every lane: atomic accesses
-                const int wb = __builtin_amdgcn_readfirstlane(
-                    __hip_atomic_load(&win_base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT));
-                if (wb >= 0 && wbase < wb + kWave) {
-                    wbase = wb;
-                } else {
-                    win_fb[lane] = wbase + lane < nw ? ~bits.word(wbase + lane, n) : 0u;
-                    if (lane == 0) __hip_atomic_store(&win_base, wbase, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
-                    wave_sync();
-                }
-                fb = win_fb[lane];  // this lane's own word
-            }
-            const int wi = wbase + lane;
-            if (wi < nw) {
-                fb &= (kW == 32 ? ~0u : (1u << kW) - 1u);
-                const int d = cursor - (wi << kWShift);  // vertices of this word before the cursor
-                if (d > 0) fb = d >= kW ? 0u : fb & (~0u << d);
-                if (wi == nw - 1 && (n & (kW - 1))) fb &= (1u << (n & (kW - 1))) - 1u;
-            } else {
-                fb = 0u;
-            }
-            const int c = __popc(fb);
-            const int incl = wave_scan_dpp(c);
-            const int excl = incl - c;
-            const int total = __shfl(incl, kWave - 1, kWave);
-            const int need = want - got;
-            const int j = rank - got;  // this lane's index among the window's free vertices
-            int L = 0;                 // the lane whose word holds free vertex j
-#pragma unroll
-            for (int st = kWave / 2; st >= 1; st >>= 1)
-                if (__shfl(excl, L + st, kWave) <= j) L += st;
-            const uint32_t wL = (uint32_t)__shfl((int)fb, L, kWave);
-            const int eL = __shfl(excl, L, kWave);
-            if (mode == 0 && j >= 0 && j < min(total, need)) mys = ((wbase + L) << kWShift) + select_bit(wL, j - eL);
-            if (total >= need) {
-                got = want;
-                cursor = __builtin_amdgcn_readfirstlane(__shfl(mys, select_bit64(idle, want - 1), kWave) + 1);
-            } else {
-                got += total;
-                cursor = (wbase + kWave) << kWShift;
-            }
+    // Marks the pending entries whose start has joined the tree (state 0).  With the LDS bitmap
+    // the commit tests the start itself; with the tree state in the records that would be a
+    // global load per batch, so the marks are brought up to date after a commit that added an
+    // inner vertex among the starts in flight, and a commit trusts them.
+    auto remark = [&]() {
+        for (int o = 0; o < tail - head; o += kWave) {
+            const int e = head + o + lane;
+            if (e < tail && bits.test((int)rob_e[e & robm].s)) rob_k[e & robm] = 0;
         }
-        if (got > 0) {
+        wave_sync();
+    };
+
+    for (int round = 0;; ++round) {
+        if constexpr (!LDS) {  // walks whose start has been absorbed end (before their slot is given away)
+            if (mode == 1 && rob_k[my_e & robm] == 0) mode = 0;
+        }
+        // ---------------------------------------------------------------- allocate
+        // The idle lane of rank r takes the r-th next vertex of the window's list of free vertices
+        // (ascending start order).  The list is built once per window, by a prefix sum over the
+        // lanes' four vertices; a vertex that joined the tree since is found by a test here and
+        // takes an entry that commits nothing (the sequential algorithm skips it).  Few idle
+        // lanes are filled every fourth round only: walks that start together need their Philox
+        // block in the same round, so in long-walk phases three rounds of four run without one.
+        const uint64_t idle = __ballot(mode == 0);
+        const int want = min((int)__popcll(idle), rob - (tail - head));
+        if (want > 0 && (4 * want >= min(rob, kWave) || (round & 3) == 0 || head == tail) && (wpos < wcnt || wend < n)) {
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
+                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
+            int got = 0, mys = 0;
+            do {
+                if (wpos == wcnt) {
+                    if (wend >= n) break;
+                    uint32_t fb = bits.free4(wend, lane, n);
+                    const int left = n - (wend + 4 * lane);
+                    if (left < 4) fb &= left > 0 ? (1u << left) - 1u : 0u;
+                    const int incl = wave_scan_dpp(__popc(fb));
+                    int at = incl - __popc(fb);
+#pragma unroll
+                    for (int b = 0; b < 4; ++b)
+                        if ((fb >> b) & 1u) win[at++] = (uint8_t)(4 * lane + b);
+                    wcnt = __builtin_amdgcn_readlane(incl, kWave - 1);
+                    wpos = 0;
+                    wend += kWin;
+                    wave_sync();
+                    continue;
+                }
+                const int take = min(want - got, wcnt - wpos);
+                const int j = rank - got;  // this lane's place in this take
+                if (mode == 0 && j >= 0 && j < take) mys = wend - kWin + (int)win[wpos + j];
+                got += take;
+                wpos += take;
+            } while (got < want);
             if (mode == 0 && rank < got) {
                 my_e = tail + rank;
                 s = mys;
-                if constexpr (BV) sk = a.skey[s];
+                wkey = s;
+                if constexpr (BV) wkey = a.skey[s];
                 x = s;
                 k = 0;
-                mode = 1;
+                bool gone;  // joined the tree since the window was read
                 if constexpr (LDS) {
                     r0 = rp[s];
                     r1 = rp[s + 1];
                     fx = bflag[s];
+                    gone = bits.test(s);
                 } else {  // the vertex entry {row begin, row end, B_u flag}: one load
                     const int4 vr = vrow[s];
+                    gone = bits.test(s);
                     r0 = vr.x;
                     r1 = vr.y;
                     fx = vr.z;
                 }
                 pbits = 0;
+                mode = gone ? 0 : 1;
                 const int sl = my_e & robm;
-                rob_s[sl] = (CT)s;
-                rob_k[sl] = (short)kWalking;
+                rob_e[sl].s = (CT)s;
+                rob_k[sl] = (uint8_t)(gone ? 0 : kWalking);
             }
             tail += got;
         }
-        if (head == tail && cursor >= n) break;
+        if (head == tail && wpos == wcnt && wend >= n) break;
         wave_sync();
 
         // ---------------------------------------------------------------- one walk step
         if (mode == 1) {
+            const int sl = my_e & robm;
             if ((k & 3) == 0)
-                ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), (uint32_t)(BV ? sk : s), tlo, thi), g.key0, g.key1);
+                ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), (uint32_t)wkey, tlo, thi), g.key0, g.key1);
             const int q = k & 3;
             const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
             // y, its B_u flag and its row bounds.  With the tree bitmap in LDS (small graphs,
@@ -814,12 +816,13 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 ny1 = ey.z;
             }
             // y's tree membership, with the chain value when the walk ends here
-            bool in;
+            bool in, gone = false;
             int cvy = 0;
             if constexpr (LDS) {
                 in = bits.test(y);
+                gone = bits.test(s);  // the start has been absorbed: the walk never counts
                 if (in) {
-                    cvy = recw[2 * y + 1];
+                    cvy = load_nbx(recw, y);
                 } else {
                     ny0 = rp[y];
                     ny1 = rp[y + 1];
@@ -832,290 +835,320 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
             if (in) cvy = cv_of(y, cvy);
             ++k;
             ++draws;
-            const int sl = my_e & robm;
             const int eb = edge_bits(x, fx, y, fy);
             if (k <= kPathLds) {
-                rob_p[sl][k - 1] = (CT)y;
+                rob_p[sl].v[k - 1] = (CT)y;
                 pbits |= eb << (2 * (k - 1));
-                rob_pb[sl] = (unsigned short)pbits;
+                rob_pb[sl] = (uint8_t)pbits;
             } else {
-                gpath[sl * (kPath - kPathLds) + (k - 1 - kPathLds)] = y | (eb << 30);
+                gpath[sl * kSamplerPathGlobal + (k - 1 - kPathLds)] = y | (eb << 30);
             }
-            if (in) { rob_k[sl] = (short)k; rob_cv[sl] = (CT)cvy; mode = 0; }
-            else if (k == kPath) { rob_k[sl] = (short)kOverflow; mode = 0; }
-            else if (bits.test(s)) { rob_k[sl] = 0; mode = 0; }  // s absorbed: never walks
+            if (gone) { rob_k[sl] = 0; mode = 0; }
+            else if (in) { rob_k[sl] = (uint8_t)k; rob_e[sl].cv = (CT)cvy; mode = 0; }
+            else if (k == kPath) { rob_k[sl] = (uint8_t)kOverflow; mode = 0; }
             else { x = y; fx = fy; r0 = ny0; r1 = ny1; }
         }
         wave_sync();
 
         // ---------------------------------------------------------------- in-order commit
         while (head < tail) {
-            const int hs = rob_k[head & robm];
-            if (hs == kWalking) break;
-            if (hs == kContinue || hs == kRewalk) {
-                // lane 0 runs the sequential algorithm for this start against the current tree
-                // (all earlier starts are committed).  An overflowed walk whose record misses
-                // the tree resumes after its record: the recorded steps become Next pointers.
-                const int sl = head & robm;
-                const int s0 = (int)rob_s[sl];
-                if (!bits.test(s0)) {
-                    uint32_t wk0 = (uint32_t)s0;  // the walk's Philox key
-                    if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
-                    if (hs == kContinue) wait_global();  // recorded steps stored by another lane
-                    int xs = s0;
-                    const long long k0 = hs == kContinue ? kPath : 0;
-                    if (lane == 0 && hs == kContinue) {
-#pragma unroll 8
-                        for (int j = 1; j <= kPath; ++j) {
-                            const int xj = j <= kPathLds ? (int)rob_p[sl][j - 1]
-                                                         : gpath[sl * (kPath - kPathLds) + (j - 1 - kPathLds)] & kVertexMask;
-                            recw[2 * xs] = xj;
-                            xs = xj;
-                        }
-                    }
-                    long long kk = 0;
-                    if constexpr (GL) {
-                        // the conflict tables (all free now) hold the walk's Philox words meanwhile
-                        xs = __shfl(xs, 0, kWave);
-                        kk = walk_next_wave<CT, WT>(bits, recw, rp, col, cw, guide, wk0, xs, k0, tlo, thi, g.key0,
-                                                    g.key1, reinterpret_cast<uint32_t *>(htab));
-                        for (int i = lane; i < 4 * kWave; i += kWave) htab[i] = kWave;
-                        wave_sync();
-                        if (lane == 0) retrace_commit<true>(bits, recw, bflag, s0);
-                    } else {
-                        if (lane == 0)
-                            kk = rewalk_commit<LDS, CT, WT>(bits, recw, rp, col, edge, vrow, cw, guide, bflag, s0, wk0,
-                                                            xs, k0, tlo, thi, g.key0, g.key1);
-                    }
-                    if (lane == 0) {
-                        steps += kk;
-                        draws += kk - k0;
-                    }
-                }
-                ++head;
-                wave_sync();
-                continue;
-            }
             const int idx = head + lane;
-            const int sk = idx < tail ? (int)rob_k[idx & robm] : kWalking;
-            const uint64_t okm = __ballot(sk >= 0 && sk <= kPathLds);
+            const int sl = idx & robm;
+            const int sk = idx < tail ? (int)rob_k[sl] : kWalking;
+            const uint64_t okm = __ballot(sk <= kPathLds);
             const int r = (~okm == 0ull) ? kWave : __builtin_ctzll(~okm);
             if (r > 0) {
-                // Batch commit of the done entries head .. head+r-1 (walks of <= kPathLds steps), one
-                // lane each, all planned against the current tree T0.  Entry j's plan is what
-                // the sequential algorithm does unless an earlier entry of the batch adds a
-                // vertex j has read (its start or a vertex before its truncation point); the
-                // plan's written vertices go into the two minimum-writer tables, and the batch
-                // commits up to the first lane that reads a vertex whose two slots both hold a
-                // smaller lane (collisions only shorten the batch).  The head never conflicts.
-                const bool act = lane < r;
-                const int sl = idx & robm;
-                const int K = act ? sk : 0;
-                // xv[j] = x_j; bits j = edge bits of the step x_{j-1} -> x_j
-                int xv[kPathLds + 1];
-                xv[0] = act ? (int)rob_s[sl] : -1;
-                const int pb = act ? (int)rob_pb[sl] : 0;
-#pragma unroll
-                for (int j = 1; j <= kPathLds; ++j) xv[j] = (j <= K) ? (int)rob_p[sl][j - 1] : -1;
-                const bool live = K > 0 && !bits.test(act ? xv[0] : 0);
-                int istar = kPathLds + 1;
-#pragma unroll
-                for (int j = kPathLds; j >= 1; --j)
-                    if (live && j <= K && bits.test(xv[j])) istar = j;
-                const bool bad = live && istar > K;  // cannot happen for a recorded walk
-                // loop erasure in registers: keep = positions on the erased branch
-                unsigned keep = 0u;
-                if (live && !bad) {
-                    int b = xv[0];
-#pragma unroll
-                    for (int step = 0; step <= kPathLds; ++step) {
-                        int q = -1;
-#pragma unroll
-                        for (int j = 0; j <= kPathLds; ++j)
-                            if (j < istar && xv[j] == b) q = j;
-                        if (q < 0) break;
-                        keep |= 1u << q;
-                        if (q + 1 >= istar) break;
-                        int nb = -1;
-#pragma unroll
-                        for (int j = 1; j <= kPathLds; ++j)
-                            if (j == q + 1) nb = xv[j];
-                        b = nb;
-                    }
+                // Batch commit of the done entries head .. head+r-1, one lane each, all planned
+                // against the current tree T0.  Entry j's plan is what the sequential algorithm
+                // does unless an earlier entry of the batch adds a vertex j has read.
+                const Ends en = rob_e[sl];
+                const Steps st = rob_p[sl];
+                const int pb = (int)rob_pb[sl];
+                const int s0 = (int)en.s;
+                int carry = (int)en.cv;
+                int K = lane < r ? sk : 0;
+                if constexpr (LDS) {
+                    if (K > 0 && bits.test(s0)) K = 0;  // absorbed
                 }
-                const uint64_t badm = __ballot(bad);
-                if (badm & 1ull) {  // never expected: fall back to the exact re-walk
-                    rob_k[head & robm] = (short)kRewalk;
+                const uint64_t multi = __ballot(K >= 2);
+                const int x1 = (int)st.v[0];
+                if (multi == 0ull) {  // single steps only: no two of them interfere
+                    if (K > 0) {
+                        rec[s0] = make_int2(x1, carry | (int)((unsigned)pb << 30));
+                        bits.set(s0);
+                        ++steps;
+                    }
+                    head += r;
                     wave_sync();
                     continue;
                 }
-                if (live && !bad) {
-#pragma unroll
-                    for (int j = 0; j <= kPathLds; ++j)
-                        if ((keep >> j) & 1u) {
-                            atomicMin(&hslot[hash_slot<LDS>(xv[j])], lane);
-                            atomicMin(&hslot2[hash_slot2<LDS>(xv[j])], lane);
+                const int x2 = (int)st.v[1], x3 = (int)st.v[2], x4 = (int)st.v[3];
+                const bool any3 = __ballot(K >= 3) != 0ull, any4 = __ballot(K >= 4) != 0ull;  // uniform
+                // truncation at the first vertex in T0, whose chain value is then its own
+                int istar = K, ya = K >= 2 ? (K == 2 ? x2 : (K == 3 ? x3 : x4)) : x1;
+                {
+                    int n1 = kFree, n2 = kFree, n3 = kFree;
+                    if constexpr (LDS) {
+                        if (K >= 2 && bits.test(x1)) n1 = 0;
+                        if (any3 && K >= 3 && bits.test(x2)) n2 = 0;
+                        if (any4 && K >= 4 && bits.test(x3)) n3 = 0;
+                    } else {
+                        if (K >= 2) n1 = bits.nbx(x1);
+                        if (K >= 3) n2 = bits.nbx(x2);
+                        if (K >= 4) n3 = bits.nbx(x3);
+                    }
+                    int nt = kFree;
+                    if (n3 != kFree) { istar = 3; ya = x3; nt = n3; }
+                    if (n2 != kFree) { istar = 2; ya = x2; nt = n2; }
+                    if (n1 != kFree) { istar = 1; ya = x1; nt = n1; }
+                    if constexpr (LDS) {
+                        const bool need = istar < K;  // ya joined T after the walk passed it
+                        if (__ballot(need)) {
+                            if (need) carry = cv_of(ya, load_nbx(recw, ya));
                         }
+                    } else {
+                        if (nt != kFree) carry = cv_of(ya, nt);
+                    }
                 }
-                wave_sync();
-                bool conflict = bad;
-                if (live && !bad) {
-#pragma unroll
-                    for (int j = 0; j <= kPathLds; ++j)
-                        if (j < istar && hslot[hash_slot<LDS>(xv[j])] < lane && hslot2[hash_slot2<LDS>(xv[j])] < lane)
-                            conflict = true;
+                // loop erasure: keep = positions on the erased branch (neighbours on a walk differ)
+                unsigned keep = (1u << istar) - 1u;
+                if (any3) {
+                    if (istar >= 3 && x2 == s0) keep &= ~3u;
+                    if (istar == 4) {
+                        if (x3 == s0) keep = 8u;
+                        else if (x3 == x1 && x2 != s0) keep = 9u;
+                    }
                 }
-                wave_sync();
-                if (live && !bad) {
-#pragma unroll
-                    for (int j = 0; j <= kPathLds; ++j)
-                        if ((keep >> j) & 1u) {
-                            hslot[hash_slot<LDS>(xv[j])] = kWave;
-                            hslot2[hash_slot2<LDS>(xv[j])] = kWave;
-                        }
+                // an inner vertex (read, not in T0) among the starts in flight?
+                const int slo = __builtin_amdgcn_readfirstlane(s0), shi = wend - 1;
+                bool inr = istar >= 2 && x1 >= slo && x1 <= shi;
+                if (any3) inr = inr || (istar >= 3 && x2 >= slo && x2 <= shi) || (istar >= 4 && x3 >= slo && x3 <= shi);
+                const bool starts = __ballot(inr) != 0ull;
+                int jstar = r;
+                if (starts || (multi & (multi - 1)) != 0ull) {
+                    auto each = [&](auto f) {  // the vertices this lane reads and may add
+                        if (starts && K > 0) f(s0);
+                        if (istar >= 2) f(x1);
+                        if (any3 && istar >= 3) f(x2);
+                        if (any4 && istar >= 4) f(x3);
+                    };
+                    each([&](int v) {
+                        atomicMin(&hslot[hash_slot<LDS>(v)], lane);
+                        atomicMin(&hslot2[hash_slot2<LDS>(v)], lane);
+                    });
+                    wave_sync();
+                    bool conflict = false;
+                    each([&](int v) {
+                        if (hslot[hash_slot<LDS>(v)] < lane && hslot2[hash_slot2<LDS>(v)] < lane) conflict = true;
+                    });
+                    wave_sync();
+                    each([&](int v) {
+                        hslot[hash_slot<LDS>(v)] = kWave;
+                        hslot2[hash_slot2<LDS>(v)] = kWave;
+                    });
+                    const uint64_t cm = __ballot(conflict);  // never the head: no lane is below it
+                    jstar = cm ? __builtin_ctzll(cm) : r;
                 }
-                const uint64_t cm = __ballot(conflict);
-                const int jstar = cm ? __builtin_ctzll(cm) : r;
-                const bool commit = live && !bad && lane < jstar;
-                int ya = -1;
-#pragma unroll
-                for (int j = 1; j <= kPathLds; ++j)
-                    if (j == istar) ya = xv[j];
-                int carry = commit ? (int)rob_cv[sl] : 0;
-                const bool need = commit && istar < K;  // ya joined T after the walk passed it
-                if (__ballot(need)) {
-                    wait_global();
-                    if (need) carry = cv_of(ya, load_nbx(recw, ya));
-                }
-                if (commit) {
+                if (K > 0 && lane < jstar) {
                     // a kept x_j is the last visit of its vertex, so its tree edge is the
                     // recorded step x_j -> x_{j+1}, whose edge bits are step j+1's
                     int pv = ya;
-#pragma unroll
-                    for (int j = kPathLds; j >= 0; --j) {
+                    auto put = [&](int j, int v) {
                         if ((keep >> j) & 1u) {
-                            const int v = xv[j];
-                            const int mb = (int)((unsigned)(pb >> (2 * j)) << 30);  // j + 1 <= kPathLds
-                            const int cv = mb ? v : carry;
+                            const int mb = (int)((unsigned)(pb >> (2 * j)) << 30);
                             rec[v] = make_int2(pv, carry | mb);
                             bits.set(v);
-                            carry = cv;
+                            carry = mb ? v : carry;
                             pv = v;
                         }
-                    }
+                    };
+                    if (any4) put(3, x3);
+                    if (any3) put(2, x2);
+                    put(1, x1);
+                    put(0, s0);
                     steps += istar;
                 }
                 head += jstar;
                 wave_sync();
+                if constexpr (!LDS) {
+                    if (__ballot(inr && lane < jstar)) remark();
+                }
                 continue;
             }
-            // head: recorded walk x_0..x_K, kPathLds < K <= 255 (an overflowed walk: its whole
-            // record, K = 255), committed cooperatively; lane j holds x_{j+64c} and the edge bits
-            // of the step into it, c = 0..3
-            const int sl = head & robm;
-            const int s0 = (int)rob_s[sl];
-            if (!bits.test(s0)) {
-                const bool ended = hs >= 0;  // the walk reached the tree it saw
-                const int K = ended ? hs : kPath;
-                int xv[4] = {-1, -1, -1, -1}, xb[4] = {0, 0, 0, 0};
-                if (lane == 0) {
-                    xv[0] = s0;
-                } else if (lane <= min(K, kPathLds)) {
-                    xv[0] = (int)rob_p[sl][lane - 1];
-                    xb[0] = ((int)rob_pb[sl] >> (2 * (lane - 1))) & 3;
-                }
-                if (K > kPathLds) {
-                    wait_global();  // steps beyond the LDS part were stored by other lanes
-                    int e[4] = {0, 0, 0, 0};
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int j = c * kWave + lane;
-                        if (j > kPathLds && j <= K) e[c] = gpath[sl * (kPath - kPathLds) + (j - 1 - kPathLds)];
-                    }
-                    consume(e[0], e[1], e[2], e[3]);
-#pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        const int j = c * kWave + lane;
-                        if (j > kPathLds && j <= K) {
-                            xv[c] = e[c] & kVertexMask;
-                            xb[c] = (int)((unsigned)e[c] >> 30);
-                        }
-                    }
-                }
-                int istar = -1;
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    if (istar < 0 && c * kWave <= K) {
-                        const int j = c * kWave + lane;
-                        const bool valid = j >= 1 && j <= K;
-                        const uint64_t im = __ballot(valid && bits.test(valid ? xv[c] : 0));
-                        if (im) istar = c * kWave + __builtin_ctzll(im);
-                    }
-                }
-                if (istar < 0) {
-                    // an overflowed walk that still misses the tree resumes after its record; for
-                    // a finished walk this cannot happen, and the re-walk keeps the commit exact
-                    rob_k[sl] = (short)(ended ? kRewalk : kContinue);
-                    wave_sync();
+            const int hs = __builtin_amdgcn_readfirstlane(sk);
+            if (hs == kWalking) break;
+            const int hsl = head & robm;
+            const int s0 = __builtin_amdgcn_readfirstlane((int)rob_e[hsl].s);
+            if constexpr (LDS) {
+                if (bits.test(s0)) {  // absorbed
+                    ++head;
                     continue;
                 }
-                // loop erasure: from b, jump past b's last visit before istar
-                int b = s0, blen = 0, ya = -1;
-                for (;;) {
-                    int qlast = -1;
+            }
+            // the head's recorded walk x_0..x_K, kPathLds < K <= kPath (an overflowed walk: its
+            // whole record, K = kPath): lane j holds x_{j+64c} and the edge bits of the step into it
+            const bool ended = hs <= kPath;  // the walk reached the tree it saw
+            const int K = ended ? hs : kPath;
+            int xv[4] = {-1, -1, -1, -1}, xb[4] = {0, 0, 0, 0};
+            if (hs != kRewalk) {
 #pragma unroll
-                    for (int c = 3; c >= 0; --c) {
-                        if (qlast < 0 && c * kWave < istar) {
-                            const uint64_t mm = __ballot(c * kWave + lane < istar && xv[c] == b);
-                            if (mm) qlast = c * kWave + 63 - __builtin_clzll(mm);
-                        }
-                    }
-                    if (qlast < 0) break;  // unreachable for a recorded walk; never spin
-                    const int nq = qlast + 1, cq = nq >> 6, lq = nq & 63;
-                    const int nx = __shfl(sel4(cq, xv[0], xv[1], xv[2], xv[3]), lq, kWave);
-                    const int nb = __shfl(sel4(cq, xb[0], xb[1], xb[2], xb[3]), lq, kWave);  // edge b -> nx
-                    if (lane == 0) {
-                        br[blen] = b | (nb << 30);
-                        bits.set(b);
-                    }
-                    ++blen;
-                    if (nq == istar) {
-                        ya = nx;
-                        break;
-                    }
-                    b = nx;
+                for (int c = 0; c < 4; ++c) {
+                    const int j = c * kWave + lane;
+                    if (j > kPathLds && j <= K) xv[c] = gpath[hsl * kSamplerPathGlobal + (j - 1 - kPathLds)];
                 }
-                wave_sync();
-                if (ya >= 0) {
-                    // records of the branch b_0 = s .. b_{blen-1}, attached to ya
-                    int carry;
-                    if (ended && istar == K) {
-                        carry = (int)rob_cv[sl];
-                    } else {  // ya joined T after the walk passed it: its record was written since
-                        wait_global();
-                        carry = cv_of(ya, load_nbx(recw, ya));
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const int j = c * kWave + lane;
+                    if (j > kPathLds && j <= K) {
+                        xb[c] = (int)((unsigned)xv[c] >> 30);
+                        xv[c] &= kVertexMask;
                     }
-                    for (int c = (blen - 1) >> 6; c >= 0; --c) {
-                        const int i = c * kWave + lane;
-                        const bool mine = i < blen;
-                        const int be = mine ? br[i] : 0;
-                        const int bi = be & kVertexMask;
-                        const int nexti = mine ? (i + 1 < blen ? br[i + 1] & kVertexMask : ya) : 0;
-                        const int mb = be & ~kVertexMask;  // the edge bits, in the record's flag position
-                        const bool mk = mb != 0;
-                        const uint64_t m = __ballot(mk);
-                        const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
-                        const int nba = above ? br[c * kWave + __builtin_ctzll(above)] & kVertexMask : carry;
-                        if (mine) rec[bi] = make_int2(nexti, nba | mb);
-                        carry = m ? br[c * kWave + __builtin_ctzll(m)] & kVertexMask : carry;
-                    }
-                    if (lane == 0) steps += istar;
+                }
+                if (lane == 0) {
+                    xv[0] = s0;
+                } else if (lane <= kPathLds) {
+                    xv[0] = (int)rob_p[hsl].v[lane - 1];
+                    xb[0] = ((int)rob_pb[hsl] >> (2 * (lane - 1))) & 3;
                 }
             }
-            wave_sync();
-            for (int i = lane; i < kPath + 1; i += kWave) htab[i] = kWave;
+            if (hs == kContinue || hs == kRewalk) {
+                // lane 0 runs the sequential algorithm for this start against the current tree
+                // (all earlier starts are committed).  An overflowed walk whose record misses
+                // the tree resumes after its record: the recorded steps become Next pointers.
+                const long long k0 = hs == kContinue ? kPath : 0;
+                int xs = s0;
+                if (hs == kContinue) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (c * kWave + lane <= kPath) htab[c * kWave + lane] = xv[c];
+                    wave_sync();
+                    if (lane == 0) {
+#pragma unroll 10
+                        for (int j = 0; j < kPath; ++j) next.set(htab[j], htab[j + 1]);
+                    }
+                    xs = htab[kPath];
+                    wave_sync();
+                }
+                uint32_t wk0 = (uint32_t)s0;  // the walk's Philox key
+                if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
+                const long long kk = walk_next<LDS, CT, WT>(bits, next, rp, col, edge, vrow, cw, guide, wk0, xs, k0, tlo, thi,
+                                                            g.key0, g.key1, reinterpret_cast<uint32_t *>(htab));
+                retrace<LDS>(bits, next, recw, bflag, u, s0, htab);
+                for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
+                if (lane == 0) {
+                    steps += kk;
+                    draws += kk - k0;
+                }
+                ++head;
+                wave_sync();
+                if constexpr (!LDS) remark();
+                continue;
+            }
+            // truncation; with the tree state in the records the test's load is ya's chain value too
+            int istar = -1, nt = kFree;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (c * kWave <= K && istar < 0) {  // uniform
+                    const int j = c * kWave + lane;
+                    const bool valid = j >= 1 && j <= K;
+                    int nb = kFree;
+                    if (valid) {
+                        if constexpr (LDS) nb = bits.test(xv[c]) ? 0 : kFree;
+                        else nb = bits.nbx(xv[c]);
+                    }
+                    const uint64_t im = __ballot(nb != kFree);
+                    if (im) {
+                        istar = c * kWave + __builtin_ctzll(im);
+                        nt = __builtin_amdgcn_readlane(nb, __builtin_ctzll(im));
+                    }
+                }
+            }
+            if (istar < 0) {
+                // an overflowed walk that still misses the tree resumes after its record; for
+                // a finished walk this cannot happen, and the re-walk keeps the commit exact
+                rob_k[hsl] = (uint8_t)(ended ? kRewalk : kContinue);
+                wave_sync();
+                continue;
+            }
+            auto xat = [&](int j) {  // x_j, j uniform
+                const int l = j & (kWave - 1);
+                const int c = j >> 6;
+                int v = __builtin_amdgcn_readlane(xv[0], l);
+                if (c == 1) v = __builtin_amdgcn_readlane(xv[1], l);
+                if (c == 2) v = __builtin_amdgcn_readlane(xv[2], l);
+                if (c == 3) v = __builtin_amdgcn_readlane(xv[3], l);
+                return v;
+            };
+            const int ya = xat(istar);
+            int carry;
+            if constexpr (LDS) carry = ended && istar == K ? (int)rob_e[hsl].cv : cv_of(ya, load_nbx(recw, ya));
+            else carry = cv_of(ya, nt);
+            carry = __builtin_amdgcn_readfirstlane(carry);
+            // loop erasure: from b, jump past b's last visit before istar; kept positions per chunk
+            uint64_t kept[4] = {0ull, 0ull, 0ull, 0ull};
+            if (istar <= kWave) {
+                const uint64_t before = istar == kWave ? ~0ull : (1ull << istar) - 1ull;
+                int q = 0;
+                do {
+                    const int b = __builtin_amdgcn_readlane(xv[0], q);
+                    const uint64_t mm = __ballot(xv[0] == b) & before;  // holds q
+                    q = 63 - __builtin_clzll(mm);
+                    kept[0] |= 1ull << q;
+                    ++q;
+                } while (q < istar);
+            } else {
+                int q = 0;
+                do {
+                    const int b = xat(q);
+                    int last = q;  // b's last visit: at q or later
+#pragma unroll
+                    for (int c = 3; c >= 0; --c) {
+                        if (last == q && c * kWave < istar) {
+                            const uint64_t mm = __ballot(xv[c] == b && c * kWave + lane < istar);
+                            if (mm) {
+                                const int p = c * kWave + 63 - __builtin_clzll(mm);
+                                if (p > last) last = p;
+                            }
+                        }
+                    }
+#pragma unroll
+                    for (int c = 0; c < 4; ++c)
+                        if (last >> 6 == c) kept[c] |= 1ull << (last & 63);
+                    q = last + 1;
+                } while (q < istar);
+            }
+            // records of the kept positions, attached to ya: x_q's parent is x_{q+1}, its flags the
+            // edge bits of step q+1, its nba the next marked kept vertex
+            const int shi = wend - 1;
+            bool inr = false;
+#pragma unroll
+            for (int c = 3; c >= 0; --c) {
+                if (c * kWave < istar) {  // uniform
+                    const int hix = c < 3 ? __builtin_amdgcn_readlane(xv[c < 3 ? c + 1 : 3], 0) : 0;
+                    const int hib = c < 3 ? __builtin_amdgcn_readlane(xb[c < 3 ? c + 1 : 3], 0) : 0;
+                    int nx = __shfl_down(xv[c], 1, kWave), nb = __shfl_down(xb[c], 1, kWave);
+                    if (lane == kWave - 1) {
+                        nx = hix;
+                        nb = hib;
+                    }
+                    const bool mine = (kept[c] >> lane) & 1ull;
+                    const uint64_t m = __ballot(mine && nb != 0);
+                    const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
+                    const int up = __shfl(xv[c], above ? __builtin_ctzll(above) : 0, kWave);
+                    if (mine) {
+                        rec[xv[c]] = make_int2(nx, (above ? up : carry) | (nb << 30));
+                        bits.set(xv[c]);
+                        inr = inr || (xv[c] > s0 && xv[c] <= shi);
+                    }
+                    if (m) carry = __builtin_amdgcn_readlane(xv[c], __builtin_ctzll(m));
+                }
+            }
+            if (lane == 0) steps += istar;
             ++head;
             wave_sync();
+            if constexpr (!LDS) {
+                if (__ballot(inr)) remark();
+            }
         }
     }
 
