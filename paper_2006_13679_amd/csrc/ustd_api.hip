@@ -2018,17 +2018,23 @@ int ustd_tree_counts(const ustd_problem *prob, const int32_t *d_parents, int64_t
     // not a spanning tree rooted at the pivot returns USTD_EINVAL with d_counts unchanged.
     long long *acc = at<long long>(c.ws, c.L.off_counts);
     HIP_TRY(launch_fill_i64(c.L.n, acc, 0, c.st));
-    for (long long b0 = 0; b0 < tree_count; b0 += c.L.Kiv) {
-        const int cnt = (int)std::min<long long>(c.L.Kiv, tree_count - b0);
+    // One block builds a tree's records, so a launch takes as many trees as fit: nothing is sampled
+    // here, and the record pool, the sampler's path slots and the builder's own scratch lie side by
+    // side in the workspace.  They hold the records of a launch's trees, then the scratch (at least
+    // Kiv trees' worth; 16 trees a launch left 240 of 256 compute units idle).
+    const long long room = c.L.off_part - c.L.off_rec, rec_bytes = c.L.rec_stride * 8, scr_bytes = c.L.scr_stride * 4;
+    const long long per = std::min<long long>(std::max<long long>(room / (rec_bytes + scr_bytes), c.L.Kiv), c.L.K);
+    for (long long b0 = 0; b0 < tree_count; b0 += per) {
+        const int cnt = (int)std::min<long long>(per, tree_count - b0);
         IntervalArgs ia{};
         ia.n = c.L.n;
         ia.u = c.pivot;
         ia.par = d_parents + b0 * c.L.n;
         ia.par_stride = c.L.n;
-        ia.scratch = at<int>(c.ws, c.L.off_scr);
-        ia.scratch_stride = c.L.scr_stride;
         ia.rec = at<int2>(c.ws, c.L.off_rec);
         ia.rec_stride = c.L.rec_stride;
+        ia.scratch = at<int>(c.ws, c.L.off_rec + cnt * rec_bytes);
+        ia.scratch_stride = c.L.scr_stride;
         ia.bflag = at<int>(c.ws, c.L.off_bflag);
         ia.err = &c.misc->err_interval;
         HIP_TRY(launch_tree_records(ia, cnt, c.st));

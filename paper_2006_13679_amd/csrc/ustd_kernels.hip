@@ -1169,7 +1169,10 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
 // and writes the records top-down along that order, so a vertex's parent is done first.
 // A parent array that is not a spanning tree rooted at u sets err |= 64.
 // ======================================================================================
-constexpr int kIvThreads = 256;
+// A block works through its tree in passes and levels, each bounded by the latency of its loads and
+// barriers: 1024 threads take four times the vertices of a pass at once (256 threads: 880 us a
+// launch at 21,000 vertices).
+constexpr int kIvThreads = 1024;
 
 __global__ __launch_bounds__(kIvThreads) void tree_records_kernel(IntervalArgs a) {
     __shared__ int sh[kIvThreads / kWave + 1];
