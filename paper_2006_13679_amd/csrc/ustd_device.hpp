@@ -82,11 +82,12 @@ __device__ __forceinline__ double block_sum(double v, double *sh) {
     return s;
 }
 
-// Block-wide sum of one value per thread in a fixed order (deterministic for a fixed blockDim);
-// `sh` holds at least blockDim.x / 64 values.  Contains two barriers.
+// Block-wide sum of one value per thread in a fixed order (deterministic for a fixed number of
+// threads nt: the block, or its first nt threads when the others have left the kernel);
+// `sh` holds at least nt / 64 values.  Contains two barriers.
 template <typename T>
-__device__ __forceinline__ T block_sum_t(T v, T *sh) {
-    const int l = lane_id(), w = threadIdx.x / kWave, nw = blockDim.x / kWave;
+__device__ __forceinline__ T block_sum_t(T v, T *sh, int nt) {
+    const int l = lane_id(), w = threadIdx.x / kWave, nw = nt / kWave;
     v = wave_sum(v);
     if (l == 0) sh[w] = v;
     __syncthreads();
@@ -94,6 +95,10 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
     for (int i = 0; i < nw; ++i) s += sh[i];
     __syncthreads();
     return s;
+}
+template <typename T>
+__device__ __forceinline__ T block_sum_t(T v, T *sh) {
+    return block_sum_t<T>(v, sh, (int)blockDim.x);
 }
 
 }  // namespace ustd

@@ -134,7 +134,8 @@ struct SolveScalars {
     double delta2;
     int iter, maxit;
     int done;        // later kernels of the solve are no-ops
-    int upd;         // a reliable update is due in this iteration
+    int upd;         // a reliable update is due: this slot's fold, the next slot's true residual
+    int skip;        // this slot's product was the true residual: no iteration
     int updates;     // reliable updates taken
     int stalls;      // consecutive updates whose true residual fell by less than 2x
     int broke;       // p.q was not positive (breakdown): the next update ends the solve
@@ -218,14 +219,14 @@ hipError_t launch_setup_small(const RowMap &m, int G, int u, int *dist, int *par
                               int *bflag, int *out, hipStream_t st);
 hipError_t launch_b_intervals(int n, int u, int ecc, const int *dist, const int *parB, int *scratch, int2 *bint,
                               int *bflag, hipStream_t st);
-// Pivot-column solve (SolveScalars): start (x = 0, r = b) and iterations of the multi-kernel
+// Pivot-column solve (SolveScalars): start (x = 0, r = b) and slots of the multi-kernel
 // engine; the whole solve in one workgroup (one-workgroup engine); many one-workgroup solves in
 // one launch (one workgroup each).
 constexpr int kSmallSolveMaxN = 16384;
 template <typename T>
 hipError_t launch_solve_start(const SolveArgs<T> &a, double tol2, double delta2, int maxit, hipStream_t st);
 template <typename T>
-hipError_t launch_solve_iteration(const SolveArgs<T> &a, const RowMap &m, int G, hipStream_t st);
+hipError_t launch_solve_slot(const SolveArgs<T> &a, const RowMap &m, int G, hipStream_t st);
 template <typename T>
 hipError_t launch_solve_small(const SolveArgs<T> &a, const RowMap &m, int G, double tol2, double delta2, int maxit,
                               hipStream_t st);

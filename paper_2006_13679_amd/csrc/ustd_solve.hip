@@ -14,9 +14,9 @@
 // true residual meets the target.  Dot products are accumulated in FP64 in a fixed order.
 //
 // Two engines: the whole solve in one workgroup (small graphs; many graphs of a batch side by
-// side, one workgroup each), with no host round trip; or eight kernels per iteration whose
-// scalars stay on the device, enqueued by the host in growing chunks ahead of a `done` flag that
-// turns later launches into no-ops.
+// side, one workgroup each), with no host round trip; or three kernels per slot whose scalars
+// stay on the device, enqueued by the host in growing chunks ahead of a `done` flag that turns
+// later launches into no-ops.  A slot is one CG iteration or the second half of a reliable update.
 #include "ustd_kernels.hpp"
 
 #include <algorithm>
@@ -24,46 +24,100 @@
 namespace ustd {
 
 constexpr int kSmallThreads = 1024;
+// blocks of the multi-kernel engine: at most one resident set (8 per compute unit), since every
+// block adds a ticket and a partial result to its kernel's tail
+constexpr int kSolveGrid = 2048;
+static_assert(kSolveGrid <= kMaxSolveGrid, "partial results fit the workspace");
 
 // y = L p over all rows, degree-balanced: rows of degree <= heavy_thresh by groups of G lanes,
 // heavier rows (listed in ascending order) by the whole block.  emit(v, (L p)_v) is called once
 // per row from one thread.  Fixed grid and fixed per-row reduction trees: deterministic.
 // Block blk of nblk takes every nblk-th heavy row and row tile (a whole grid: blockIdx.x of
 // gridDim.x; a workgroup that solves a graph alone: 0 of 1).  BS = block size.
+// A row is a chain of three loads (row bounds, columns, the gathered entries), so what bounds the
+// product is how many chains are in flight: a group takes the first two entries a lane of
+// kRowsInFlight rows at once, then what is left of the longer rows four entries a lane at a time,
+// and a heavy row goes eight entries a thread at a time.  (One entry at a time, a light row of
+// degree 512 is 32 loads in a row, longer than the rest of the product at n = 200k, and the hub of
+// R-MAT scale 22 kept one workgroup busy for 1.0 ms of a 1.2 ms product.)
+constexpr int kRowsInFlight = 4;
+
+// acc + sum of the entries first, first + step, ... below end, in that order, U loads at a time
+template <typename T, int U>
+__device__ __forceinline__ T row_sum(T acc, const int *__restrict__ col, const double *__restrict__ w,
+                                     const T *__restrict__ p, int first, int end, int step) {
+    for (int e = first; e < end; e += U * step) {
+        int c[U];
+        T q[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            c[k] = -1;
+            if (e + k * step < end) c[k] = col[e + k * step];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            q[k] = (T)0;
+            if (c[k] >= 0) q[k] = w ? (T)w[e + k * step] * p[c[k]] : p[c[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) acc += q[k];
+    }
+    return acc;
+}
+
 template <typename T, int G, int BS = 256, typename Emit>
 __device__ __forceinline__ void lap_apply_rows(const RowMap &m, const T *__restrict__ p, Emit emit, int blk,
-                                               int nblk) {
+                                               int nblk, int bs = BS) {
     __shared__ T shr[BS / kWave];
     const int nh = *m.nheavy;
     const double *__restrict__ w = m.w;  // uniform: weighted Laplacian when set
     for (int h = blk; h < nh; h += nblk) {
         const int v = m.heavy[h];
         const int lo = m.rp[v], hi = m.rp[v + 1];
-        T acc = (T)0;
-        if (w)
-            for (int e = lo + threadIdx.x; e < hi; e += blockDim.x) acc += (T)w[e] * p[m.col[e]];
-        else
-            for (int e = lo + threadIdx.x; e < hi; e += blockDim.x) acc += p[m.col[e]];
-        acc = block_sum_t<T>(acc, shr);
+        T acc = row_sum<T, 8>((T)0, m.col, w, p, lo + threadIdx.x, hi, bs);
+        acc = block_sum_t<T>(acc, shr, bs);
         if (threadIdx.x == 0) emit(v, (w ? (T)m.wdeg[v] : (T)(hi - lo)) * p[v] - acc);
     }
-    constexpr int rows_per_tile = BS / G;
+    const int rows_per_tile = bs / G;
     const int g = threadIdx.x / G, l = threadIdx.x % G;
-    for (int tile = blk; tile * rows_per_tile < m.n; tile += nblk) {
-        const int v = tile * rows_per_tile + g;
-        const bool ok = v < m.n;
-        const int lo = ok ? m.rp[v] : 0, hi = ok ? m.rp[v + 1] : 0;
-        const bool light = ok && (hi - lo <= m.heavy_thresh);
-        T acc = (T)0;
-        if (light) {
-            if (w)
-                for (int e = lo + l; e < hi; e += G) acc += (T)w[e] * p[m.col[e]];
-            else
-                for (int e = lo + l; e < hi; e += G) acc += p[m.col[e]];
+    for (int tile = blk; tile * rows_per_tile < m.n; tile += kRowsInFlight * nblk) {
+        int lo[kRowsInFlight], deg[kRowsInFlight], len[kRowsInFlight];
+        int c[kRowsInFlight][2];
+        T q[kRowsInFlight][2];
+#pragma unroll
+        for (int i = 0; i < kRowsInFlight; ++i) {
+            const int v = (tile + i * nblk) * rows_per_tile + g;
+            lo[i] = v < m.n ? m.rp[v] : 0;
+            deg[i] = v < m.n ? m.rp[v + 1] : -1;
         }
 #pragma unroll
-        for (int dd = G / 2; dd > 0; dd >>= 1) acc += __shfl_xor(acc, dd, G);
-        if (light && l == 0) emit(v, (w ? (T)m.wdeg[v] : (T)(hi - lo)) * p[v] - acc);
+        for (int i = 0; i < kRowsInFlight; ++i) {
+            deg[i] = deg[i] < 0 ? -1 : deg[i] - lo[i];
+            len[i] = deg[i] <= m.heavy_thresh ? deg[i] : 0;  // heavy rows are done above
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                c[i][s] = -1;
+                if (l + s * G < len[i]) c[i][s] = m.col[lo[i] + l + s * G];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kRowsInFlight; ++i)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                q[i][s] = (T)0;
+                if (c[i][s] >= 0) q[i][s] = w ? (T)w[lo[i] + l + s * G] * p[c[i][s]] : p[c[i][s]];
+            }
+#pragma unroll
+        for (int i = 0; i < kRowsInFlight; ++i) {
+            T acc = q[i][0] + q[i][1];
+            if (len[i] > 2 * G) acc = row_sum<T, 4>(acc, m.col, w, p, lo[i] + l + 2 * G, lo[i] + len[i], G);
+#pragma unroll
+            for (int dd = G / 2; dd > 0; dd >>= 1) acc += __shfl_xor(acc, dd, G);
+            if (deg[i] >= 0 && deg[i] <= m.heavy_thresh && l == 0) {
+                const int v = (tile + i * nblk) * rows_per_tile + g;
+                emit(v, (w ? (T)m.wdeg[v] : (T)deg[i]) * p[v] - acc);
+            }
+        }
     }
 }
 
@@ -88,9 +142,69 @@ __device__ __forceinline__ double *part_pq(double *part) { return part; }
 __device__ __forceinline__ double *part_upd(double *part) { return part + kMaxSolveGrid; }
 __device__ __forceinline__ double *part_rel(double *part) { return part + 3 * kMaxSolveGrid; }
 
+// The last block of a grid to finish sums the blocks' partial results, so a reduction needs no
+// kernel of its own.  The blocks run on several XCDs whose L2s are not coherent within a kernel:
+// partial results are stored past the L2 (agent scope), the store is complete before the block
+// takes its ticket, and the last block reads them past the L2.  Tickets on one address cost 14 ns
+// each (2048 blocks: 28 us), so block b takes one of group b mod kTicketGroups (its own cache
+// line), and the last of a group one of the root.  Thread 0 stores and takes tickets; every
+// thread learns the answer.  The counters are left at zero.
+constexpr int kTicketGroups = 32, kTicketStride = 32;  // counters a 128-byte line apart
+static_assert(2 * kSolveGrid + (kTicketGroups + 1) * kTicketStride / 2 <= 2 * kMaxSolveGrid, "counters fit beside the partials");
+__device__ __forceinline__ unsigned *part_tickets(double *part) {  // behind the partials of the update
+    return reinterpret_cast<unsigned *>(part_upd(part) + 2 * kSolveGrid);
+}
+__device__ __forceinline__ void put_partial(double *p, double v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ bool take_ticket(unsigned *t, unsigned of) {
+    const bool last = __hip_atomic_fetch_add(t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == of - 1;
+    if (last) __hip_atomic_store(t, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return last;
+}
+__device__ __forceinline__ bool last_block(double *part) {
+    __shared__ int last;
+    if (threadIdx.x == 0) {
+        unsigned *t = part_tickets(part);
+        const unsigned groups = min(gridDim.x, (unsigned)kTicketGroups), g = blockIdx.x % groups;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the partial results have been stored
+        last = 0;
+        if (take_ticket(t + g * kTicketStride, (gridDim.x - g + groups - 1) / groups))
+            last = take_ticket(t + kTicketGroups * kTicketStride, groups);
+    }
+    __syncthreads();
+    return last;
+}
+// sums of part[N i + j], i < nparts (at most kSolveGrid), j < N, into out[j], in the order of
+// sum_partials; every load is issued before the first is waited for
+template <int N>
+__device__ __forceinline__ void sum_fresh(double *part, int nparts, double *out, double *sh) {
+    constexpr int kEach = kSolveGrid / 256;
+    double v[kEach][N];
+#pragma unroll
+    for (int k = 0; k < kEach; ++k)
+#pragma unroll
+        for (int j = 0; j < N; ++j) {
+            const int i = threadIdx.x + k * 256;
+            v[k][j] = 0.0;
+            if (i < nparts)
+                v[k][j] = __hip_atomic_load(&part[(long long)N * i + j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) s += v[k][j];
+        out[j] = block_sum(s, sh);
+    }
+}
+
 // ---------------------------------------------------------------------------------------
-// multi-kernel solve (large graphs): eight kernels per iteration, whose scalars stay on the
-// device; once `done` is set every later launch of the solve returns at once.
+// multi-kernel solve (large graphs): three kernels per slot, whose scalars stay on the device; once
+// `done` is set every later launch of the solve returns at once.  With a kernel per reduction and
+// per half of an update (eight an iteration, five of them a few microseconds of launch for next
+// to no work) an iteration took 50 us at n = 200k, half of it the product.
 // ---------------------------------------------------------------------------------------
 // x = 0, xs = 0, rs = b, z = p = rs / diag; partials of z.r, r.r and b.b (3 per block)
 template <typename T>
@@ -127,6 +241,7 @@ __global__ __launch_bounds__(256) void solve_start_finish_kernel(SolveArgs<T> a,
                                                                  int maxit) {
     __shared__ double sh[4];
     const double *pr = part_rel(a.part);
+    for (int i = threadIdx.x; i < (kTicketGroups + 1) * kTicketStride; i += blockDim.x) part_tickets(a.part)[i] = 0u;
     const double rz = sum_partials(pr, a.grid_vec, 3, sh);
     const double rr = sum_partials(pr + 1, a.grid_vec, 3, sh);
     const double bb = sum_partials(pr + 2, a.grid_vec, 3, sh);
@@ -143,6 +258,7 @@ __global__ __launch_bounds__(256) void solve_start_finish_kernel(SolveArgs<T> a,
         S->iter = 0;
         S->maxit = maxit;
         S->upd = 0;
+        S->skip = 0;
         S->updates = 0;
         S->stalls = 0;
         S->broke = 0;
@@ -150,103 +266,43 @@ __global__ __launch_bounds__(256) void solve_start_finish_kernel(SolveArgs<T> a,
     }
 }
 
-// q = L p; partial p.q per block
+// First kernel of a slot.  An iteration: q = L p, and the last block alpha = z.r / p.q (a
+// breakdown, p.q not positive, ends the solve at the next update).  After a fold: the second half
+// of a reliable update, r = b - L x in FP64, rs = r, z = rs / diag, and the last block decides on
+// the true residual whether the solve ends, else beta from the replaced residual.  Three updates in
+// a row whose true residual fell by less than 2x (the rounding floor) also end the solve.
 template <typename T, int G>
-__global__ __launch_bounds__(256) void solve_spmv_kernel(SolveArgs<T> a, RowMap m) {
-    __shared__ double sh[4];
-    if (a.sc->done) return;  // uniform: written by an earlier kernel
-    double acc = 0.0;
-    T *__restrict__ q = a.q;
-    const T *__restrict__ p = a.p;
-    lap_apply_rows<T, G>(
-        m, p,
-        [&](int v, T qv) {
-            q[v] = qv;
-            acc += (double)p[v] * (double)qv;
-        },
-        blockIdx.x, gridDim.x);
-    acc = block_sum(acc, sh);
-    if (threadIdx.x == 0) part_pq(a.part)[blockIdx.x] = acc;
-}
-
-// alpha = z.r / p.q (one block); a breakdown (p.q not positive) ends the solve at the next update
-template <typename T>
-__global__ __launch_bounds__(256) void solve_alpha_kernel(SolveArgs<T> a) {
+__global__ __launch_bounds__(256) void solve_apply_kernel(SolveArgs<T> a, RowMap m) {
     __shared__ double sh[4];
     SolveScalars *S = a.sc;
-    if (S->done) return;
-    const double pq = sum_partials(part_pq(a.part), a.grid_spmv, 1, sh);
-    if (threadIdx.x == 0) {
-        if (pq > 0.0 && pq == pq) {
-            S->alpha = S->rz / pq;
-        } else {
-            S->alpha = 0.0;
-            S->broke = 1;
+    if (S->done) return;  // uniform: written by an earlier kernel
+    if (!S->upd) {
+        double acc = 0.0;
+        T *__restrict__ q = a.q;
+        const T *__restrict__ p = a.p;
+        lap_apply_rows<T, G>(
+            m, p,
+            [&](int v, T qv) {
+                q[v] = qv;
+                acc += (double)p[v] * (double)qv;
+            },
+            blockIdx.x, gridDim.x);
+        acc = block_sum(acc, sh);
+        if (threadIdx.x == 0) put_partial(part_pq(a.part) + blockIdx.x, acc);
+        if (!last_block(a.part)) return;
+        double pq;
+        sum_fresh<1>(part_pq(a.part), gridDim.x, &pq, sh);
+        if (threadIdx.x == 0) {
+            S->skip = 0;
+            if (pq > 0.0 && pq == pq) {
+                S->alpha = S->rz / pq;
+            } else {
+                S->alpha = 0.0;
+                S->broke = 1;
+            }
         }
+        return;
     }
-}
-
-// xs += alpha p; rs -= alpha q; z = rs / diag; partials of z.r and r.r
-template <typename T>
-__global__ __launch_bounds__(256) void solve_update_kernel(SolveArgs<T> a) {
-    __shared__ double sh[4];
-    if (a.sc->done) return;
-    const T al = (T)a.sc->alpha;
-    double rz = 0.0, rr = 0.0;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x) {
-        a.xs[v] += al * a.p[v];
-        const T rv = a.rs[v] - al * a.q[v];
-        a.rs[v] = rv;
-        const T zv = rv / jacobi_diag(a, v);
-        a.z[v] = zv;
-        rz += (double)rv * (double)zv;
-        rr += (double)rv * (double)rv;
-    }
-    rz = block_sum(rz, sh);
-    rr = block_sum(rr, sh);
-    if (threadIdx.x == 0) {
-        double *pu = part_upd(a.part) + 2 * blockIdx.x;
-        pu[0] = rz;
-        pu[1] = rr;
-    }
-}
-
-// one block: the iteration count, the reliable-update test, else beta
-template <typename T>
-__global__ __launch_bounds__(256) void solve_beta_kernel(SolveArgs<T> a) {
-    __shared__ double sh[4];
-    SolveScalars *S = a.sc;
-    if (S->done) return;
-    const double rzn = sum_partials(part_upd(a.part), a.grid_vec, 2, sh);
-    const double rr = sum_partials(part_upd(a.part) + 1, a.grid_vec, 2, sh);
-    if (threadIdx.x == 0) {
-        S->iter += 1;
-        S->rr = rr;
-        const bool upd = S->broke || S->iter >= S->maxit || !(rr > S->tol2 * S->bb) || rr < S->delta2 * S->rr_max;
-        if (rr > S->rr_max) S->rr_max = rr;
-        S->upd = upd ? 1 : 0;
-        if (!upd) {
-            S->beta = S->rz != 0.0 ? rzn / S->rz : 0.0;
-            S->rz = rzn;
-        }
-    }
-}
-
-// reliable update, part 1: x += xs, xs = 0
-template <typename T>
-__global__ __launch_bounds__(256) void solve_fold_kernel(SolveArgs<T> a) {
-    if (!a.sc->upd) return;
-    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x) {
-        a.x[v] += (double)a.xs[v];
-        a.xs[v] = (T)0;
-    }
-}
-
-// reliable update, part 2: r = b - L x in FP64; rs = r; z = rs / diag; partials of z.r, r.r
-template <typename T, int G>
-__global__ __launch_bounds__(256) void solve_true_residual_kernel(SolveArgs<T> a, RowMap m) {
-    __shared__ double sh[4];
-    if (!a.sc->upd) return;
     const double inv_n = 1.0 / (double)a.n;
     double rz = 0.0, rt = 0.0;
     lap_apply_rows<double, G>(
@@ -263,23 +319,16 @@ __global__ __launch_bounds__(256) void solve_true_residual_kernel(SolveArgs<T> a
         blockIdx.x, gridDim.x);
     rz = block_sum(rz, sh);
     rt = block_sum(rt, sh);
+    double *pr = part_rel(a.part);
     if (threadIdx.x == 0) {
-        double *pr = part_rel(a.part) + 2 * blockIdx.x;
-        pr[0] = rz;
-        pr[1] = rt;
+        put_partial(pr + 2 * blockIdx.x, rz);
+        put_partial(pr + 2 * blockIdx.x + 1, rt);
     }
-}
-
-// reliable update, part 3 (one block): the true residual decides the end; else beta from the
-// replaced residual.  Three updates in a row whose true residual fell by less than 2x
-// (the rounding floor) also end the solve.
-template <typename T>
-__global__ __launch_bounds__(256) void solve_update_end_kernel(SolveArgs<T> a) {
-    __shared__ double sh[4];
-    SolveScalars *S = a.sc;
-    if (!S->upd) return;
-    const double rzn = sum_partials(part_rel(a.part), a.grid_spmv, 2, sh);
-    const double rt = sum_partials(part_rel(a.part) + 1, a.grid_spmv, 2, sh);
+    if (!last_block(a.part)) return;
+    double tot[2];
+    sum_fresh<2>(pr, gridDim.x, tot, sh);
+    const double rzn = tot[0];
+    rt = tot[1];
     if (threadIdx.x == 0) {
         S->updates += 1;
         S->stalls = rt > 0.25 * S->rr_true ? S->stalls + 1 : 0;
@@ -287,6 +336,7 @@ __global__ __launch_bounds__(256) void solve_update_end_kernel(SolveArgs<T> a) {
         S->rr_max = rt;
         S->rr = rt;
         S->upd = 0;
+        S->skip = 1;
         if (!(rt > S->tol2 * S->bb) || S->iter >= S->maxit || S->broke || S->stalls >= 3) {
             S->done = 1;
         } else {
@@ -296,10 +346,60 @@ __global__ __launch_bounds__(256) void solve_update_end_kernel(SolveArgs<T> a) {
     }
 }
 
-// p = z + beta p
+// Second kernel of a slot, iterations only: xs += alpha p; rs -= alpha q; z = rs / diag; the last
+// block counts the iteration and tests for a reliable update, else beta
 template <typename T>
-__global__ __launch_bounds__(256) void solve_pdir_kernel(SolveArgs<T> a) {
+__global__ __launch_bounds__(256) void solve_update_kernel(SolveArgs<T> a) {
+    __shared__ double sh[4];
+    SolveScalars *S = a.sc;
+    if (S->done || S->skip) return;
+    const T al = (T)S->alpha;
+    double rz = 0.0, rr = 0.0;
+    for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x) {
+        a.xs[v] += al * a.p[v];
+        const T rv = a.rs[v] - al * a.q[v];
+        a.rs[v] = rv;
+        const T zv = rv / jacobi_diag(a, v);
+        a.z[v] = zv;
+        rz += (double)rv * (double)zv;
+        rr += (double)rv * (double)rv;
+    }
+    rz = block_sum(rz, sh);
+    rr = block_sum(rr, sh);
+    double *pu = part_upd(a.part);
+    if (threadIdx.x == 0) {
+        put_partial(pu + 2 * blockIdx.x, rz);
+        put_partial(pu + 2 * blockIdx.x + 1, rr);
+    }
+    if (!last_block(a.part)) return;
+    double tot[2];
+    sum_fresh<2>(pu, gridDim.x, tot, sh);
+    const double rzn = tot[0];
+    rr = tot[1];
+    if (threadIdx.x == 0) {
+        S->iter += 1;
+        S->rr = rr;
+        const bool upd = S->broke || S->iter >= S->maxit || !(rr > S->tol2 * S->bb) || rr < S->delta2 * S->rr_max;
+        if (rr > S->rr_max) S->rr_max = rr;
+        S->upd = upd ? 1 : 0;
+        if (!upd) {
+            S->beta = S->rz != 0.0 ? rzn / S->rz : 0.0;
+            S->rz = rzn;
+        }
+    }
+}
+
+// Third kernel of a slot: p = z + beta p, or the first half of a reliable update, x += xs, xs = 0
+template <typename T>
+__global__ __launch_bounds__(256) void solve_direction_kernel(SolveArgs<T> a) {
     if (a.sc->done) return;
+    if (a.sc->upd) {
+        for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x) {
+            a.x[v] += (double)a.xs[v];
+            a.xs[v] = (T)0;
+        }
+        return;
+    }
     const T be = (T)a.sc->beta;
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < a.n; v += gridDim.x * blockDim.x)
         a.p[v] = a.z[v] + be * a.p[v];
@@ -310,13 +410,20 @@ __global__ __launch_bounds__(256) void solve_pdir_kernel(SolveArgs<T> a) {
 // reliable updates and end rule, with no kernel boundary or host poll between iterations.
 // Ends with the scalars the multi-kernel path leaves.
 // ---------------------------------------------------------------------------------------
+// Up to 1024 rows four waves do the work and the others leave at once (a barrier counts the waves
+// that are left): an iteration is a chain of a dozen barriers, which cost less among four.  The
+// choice depends on n alone, so a batch member's solve is that of a single call.
+constexpr int kFewRows = 1024, kFewThreads = 256;
+
 template <typename T, int G>
 __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double tol2, double delta2, int maxit,
                                  double *sh) {
     const int n = a.n, tid = threadIdx.x, u = a.u;
+    const int nt = n <= kFewRows ? kFewThreads : kSmallThreads;
+    if (tid >= nt) return;
     const double inv_n = 1.0 / (double)n;
     double rz = 0.0, rr = 0.0, bb = 0.0;
-    for (int v = tid; v < n; v += kSmallThreads) {
+    for (int v = tid; v < n; v += nt) {
         const double b = rhs_of(v, u, inv_n);
         const T rv = (T)b;
         const T zv = rv / jacobi_diag(a, v);
@@ -329,9 +436,9 @@ __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double 
         rr += (double)rv * (double)rv;
         bb += b * b;
     }
-    rz = block_sum_t<double>(rz, sh);  // the barriers also publish p before the first product
-    rr = block_sum_t<double>(rr, sh);
-    bb = block_sum_t<double>(bb, sh);
+    rz = block_sum_t<double>(rz, sh, nt);  // the barriers also publish p before the first product
+    rr = block_sum_t<double>(rr, sh, nt);
+    bb = block_sum_t<double>(bb, sh, nt);
     double rr_max = rr, rr_true = bb;
     int it = 0, updates = 0, stalls = 0;
     bool done = !(bb > 0.0 && rz > 0.0 && maxit > 0);
@@ -343,12 +450,12 @@ __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double 
                 a.q[v] = qv;
                 pq += (double)a.p[v] * (double)qv;
             },
-            0, 1);
-        pq = block_sum_t<double>(pq, sh);
+            0, 1, nt);
+        pq = block_sum_t<double>(pq, sh, nt);
         const bool broke = !(pq > 0.0 && pq == pq);
         const T al = broke ? (T)0 : (T)(rz / pq);
         double rzn = 0.0, rrn = 0.0;
-        for (int v = tid; v < n; v += kSmallThreads) {
+        for (int v = tid; v < n; v += nt) {
             a.xs[v] += al * a.p[v];
             const T rv = a.rs[v] - al * a.q[v];
             a.rs[v] = rv;
@@ -357,14 +464,14 @@ __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double 
             rzn += (double)rv * (double)zv;
             rrn += (double)rv * (double)rv;
         }
-        rzn = block_sum_t<double>(rzn, sh);
-        rrn = block_sum_t<double>(rrn, sh);
+        rzn = block_sum_t<double>(rzn, sh, nt);
+        rrn = block_sum_t<double>(rrn, sh, nt);
         ++it;
         const bool upd = broke || it >= maxit || !(rrn > tol2 * bb) || rrn < delta2 * rr_max;
         if (rrn > rr_max) rr_max = rrn;
         double beta;
         if (upd) {
-            for (int v = tid; v < n; v += kSmallThreads) {
+            for (int v = tid; v < n; v += nt) {
                 a.x[v] += (double)a.xs[v];
                 a.xs[v] = (T)0;
             }
@@ -381,9 +488,9 @@ __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double 
                     rz2 += (double)rs * (double)zv;
                     rt += rv * rv;
                 },
-                0, 1);
-            rz2 = block_sum_t<double>(rz2, sh);
-            rt = block_sum_t<double>(rt, sh);
+                0, 1, nt);
+            rz2 = block_sum_t<double>(rz2, sh, nt);
+            rt = block_sum_t<double>(rt, sh, nt);
             ++updates;
             stalls = rt > 0.25 * rr_true ? stalls + 1 : 0;
             rr_true = rt;
@@ -396,7 +503,7 @@ __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double 
             rz = rzn;
         }
         const T be = (T)beta;
-        for (int v = tid; v < n; v += kSmallThreads) a.p[v] = a.z[v] + be * a.p[v];
+        for (int v = tid; v < n; v += nt) a.p[v] = a.z[v] + be * a.p[v];
         __syncthreads();  // p complete before the next product gathers it
     }
     if (tid == 0) {
@@ -488,9 +595,10 @@ __global__ __launch_bounds__(256) void project_kernel(int n, double *__restrict_
 // ---------------------------------------------------------------------------------------
 int solve_grid(const RowMap &m, int G) {
     const long long tiles = ((long long)m.n + (256 / G) - 1) / (256 / G);
-    return (int)std::min<long long>(std::max<long long>(tiles, 1), kMaxSolveGrid);
+    const long long blocks = (tiles + kRowsInFlight - 1) / kRowsInFlight;
+    return (int)std::min<long long>(std::max<long long>(blocks, 1), kSolveGrid);
 }
-int vec_grid(int n) { return std::max(1, std::min((n + 255) / 256, kMaxSolveGrid)); }
+int vec_grid(int n) { return std::max(1, std::min((n + 255) / 256, kSolveGrid)); }
 
 template <typename T>
 hipError_t launch_solve_start(const SolveArgs<T> &a, double tol2, double delta2, int maxit, hipStream_t st) {
@@ -500,15 +608,10 @@ hipError_t launch_solve_start(const SolveArgs<T> &a, double tol2, double delta2,
 }
 
 template <typename T>
-hipError_t launch_solve_iteration(const SolveArgs<T> &a, const RowMap &m, int G, hipStream_t st) {
-    USTD_DISPATCH_G(G, (solve_spmv_kernel<T, GG><<<a.grid_spmv, 256, 0, st>>>(a, m)));
-    solve_alpha_kernel<T><<<1, 256, 0, st>>>(a);
+hipError_t launch_solve_slot(const SolveArgs<T> &a, const RowMap &m, int G, hipStream_t st) {
+    USTD_DISPATCH_G(G, (solve_apply_kernel<T, GG><<<a.grid_spmv, 256, 0, st>>>(a, m)));
     solve_update_kernel<T><<<a.grid_vec, 256, 0, st>>>(a);
-    solve_beta_kernel<T><<<1, 256, 0, st>>>(a);
-    solve_fold_kernel<T><<<a.grid_vec, 256, 0, st>>>(a);
-    USTD_DISPATCH_G(G, (solve_true_residual_kernel<T, GG><<<a.grid_spmv, 256, 0, st>>>(a, m)));
-    solve_update_end_kernel<T><<<1, 256, 0, st>>>(a);
-    solve_pdir_kernel<T><<<a.grid_vec, 256, 0, st>>>(a);
+    solve_direction_kernel<T><<<a.grid_vec, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 
@@ -528,7 +631,7 @@ hipError_t launch_solve_small_batch(const SolveJob<T> *jobs, int count, int G, h
 
 #define USTD_SOLVE_INSTANTIATE(T)                                                                              \
     template hipError_t launch_solve_start<T>(const SolveArgs<T> &, double, double, int, hipStream_t);         \
-    template hipError_t launch_solve_iteration<T>(const SolveArgs<T> &, const RowMap &, int, hipStream_t);     \
+    template hipError_t launch_solve_slot<T>(const SolveArgs<T> &, const RowMap &, int, hipStream_t);          \
     template hipError_t launch_solve_small<T>(const SolveArgs<T> &, const RowMap &, int, double, double, int,  \
                                               hipStream_t);                                                    \
     template hipError_t launch_solve_small_batch<T>(const SolveJob<T> *, int, int, hipStream_t);
