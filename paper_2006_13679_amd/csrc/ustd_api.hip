@@ -74,10 +74,10 @@ struct Misc {                      // small zero-initialised block at the front 
 };
 
 struct Plan {
-    int n, nnz, K, Kiv, slots, pools, rob, nwords, G, heavy_thresh;
+    int n, nnz, K, slots, pools, rob, nwords, G, heavy_thresh;
     bool lds_bits, col16, weighted;
     bool edges;  // edge entries for the sampler (tree state in global memory)
-    long long rec_stride, scr_stride;
+    long long rec_stride;
     long long off_misc, off_rp32, off_col16, off_dist, off_parB, off_bint, off_bflag, off_vrow, off_edge, off_heavy, off_bcount, off_counts, off_steps,
         off_draws, off_rec, off_path, off_scr, off_part, off_x64, off_r64, off_z64, off_p64, off_q64,
         off_res64, off_x32, off_r32, off_z32, off_p32, off_q32, off_cw, off_guide, off_wdeg, off_wB, off_F;
@@ -136,7 +136,6 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     L.G = avg <= 6.0 ? 4 : (avg <= 16.0 ? 8 : (avg <= 48.0 ? 16 : 32));
     L.heavy_thresh = 32 * L.G;
     L.rec_stride = align_up((long long)L.n * 8) / 8;  // int2 records
-    L.scr_stride = align_up(interval_scratch_ints(L.n) * 4) / 4;
     // trees resident at once (records), and sampler blocks resident at once (scratch slots).
     // Graphs past the LDS bitmap run several batches.  When the budget holds two pools that
     // can each fill the GPU (kPoolMinTrees trees), they are sampled on two streams, so one
@@ -164,7 +163,6 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     if (p->tau_override > 0) K = std::min<long long>(K, p->tau_override);
     if (p->tau_cap > 0) K = std::min<long long>(K, p->tau_cap);
     L.K = with_trees ? (int)std::max(1ll, K) : 0;
-    L.Kiv = std::min(L.K, 16);
     L.slots = std::min(L.K, kSamplerMaxBlocks);
     long long o = 0;
     auto take = [&](long long bytes) {
@@ -189,7 +187,7 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     L.off_draws = take((long long)L.pools * L.K * 8);
     L.off_rec = take((long long)L.pools * L.K * L.rec_stride * 8);
     L.off_path = take((long long)L.pools * L.slots * kSamplerPathSlot * 4);
-    L.off_scr = take(std::max((long long)L.Kiv * L.scr_stride, 3 * n) * 4);
+    L.off_scr = take(3 * n * 4);
     L.off_part = take((long long)kMaxSolveGrid * 6 * 8);
     L.off_x64 = take(n * 8);
     L.off_r64 = take(n * 8);
@@ -2022,14 +2020,18 @@ int ustd_tree_counts(const ustd_problem *prob, const int32_t *d_parents, int64_t
     // not a spanning tree rooted at the pivot returns USTD_EINVAL with d_counts unchanged.
     long long *acc = at<long long>(c.ws, c.L.off_counts);
     HIP_TRY(launch_fill_i64(c.L.n, acc, 0, c.st));
-    // One block builds a tree's records, so a launch takes as many trees as fit: nothing is sampled
-    // here, and the record pool, the sampler's path slots and the builder's own scratch lie side by
-    // side in the workspace.  They hold the records of a launch's trees, then the scratch (at least
-    // Kiv trees' worth; 16 trees a launch left 240 of 256 compute units idle).
-    const long long room = c.L.off_part - c.L.off_rec, rec_bytes = c.L.rec_stride * 8, scr_bytes = c.L.scr_stride * 4;
-    const long long per = std::min<long long>(std::max<long long>(room / (rec_bytes + scr_bytes), c.L.Kiv), c.L.K);
+    // A launch takes as many trees as fit: nothing is sampled here, and the record pool, the
+    // sampler's path slots and the builder's scratch lie side by side in the workspace.  They hold
+    // the records of a launch's trees, then one word per vertex and tree.
+    const long long rec_bytes = c.L.rec_stride * 8, word_bytes = align_up((long long)c.L.n * 4);
+    const long long per = std::max(1ll, std::min({(c.L.off_part - c.L.off_rec) / (rec_bytes + word_bytes), (long long)c.L.K,
+                                                  ((1ll << 31) - 1) / (c.L.n + 256)}));
+    int *open = c.misc->bfs_found;  // free after the set-up
+    static_assert(sizeof(c.misc->bfs_found) >= (kTreeJumpRounds + 1) * sizeof(int), "one flag per round");
     for (long long b0 = 0; b0 < tree_count; b0 += per) {
         const int cnt = (int)std::min<long long>(per, tree_count - b0);
+        HIP_TRY(hipMemsetAsync(open, 0, (kTreeJumpRounds + 1) * sizeof(int), c.st));
+        HIP_TRY(launch_fill_i32(1, open, 1, c.st));
         IntervalArgs ia{};
         ia.n = c.L.n;
         ia.u = c.pivot;
@@ -2038,10 +2040,10 @@ int ustd_tree_counts(const ustd_problem *prob, const int32_t *d_parents, int64_t
         ia.rec = at<int2>(c.ws, c.L.off_rec);
         ia.rec_stride = c.L.rec_stride;
         ia.scratch = at<int>(c.ws, c.L.off_rec + cnt * rec_bytes);
-        ia.scratch_stride = c.L.scr_stride;
+        ia.scratch_stride = word_bytes / 4;
         ia.bflag = at<int>(c.ws, c.L.off_bflag);
         ia.err = &c.misc->err_interval;
-        HIP_TRY(launch_tree_records(ia, cnt, c.st));
+        HIP_TRY(launch_tree_records(ia, cnt, open, c.st));
         int err = 0;
         HIP_TRY(hipMemcpyAsync(&err, &c.misc->err_interval, sizeof(int), hipMemcpyDeviceToHost, c.st));
         HIP_TRY(hipStreamSynchronize(c.st));

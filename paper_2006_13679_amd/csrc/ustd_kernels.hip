@@ -1164,136 +1164,84 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
 // ======================================================================================
 // Records of caller-supplied trees.  The sampler writes each vertex's record {parent,
 // nba | flags} as it commits; for trees given as parent arrays the same records are built
-// here.  One block per tree checks the parents, builds a child CSR (counting sort by
-// parent), expands a BFS order of T level by level (children of one vertex contiguous),
-// and writes the records top-down along that order, so a vertex's parent is done first.
-// A parent array that is not a spanning tree rooted at u sets err |= 64.
+// here by pointer jumping, a thread per (vertex, tree).  Two words per vertex are doubled
+// side by side: anc(v), an ancestor of v (u once reached), whose end tells whether v reaches the
+// pivot; and jw(v) = J | done << 31, where J is an ancestor of v such that every vertex
+// from parent(v) up to J is unmarked and not u (not done), or J = nba(v) (done).  A round follows
+// kJumps pointers, so the covered path grows by a factor of 8; any value that another thread has
+// stored keeps the invariants, so threads need no ordering within a round.  A round after one
+// that left nothing open returns at once.  A parent array that is not a spanning tree rooted at u
+// sets err |= 64 (a vertex on or below a cycle never reaches u).
+//
+// (One block per tree that built a child list and walked the levels of T took 880 us a launch at
+// 21,000 vertices whatever the number of trees: a chain of levels, barriers and hub lists.)
 // ======================================================================================
-// A block works through its tree in passes and levels, each bounded by the latency of its loads and
-// barriers: 1024 threads take four times the vertices of a pass at once (256 threads: 880 us a
-// launch at 21,000 vertices).
-constexpr int kIvThreads = 1024;
+constexpr unsigned kJumpDone = 0x80000000u;
+constexpr int kJumps = 7;
 
-__global__ __launch_bounds__(kIvThreads) void tree_records_kernel(IntervalArgs a) {
-    __shared__ int sh[kIvThreads / kWave + 1];
-    __shared__ int bigq[kIvThreads];
-    __shared__ int nbig;
-    const int tid = threadIdx.x;
+__device__ __forceinline__ bool in_tree_ids(int v, int n) { return v >= 0 && v < n; }
+
+__global__ __launch_bounds__(256) void tree_jump_init_kernel(IntervalArgs a) {
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= a.n) return;
     const int n = a.n, u = a.u;
-    const int *__restrict__ par = a.par + (long long)blockIdx.x * a.par_stride;
-    int *__restrict__ scr = a.scratch + (long long)blockIdx.x * a.scratch_stride;
-    int *__restrict__ cnt = scr;            // n
-    int *__restrict__ cst = cnt + n;        // n + 1
-    int *__restrict__ child = cst + n + 1;  // n
-    int *__restrict__ ord = child + n;      // n
-    int *__restrict__ fc = ord + n;         // n   first-child position of each position
-    int *__restrict__ ppos = fc + n;        // n   parent position of each position
-    int *__restrict__ lv = ppos + n;        // n + 2 level starts
-
-    for (int v = tid; v < n; v += kIvThreads) cnt[v] = 0;
-    __syncthreads();
-    int bad = 0;
-    for (int v = tid; v < n; v += kIvThreads) {
-        if (v == u) continue;
-        const int pv = par[v];
-        if (pv < 0 || pv >= n || pv == v) bad = 1;
-        else atomicAdd(&cnt[pv], 1);
+    const int *__restrict__ par = a.par + (long long)blockIdx.y * a.par_stride;
+    int anc = u;
+    unsigned jw = (unsigned)u | kJumpDone;
+    int pv = -1;
+    if (v != u) {
+        pv = par[v];
+        if (!in_tree_ids(pv, n) || pv == v) {
+            atomicOr(a.err, 64);
+        } else if (pv != u) {
+            const int ppv = par[pv];
+            const bool marked = in_tree_ids(ppv, n) && (mark_bits(pv, a.bflag[pv], ppv, a.bflag[ppv]) & kMarkBit);
+            anc = pv;
+            jw = (unsigned)pv | (marked ? kJumpDone : 0u);
+        }
     }
-    if (__syncthreads_or(bad)) {
-        if (tid == 0) atomicOr(a.err, 64);
+    a.scratch[(long long)blockIdx.y * a.scratch_stride + v] = anc;
+    a.rec[(long long)blockIdx.y * a.rec_stride + v] = make_int2(pv, (int)jw);
+}
+
+// one round; open[0]: the round before left something open, open[1]: this one did
+__global__ __launch_bounds__(256) void tree_jump_kernel(IntervalArgs a, int *__restrict__ open) {
+    if (open[0] == 0) return;  // uniform over the grid
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    bool more = false;
+    if (v < a.n) {
+        int *anc = a.scratch + (long long)blockIdx.y * a.scratch_stride;
+        int2 *rec = a.rec + (long long)blockIdx.y * a.rec_stride;
+        int x = anc[v];
+        if (x != a.u) {
+            for (int i = 0; i < kJumps && x != a.u; ++i) x = anc[x];
+            anc[v] = x;
+            more = x != a.u;
+        }
+        unsigned w = (unsigned)rec[v].y;
+        if (!(w & kJumpDone)) {
+            for (int i = 0; i < kJumps && !(w & kJumpDone); ++i) w = (unsigned)rec[w].y;
+            rec[v].y = (int)w;
+            more = more || !(w & kJumpDone);
+        }
+    }
+    if (__any(more) && lane_id() == 0) open[1] = 1;
+}
+
+__global__ __launch_bounds__(256) void tree_records_kernel(IntervalArgs a) {
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (v >= a.n) return;
+    int2 *rec = a.rec + (long long)blockIdx.y * a.rec_stride;
+    if (v == a.u) {
+        rec[v] = make_int2(-1, v);
         return;
     }
-    int carry = 0;
-    for (int base = 0; base < n; base += kIvThreads) {
-        const int v = base + tid;
-        const int c = v < n ? cnt[v] : 0;
-        int tot;
-        const int incl = block_incl_scan(c, &tot, sh);
-        if (v < n) cst[v] = carry + incl - c;
-        carry += tot;
-    }
-    if (tid == 0) cst[n] = carry;
-    __syncthreads();
-    for (int v = tid; v < n; v += kIvThreads) cnt[v] = cst[v];
-    __syncthreads();
-    for (int v = tid; v < n; v += kIvThreads)
-        if (v != u) child[atomicAdd(&cnt[par[v]], 1)] = v;
-    __syncthreads();
-
-    // BFS order of T from u
-    if (tid == 0) {
-        ord[0] = u;
-        ppos[0] = -1;
-        lv[0] = 0;
-    }
-    __syncthreads();
-    int ls = 0, le = 1, nlev = 0;
-    while (ls < le) {
-        carry = 0;
-        for (int base = ls; base < le; base += kIvThreads) {
-            const int i = base + tid;
-            int c = 0;
-            if (i < le) {
-                const int xv = ord[i];
-                c = cst[xv + 1] - cst[xv];
-            }
-            int tot;
-            const int incl = block_incl_scan(c, &tot, sh);
-            if (i < le) fc[i] = le + carry + incl - c;
-            carry += tot;
-        }
-        __syncthreads();
-        for (int base = ls; base < le; base += kIvThreads) {
-            if (tid == 0) nbig = 0;
-            __syncthreads();
-            const int i = base + tid;
-            if (i < le) {
-                const int xv = ord[i];
-                const int c0 = cst[xv], c = cst[xv + 1] - c0, f = fc[i];
-                if (c <= 32) {
-                    for (int j = 0; j < c; ++j) {
-                        ord[f + j] = child[c0 + j];
-                        ppos[f + j] = i;
-                    }
-                } else {
-                    bigq[atomicAdd(&nbig, 1)] = i;
-                }
-            }
-            __syncthreads();
-            const int nb = nbig;
-            for (int q = 0; q < nb; ++q) {
-                const int i2 = bigq[q];
-                const int xv = ord[i2];
-                const int c0 = cst[xv], c = cst[xv + 1] - c0, f = fc[i2];
-                for (int j = tid; j < c; j += kIvThreads) {
-                    ord[f + j] = child[c0 + j];
-                    ppos[f + j] = i2;
-                }
-            }
-            __syncthreads();
-        }
-        ++nlev;
-        if (tid == 0) lv[nlev] = le;
-        ls = le;
-        le += carry;
-        __syncthreads();
-    }
-    if (tid == 0 && ls != n) atomicOr(a.err, 64);  // not a spanning tree rooted at u
-    if (ls != n) return;
-
-    // {parent, nba | marked << 31} top-down along the BFS order of T
-    int2 *rec = a.rec + (long long)blockIdx.x * a.rec_stride;
-    if (tid == 0) rec[u] = make_int2(-1, u);
-    __syncthreads();
-    for (int L = 1; L < nlev; ++L) {
-        for (int j = lv[L] + tid; j < lv[L + 1]; j += kIvThreads) {
-            const int xv = ord[j];
-            const int pv = par[xv];
-            const int nba = cv_of(pv, rec[pv].y);
-            rec[xv] = make_int2(pv, nba | mark_bits(xv, a.bflag[xv], pv, a.bflag[pv]));
-        }
-        __syncthreads();
-    }
+    if (a.scratch[(long long)blockIdx.y * a.scratch_stride + v] != a.u) atomicOr(a.err, 64);
+    const int pv = rec[v].x;
+    const unsigned w = (unsigned)rec[v].y;
+    const int nba = (w & kJumpDone) ? (int)(w & ~kJumpDone) : a.u;  // not done: on or below a cycle
+    const int mb = in_tree_ids(pv, a.n) ? mark_bits(v, a.bflag[v], pv, a.bflag[pv]) : 0;
+    rec[v].y = nba | mb;
 }
 
 // ======================================================================================
@@ -2153,8 +2101,13 @@ hipError_t launch_wilson(const WilsonArgs &a, int blocks, bool lds_bits, bool co
     }
     return hipGetLastError();
 }
-hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, hipStream_t st) {
-    tree_records_kernel<<<ntrees, kIvThreads, 0, st>>>(a);
+hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hipStream_t st) {
+    const dim3 grid(blocks_for(a.n, 256), ntrees);
+    tree_jump_init_kernel<<<grid, 256, 0, st>>>(a);
+    int rounds = 1;  // 8^rounds >= n: then every path is covered (at most kTreeJumpRounds for n < 2^30)
+    for (long long len = 8; len < a.n; len *= 8) ++rounds;
+    for (int r = 0; r < rounds; ++r) tree_jump_kernel<<<grid, 256, 0, st>>>(a, open + r);
+    tree_records_kernel<<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
 }
 hipError_t launch_extract_parents(int n, int ntrees, const int2 *rec, long long rec_stride, int *out, hipStream_t st) {

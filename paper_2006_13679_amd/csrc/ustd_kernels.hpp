@@ -66,7 +66,7 @@ struct IntervalArgs {
     int n, u;
     const int *par;         // [ntrees][par_stride]
     long long par_stride;
-    int *scratch;           // [ntrees][scratch_stride], scratch_stride >= 7n + 3
+    int *scratch;           // [ntrees][scratch_stride], scratch_stride >= n
     long long scratch_stride;
     int2 *rec;              // [ntrees][rec_stride] {parent, nba | flags} records out
     long long rec_stride;
@@ -162,8 +162,6 @@ struct SolveJob {
     int maxit;
 };
 
-inline long long interval_scratch_ints(long long n) { return 7 * n + 3; }
-
 hipError_t launch_rp_to_i32(int n, const long long *rp64, int *rp32, hipStream_t st);
 hipError_t launch_validate(int n, long long nnz, const long long *rp64, const int *col, int *err, hipStream_t st);
 hipError_t launch_argmax_degree(int n, const int *rp, unsigned long long *best, hipStream_t st);
@@ -206,7 +204,9 @@ hipError_t launch_bpath(int n, int u, const int *rp, const int *col, const doubl
                         unsigned long long *rmax_bits, hipStream_t st);
 hipError_t launch_fixed_weights(int n, int u, const double *wB, int shift, long long *F, hipStream_t st);
 hipError_t launch_col_to_u16(long long nnz, const int *col, unsigned short *col16, hipStream_t st);
-hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, hipStream_t st);
+// ntrees <= 65535 and ntrees * n < 2^31; open[0] = 1, open[1 .. kTreeJumpRounds] = 0 at launch
+constexpr int kTreeJumpRounds = 11;
+hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hipStream_t st);
 hipError_t launch_aggregate(const AggregateArgs &a, hipStream_t st);
 hipError_t launch_extract_parents(int n, int ntrees, const int2 *rec, long long rec_stride, int *out, hipStream_t st);
 hipError_t launch_centralities(long long n, const double *diag, double *farness, double *closeness, double *nrwb,
