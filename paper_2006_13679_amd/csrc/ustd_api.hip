@@ -845,7 +845,10 @@ int sample_batch(Ctx &c, long long tree_begin, int ntrees, long long *steps, lon
 constexpr int kAggDeepEcc = 8;
 int agg_chunk(int ecc) { return ecc >= kAggDeepEcc ? kAggChunkLarge : kAggChunk; }
 // the form of Algorithm 2: a schedule's fixed chunk, else by eccentricity
-void agg_form(AggregateArgs &aa, int ecc, int sched_chunk) { aa.chunk = sched_chunk > 0 ? sched_chunk : agg_chunk(ecc); }
+void agg_form(AggregateArgs &aa, int ecc, int sched_chunk) {
+    aa.ecc = ecc;
+    aa.chunk = sched_chunk > 0 ? sched_chunk : agg_chunk(ecc);
+}
 
 // Algorithm 2 over `cnt` resident trees (records of a pool), on stream st
 int aggregate_trees(Ctx &c, int cnt, long long *counts, double *ms_ag, int pool = 0, hipStream_t st = nullptr) {

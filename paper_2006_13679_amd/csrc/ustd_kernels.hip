@@ -227,9 +227,8 @@ __global__ void count_unreached_kernel(int n, const int *__restrict__ dist, int 
 //     those needs no test at all: its end is in T for good, and nothing it adds is read by
 //     another.  Where the run holds longer walks, the vertices they read beside their start
 //     (inner vertices) are tested against the tree, and the batch commits up to the first
-//     walk that reads an inner vertex of an earlier one (two minimum-writer tables under
-//     independent hashes); the starts take part only if an inner vertex lies among the
-//     starts in flight, an interval since starts ascend;
+//     walk that reads an inner vertex of an earlier one; the starts take part only if an
+//     inner vertex lies among the starts in flight, an interval since starts ascend;
 //   - longer recorded walks (up to kPath steps) commit cooperatively: a lane per step, the
 //     loop erasure by one ballot and one lane read per branch vertex.  A walk that filled its
 //     record without reaching the tree it saw takes this path too: the tree has usually
@@ -396,6 +395,15 @@ __device__ __forceinline__ int hash_slot2(int v) {
 }
 static_assert(kHashSlots == 128, "the hashes give seven bits");
 
+// With the tree state in the records, a table of rounds tells which vertices may have joined T
+// lately without a global load: an inner vertex of a walk committed in round r (commits of a round
+// follow its steps) leaves r at its slot, so a vertex read as free in round q is still free if
+// its slot holds less than q and it is not a start that has been committed since.  A collision
+// only costs the load.
+constexpr int kStamps = 256;
+__device__ __forceinline__ int stamp_slot(int v) { return (int)(((unsigned)v * 2654435761u) >> 24); }
+static_assert(kStamps == 256, "the hash gives eight bits");
+
 // Neighbour index (0 .. deg-1) of a walk step with word w from the row [r0, r1).  Unit
 // weights: floor(w deg / 2^32).  Weighted (Section "Generalizations"): the first j with
 // t < C[j], C the row's running conductance sums (cw, taken left to right in FP64) and
@@ -534,7 +542,7 @@ __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, con
 // written with a placeholder and completed by lane 0 then.
 template <bool LDS, typename Next>
 __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw, const int *__restrict__ bflag, int u,
-                        int s0, int *buf) {
+                        int s0, int *buf, int *stamps, int round) {
     constexpr int kPiece = 2 * kHashSlots;
     const int lane = threadIdx.x;
     int z = s0, pend = -1;  // pend: first vertex whose nba is not known yet
@@ -572,6 +580,7 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw,
                 recw[2 * v] = nx;
                 recw[2 * v + 1] = (nba >= 0 ? nba : u) | mb;
                 bits.set(v);
+                if constexpr (!LDS) stamps[stamp_slot(v)] = round;
             }
             if (m) {
                 if (last < 0) last = __builtin_amdgcn_readlane(v, 63 - __builtin_clzll(m));
@@ -609,7 +618,9 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     __shared__ Steps rob_p[kRobMax];
     __shared__ uint8_t rob_k[kRobMax];
     __shared__ uint8_t rob_pb[kRobMax];  // edge bits of steps 1..kPathLds, 2 bits each
+    __shared__ uint16_t rob_r[LDS ? 1 : kRobMax];  // round of a finished walk's last step (low 16 bits)
     __shared__ alignas(16) int htab[2 * kHashSlots + 4];  // a word past the end is read, not used
+    __shared__ int stamps[LDS ? 1 : kStamps];
     __shared__ uint8_t win[kWin];  // free vertices of the window, as offsets
     int *const hslot = htab;                // first conflict table
     int *const hslot2 = htab + kHashSlots;  // second conflict table; together the one-lane walk's
@@ -690,6 +701,8 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
         for (int i = lane; i < n; i += kWave) rec[i] = make_int2(-1, kFree);
     }
     for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
+    if constexpr (!LDS)
+        for (int i = lane; i < kStamps; i += kWave) stamps[i] = -1;
     wave_sync();
     if constexpr (BV) {  // several roots (one per block of the block-split graph)
         for (int i = lane; i < a.nroots; i += kWave) {
@@ -705,9 +718,11 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
 
     int head = 0, tail = 0;               // wave-uniform
     int wend = 0, wpos = 0, wcnt = 0;     // the window is [wend - kWin, wend); list position and length
+    int wround = 0, shi = -1;             // the round that read the window; the last start taken
     int mode = 0;                         // 0 idle, 1 speculative walk
     int my_e = 0, x = 0, s = 0, wkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
     uint4 ph = make_uint4(0, 0, 0, 0);
+    int4 vx = make_int4(0, 0, 0, 0);  // tree state in the records: x's entry {row begin, row end, B_u flag, 0}
     long long steps = 0, draws = 0;
 
     // Marks the pending entries whose start has joined the tree (state 0).  With the LDS bitmap
@@ -738,7 +753,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
         if (want > 0 && (4 * want >= min(rob, kWave) || (round & 3) == 0 || head == tail) && (wpos < wcnt || wend < n)) {
             const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
-            int got = 0, mys = 0;
+            int got = 0, mys = 0, myr = 0;  // myr: the round that read the window of mys
             do {
                 if (wpos == wcnt) {
                     if (wend >= n) break;
@@ -753,16 +768,21 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     wcnt = __builtin_amdgcn_readlane(incl, kWave - 1);
                     wpos = 0;
                     wend += kWin;
+                    wround = round;
                     wave_sync();
                     continue;
                 }
                 const int take = min(want - got, wcnt - wpos);
                 const int j = rank - got;  // this lane's place in this take
-                if (mode == 0 && j >= 0 && j < take) mys = wend - kWin + (int)win[wpos + j];
+                if (mode == 0 && j >= 0 && j < take) {
+                    mys = wend - kWin + (int)win[wpos + j];
+                    myr = wround;
+                }
                 got += take;
                 wpos += take;
             } while (got < want);
-            if (mode == 0 && rank < got) {
+            const bool mode0 = mode == 0;
+            if (mode0 && rank < got) {
                 my_e = tail + rank;
                 s = mys;
                 wkey = s;
@@ -775,12 +795,9 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     r1 = rp[s + 1];
                     fx = bflag[s];
                     gone = bits.test(s);
-                } else {  // the vertex entry {row begin, row end, B_u flag}: one load
-                    const int4 vr = vrow[s];
-                    gone = bits.test(s);
-                    r0 = vr.x;
-                    r1 = vr.y;
-                    fx = vr.z;
+                } else {
+                    vx = vrow[s];  // in flight until the step's random words are there
+                    gone = stamps[stamp_slot(s)] >= myr && bits.test(s);
                 }
                 pbits = 0;
                 mode = gone ? 0 : 1;
@@ -788,6 +805,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 rob_e[sl].s = (CT)s;
                 rob_k[sl] = (uint8_t)(gone ? 0 : kWalking);
             }
+            if (got > 0) shi = __builtin_amdgcn_readlane(mys, __builtin_ctzll(__ballot(mode0 && rank == got - 1)));
             tail += got;
         }
         if (head == tail && wpos == wcnt && wend >= n) break;
@@ -800,25 +818,20 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), (uint32_t)wkey, tlo, thi), g.key0, g.key1);
             const int q = k & 3;
             const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
-            // y, its B_u flag and its row bounds.  With the tree bitmap in LDS (small graphs,
-            // whose compact column and row arrays stay in cache): a column load, then the
-            // flag, and the row bounds only if the walk goes on.  Otherwise one edge-entry load.
-            const int e = r0 + step_index<WT>(w, r0, r1, cw, guide);
-            int y, fy, ny0 = 0, ny1 = 0;
-            if constexpr (LDS) {
-                y = (int)col[e];
-                fy = bflag[y];
-            } else {
-                const int4 ey = edge[e];
-                y = ey.x;
-                fy = ey.w;
-                ny0 = ey.y;
-                ny1 = ey.z;
+            if constexpr (!LDS) {
+                r0 = vx.x;
+                r1 = vx.y;
+                fx = vx.z;
             }
-            // y's tree membership, with the chain value when the walk ends here
+            const int y = (int)col[r0 + step_index<WT>(w, r0, r1, cw, guide)];
+            // y's tree membership, with the chain value when the walk ends here, and its B_u flag.
+            // With the tree bitmap in LDS (small graphs, whose compact arrays stay in cache) y's row
+            // bounds come along if the walk goes on; else y's entry is loaded at the end, and the
+            // flag is needed only where x -> y may be a backward B_u edge (x internal in B_u).
             bool in, gone = false;
-            int cvy = 0;
+            int cvy = 0, fy = 0, ny0 = 0, ny1 = 0;
             if constexpr (LDS) {
+                fy = bflag[y];
                 in = bits.test(y);
                 gone = bits.test(s);  // the start has been absorbed: the walk never counts
                 if (in) {
@@ -829,6 +842,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 }
             } else {
                 cvy = bits.nbx(y);  // membership and chain value in one load
+                if (bf_internal(fx)) fy = bflag[y];
                 in = cvy != kFree;
             }
             consume(fy, cvy, ny0, ny1);  // no load may stay in flight into the commit phase
@@ -844,9 +858,22 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 gpath[sl * kSamplerPathGlobal + (k - 1 - kPathLds)] = y | (eb << 30);
             }
             if (gone) { rob_k[sl] = 0; mode = 0; }
-            else if (in) { rob_k[sl] = (uint8_t)k; rob_e[sl].cv = (CT)cvy; mode = 0; }
-            else if (k == kPath) { rob_k[sl] = (uint8_t)kOverflow; mode = 0; }
-            else { x = y; fx = fy; r0 = ny0; r1 = ny1; }
+            else if (in) {
+                rob_k[sl] = (uint8_t)k;
+                rob_e[sl].cv = (CT)cvy;
+                if constexpr (!LDS) rob_r[sl] = (uint16_t)round;
+                mode = 0;
+            } else if (k == kPath) { rob_k[sl] = (uint8_t)kOverflow; mode = 0; }
+            else {
+                x = y;
+                if constexpr (LDS) {
+                    fx = fy;
+                    r0 = ny0;
+                    r1 = ny1;
+                } else {
+                    vx = vrow[y];
+                }
+            }
         }
         wave_sync();
 
@@ -882,6 +909,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     wave_sync();
                     continue;
                 }
+                const int slo = __builtin_amdgcn_readfirstlane(s0);  // the starts in flight: slo .. shi
                 const int x2 = (int)st.v[1], x3 = (int)st.v[2], x4 = (int)st.v[3];
                 const bool any3 = __ballot(K >= 3) != 0ull, any4 = __ballot(K >= 4) != 0ull;  // uniform
                 // truncation at the first vertex in T0, whose chain value is then its own
@@ -893,9 +921,17 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                         if (any3 && K >= 3 && bits.test(x2)) n2 = 0;
                         if (any4 && K >= 4 && bits.test(x3)) n3 = 0;
                     } else {
-                        if (K >= 2) n1 = bits.nbx(x1);
-                        if (K >= 3) n2 = bits.nbx(x2);
-                        if (K >= 4) n3 = bits.nbx(x3);
+                        // x_j was read free in round fin - (K - j); a load only if it may have joined
+                        const int fin = round - ((round - (int)rob_r[sl]) & 0xFFFF);
+                        auto stale = [&](int v, int r) { return v < slo || stamps[stamp_slot(v)] >= r; };
+                        const bool t1 = K >= 2 && stale(x1, fin - K + 1);
+                        const bool t2 = any3 && K >= 3 && stale(x2, fin - K + 2);
+                        const bool t3 = any4 && K >= 4 && stale(x3, fin - K + 3);
+                        if (__ballot(t1 || t2 || t3)) {
+                            if (t1) n1 = bits.nbx(x1);
+                            if (t2) n2 = bits.nbx(x2);
+                            if (t3) n3 = bits.nbx(x3);
+                        }
                     }
                     int nt = kFree;
                     if (n3 != kFree) { istar = 3; ya = x3; nt = n3; }
@@ -920,7 +956,6 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     }
                 }
                 // an inner vertex (read, not in T0) among the starts in flight?
-                const int slo = __builtin_amdgcn_readfirstlane(s0), shi = wend - 1;
                 bool inr = istar >= 2 && x1 >= slo && x1 <= shi;
                 if (any3) inr = inr || (istar >= 3 && x2 >= slo && x2 <= shi) || (istar >= 4 && x3 >= slo && x3 <= shi);
                 const bool starts = __ballot(inr) != 0ull;
@@ -958,6 +993,9 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                             const int mb = (int)((unsigned)(pb >> (2 * j)) << 30);
                             rec[v] = make_int2(pv, carry | mb);
                             bits.set(v);
+                            if constexpr (!LDS) {
+                                if (j > 0) stamps[stamp_slot(v)] = round;
+                            }
                             carry = mb ? v : carry;
                             pv = v;
                         }
@@ -1033,7 +1071,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
                 const long long kk = walk_next<LDS, CT, WT>(bits, next, rp, col, edge, vrow, cw, guide, wk0, xs, k0, tlo, thi,
                                                             g.key0, g.key1, reinterpret_cast<uint32_t *>(htab));
-                retrace<LDS>(bits, next, recw, bflag, u, s0, htab);
+                retrace<LDS>(bits, next, recw, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
                 if (lane == 0) {
                     steps += kk;
@@ -1119,7 +1157,6 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
             }
             // records of the kept positions, attached to ya: x_q's parent is x_{q+1}, its flags the
             // edge bits of step q+1, its nba the next marked kept vertex
-            const int shi = wend - 1;
             bool inr = false;
 #pragma unroll
             for (int c = 3; c >= 0; --c) {
@@ -1138,6 +1175,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     if (mine) {
                         rec[xv[c]] = make_int2(nx, (above ? up : carry) | (nb << 30));
                         bits.set(xv[c]);
+                        if constexpr (!LDS) stamps[stamp_slot(xv[c])] = round;
                         inr = inr || (xv[c] > s0 && xv[c] <= shi);
                     }
                     if (m) carry = __builtin_amdgcn_readlane(xv[c], __builtin_ctzll(m));
@@ -1249,13 +1287,19 @@ __global__ __launch_bounds__(256) void tree_records_kernel(IntervalArgs a) {
 //   c_T(v) = [parent_T(v) = parB(v)]
 //          + sum over marked strict T-ancestors x of v lying on P(v) of
 //              +1 if parent_T(x) = parB(x),  -1 if parB(parent_T(x)) = x and parent_T(x) on P(v),
-// which equals Algorithm 2's signed count term by term.  "On P(v)" is the B_u subtree test
-// pre_B(x) <= pre_B(v) < pre_B(x) + size_B(x).  Thread per vertex over a chunk of resident
-// trees; one int64 atomic per vertex and chunk, skipped when the sum is zero.
+// which equals Algorithm 2's signed count term by term.  Thread per vertex over a chunk of
+// resident trees; one int64 atomic per vertex and chunk, skipped when the sum is zero.
+//
+// "On P(v)", two forms.  PL > 0 (shallow B_u): P(v) has at most ecc(u) - 1 <= PL vertices p_1 ..
+// beside v and u, which the thread keeps in registers, p_0 = v: x is on P(v) if it is one of
+// them, and a backward x = p_i counts if parent_T(x) = p_{i-1}, its B_u child towards v.  PL = 0:
+// the B_u subtree test pre_B(x) <= pre_B(v) < pre_B(x) + size_B(x).  What bounds the kernel is
+// its gathers, one per lane and chain vertex for the record and, with PL = 0, one more for the
+// interval.
 // ======================================================================================
 // WT: weighted graph, the edge (parB(b), b) of P(v) counts +-F[b] (Ohm's-law factor in fixed
 // point) instead of +-1.
-template <bool WT, int CH>
+template <bool WT, int CH, int PL>
 __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
     const int v = blockIdx.x * blockDim.x + threadIdx.x;
     if (v >= a.n || v == a.u) return;
@@ -1263,8 +1307,9 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
     const int nt = min(a.ntrees - t0, CH);
     const int u = a.u;
     const int2 *__restrict__ bint = a.bint;
-    const int pbv = a.parB[v];
-    const int pv = bint[v].x;
+    const int *__restrict__ parB = a.parB;
+    const int pbv = parB[v];
+    const int pv = PL ? 0 : bint[v].x;
     const int2 *__restrict__ rec0 = a.rec + (long long)t0 * a.rec_stride;
     // The chains of the chunk's trees are walked in lockstep, one step of every unfinished
     // chain per round, so their independent loads are in flight together.
@@ -1283,6 +1328,16 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
             if (x[i] >= a.n) x[i] = u;
         }
     }
+    int p[PL + 1];  // p_0 = v, p_1 = parB(v), ..; -1 from u on
+    p[0] = v;
+    if constexpr (PL > 0) {
+        int b = pbv;
+#pragma unroll
+        for (int i = 1; i <= PL; ++i) {
+            p[i] = b != u ? b : -1;
+            if (i < PL && b != u) b = parB[b];
+        }
+    }
     // a chain visits each T-ancestor at most once: n rounds bound it even on broken records
     for (int round = 0; round < a.n; ++round) {
         int2 rx[CH], bx[CH];
@@ -1292,7 +1347,7 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
             if (x[i] != u) {
                 act = true;
                 rx[i] = rec0[(long long)i * a.rec_stride + x[i]];
-                bx[i] = bint[x[i]];
+                if constexpr (PL == 0) bx[i] = bint[x[i]];
             }
         }
         if (!act) break;
@@ -1301,8 +1356,22 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
             if (x[i] != u) {
                 // a forward x counts +1 if x is on P(v); a backward x counts -1 if parent_T(x),
                 // a B_u child of x, is on P(v), which needs x on P(v) first
-                if (bx[i].x <= pv && pv < bx[i].x + bx[i].y) {
-                    if (rx[i].y & kFwdBit) {
+                const bool fwd = rx[i].y & kFwdBit;
+                if constexpr (PL > 0) {
+                    bool on = false, below = false;
+#pragma unroll
+                    for (int j = 1; j <= PL; ++j) {
+                        const bool e = x[i] == p[j];
+                        on |= e;
+                        below |= e & (rx[i].x == p[j - 1]);
+                    }
+                    if constexpr (WT) {
+                        if (fwd ? on : below) sum += fwd ? F[x[i]] : -F[rx[i].x];
+                    } else {
+                        sum += fwd ? (int)on : -(int)below;
+                    }
+                } else if (bx[i].x <= pv && pv < bx[i].x + bx[i].y) {
+                    if (fwd) {
                         if constexpr (WT) sum += F[x[i]];
                         else ++sum;
                     } else {
@@ -2170,16 +2239,21 @@ hipError_t launch_edge_fold(int n, long long nnz, const int *rp, const int *col,
     edge_fold_kernel<<<blocks_for(nnz, 256), 256, 0, st>>>(n, nnz, rp, col, counts);
     return hipGetLastError();
 }
+template <int CH, int PL>
+static void launch_aggregate_t(const AggregateArgs &a, hipStream_t st) {
+    const dim3 grid(blocks_for(a.n, 256), (a.ntrees + CH - 1) / CH);
+    if (a.F) aggregate_kernel<true, CH, PL><<<grid, 256, 0, st>>>(a);
+    else aggregate_kernel<false, CH, PL><<<grid, 256, 0, st>>>(a);
+}
+template <int CH>
+static void launch_aggregate_c(const AggregateArgs &a, hipStream_t st) {
+    if (a.ecc >= 1 && a.ecc <= 5) launch_aggregate_t<CH, 4>(a, st);
+    else if (a.ecc >= 1 && a.ecc <= 9) launch_aggregate_t<CH, 8>(a, st);
+    else launch_aggregate_t<CH, 0>(a, st);
+}
 hipError_t launch_aggregate(const AggregateArgs &a, hipStream_t st) {
-    const int ch = a.chunk == kAggChunkLarge ? kAggChunkLarge : kAggChunk;
-    dim3 grid(blocks_for(a.n, 256), (a.ntrees + ch - 1) / ch);
-    if (ch == kAggChunkLarge) {
-        if (a.F) aggregate_kernel<true, kAggChunkLarge><<<grid, 256, 0, st>>>(a);
-        else aggregate_kernel<false, kAggChunkLarge><<<grid, 256, 0, st>>>(a);
-    } else {
-        if (a.F) aggregate_kernel<true, kAggChunk><<<grid, 256, 0, st>>>(a);
-        else aggregate_kernel<false, kAggChunk><<<grid, 256, 0, st>>>(a);
-    }
+    if (a.chunk == kAggChunkLarge) launch_aggregate_c<kAggChunkLarge>(a, st);
+    else launch_aggregate_c<kAggChunk>(a, st);
     return hipGetLastError();
 }
 __global__ void fill_i64_kernel(long long n, long long *__restrict__ a, long long v) {

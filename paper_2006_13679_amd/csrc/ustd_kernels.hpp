@@ -81,6 +81,7 @@ constexpr int kAggChunkLarge = 4;
 
 struct AggregateArgs {
     int n, u, ntrees;
+    int ecc;                // ecc(u): the form of the path test
     const int *parB;        // [n] B_u parents
     const int2 *bint;       // [n] {pre_B, size_B} subtree intervals of B_u
     const int2 *rec;
