@@ -135,7 +135,7 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     const double avg = (double)L.nnz / (double)L.n;
     L.G = avg <= 6.0 ? 4 : (avg <= 16.0 ? 8 : (avg <= 48.0 ? 16 : 32));
     L.heavy_thresh = 32 * L.G;
-    L.rec_stride = align_up((long long)L.n * 8) / 8;  // int2 records
+    L.rec_stride = align_up((long long)L.n * 8) / 8;  // two ints per vertex, padded to 32 vertices
     // trees resident at once (records), and sampler blocks resident at once (scratch slots).
     // Graphs past the LDS bitmap run several batches.  When the budget holds two pools that
     // can each fill the GPU (kPoolMinTrees trees), they are sampled on two streams, so one
@@ -749,6 +749,7 @@ WilsonGraph wilson_graph(const Ctx &c) {
     g.u = c.pivot;
     g.nwords = c.L.nwords;
     g.rob = c.L.rob;
+    g.rec_stride = (int)c.L.rec_stride;
     g.rp = c.rp32;
     g.colv = c.L.col16 ? (const void *)at<unsigned short>(c.ws, c.L.off_col16) : (const void *)c.p->d_col;
     g.bflag = at<int>(c.ws, c.L.off_bflag);
@@ -762,7 +763,7 @@ WilsonGraph wilson_graph(const Ctx &c) {
 }
 
 // records, sampler slots, step and draw counts of tree pool `pool`
-int2 *pool_rec(const Ctx &c, int pool) { return at<int2>(c.ws, c.L.off_rec) + (long long)pool * c.L.K * c.L.rec_stride; }
+int *pool_rec(const Ctx &c, int pool) { return at<int>(c.ws, c.L.off_rec) + (long long)pool * c.L.K * 2 * c.L.rec_stride; }
 long long *pool_steps(const Ctx &c, int pool) { return at<long long>(c.ws, c.L.off_steps) + (long long)pool * c.L.K; }
 long long *pool_draws(const Ctx &c, int pool) { return at<long long>(c.ws, c.L.off_draws) + (long long)pool * c.L.K; }
 
@@ -789,9 +790,10 @@ int sample_batch_blocks(Ctx &c, long long tree_begin, int ntrees, long long *ste
     g.key1 = (uint32_t)(c.p->seed >> 32);
     a.ntiles = ntrees;
     a.tree_begin = tree_begin;
-    int2 *srec = at<int2>(c.ws, L.off_srec) + (long long)pool * L.K * L.s_rec_stride;
+    int *srec = at<int>(c.ws, L.off_srec) + (long long)pool * L.K * 2 * L.s_rec_stride;
     a.rec = srec;
-    a.rec_stride = L.s_rec_stride;
+    a.parents = 1;
+    g.rec_stride = (int)L.s_rec_stride;
     a.path = at<int>(c.ws, L.off_path) + (long long)pool * L.slots * kSamplerPathSlot;
     a.queue = &c.misc->queue[pool];
     a.steps = steps;
@@ -810,8 +812,9 @@ int sample_batch_blocks(Ctx &c, long long tree_begin, int ntrees, long long *ste
     return USTD_OK;
 }
 
-int sample_batch(Ctx &c, long long tree_begin, int ntrees, long long *steps, long long *draws, int pool = 0,
-                 hipStream_t st = nullptr) {
+// parents: every vertex's parent is wanted (else those that Algorithm 2 reads)
+int sample_batch(Ctx &c, long long tree_begin, int ntrees, long long *steps, long long *draws, bool parents,
+                 int pool = 0, hipStream_t st = nullptr) {
     if (!st) st = c.st;
     if (c.L.bv) return sample_batch_blocks(c, tree_begin, ntrees, steps, draws, pool, st);
     WilsonArgs a{};
@@ -819,7 +822,7 @@ int sample_batch(Ctx &c, long long tree_begin, int ntrees, long long *steps, lon
     a.ntiles = ntrees;
     a.tree_begin = tree_begin;
     a.rec = pool_rec(c, pool);
-    a.rec_stride = c.L.rec_stride;
+    a.parents = parents ? 1 : 0;
     a.path = at<int>(c.ws, c.L.off_path) + (long long)pool * c.L.slots * kSamplerPathSlot;
     a.queue = &c.misc->queue[pool];
     a.steps = steps;
@@ -923,7 +926,7 @@ int run_trees(Ctx &c, long long tree_begin, long long tree_count, long long *cou
         ts.emplace_back(new SpanTimer());
         ta.emplace_back(new SpanTimer());
         ts.back()->start(s);
-        rc = sample_batch(c, tree_begin + b0, cnt, pool_steps(c, pool), pool_draws(c, pool), pool, s);
+        rc = sample_batch(c, tree_begin + b0, cnt, pool_steps(c, pool), pool_draws(c, pool), edge_counts != nullptr, pool, s);
         if (rc != USTD_OK) break;
         ts.back()->stop(s);
         if (last_sampled && b0 + per >= tree_count && hipEventRecord(last_sampled, s) != hipSuccess) {
@@ -1465,9 +1468,9 @@ int batch_plan_create(const ustd_problem *probs, int count, void *d_ws, size_t w
             for (auto &pr : mem) {
                 const int gi = pr.first;
                 const long long take = pr.second;
-                G.segs.push_back(BatchSeg{gi, take, rec_used / 8});
+                G.segs.push_back(BatchSeg{gi, take, rec_used / 4});
                 for (long long j = 0; j < take; ++j)
-                    tiles.push_back(WilsonTile{next[gi] + j, rec_used / 8 + j * B.g[gi].rec_stride, gi, 0});
+                    tiles.push_back(WilsonTile{next[gi] + j, rec_used / 4 + j * 2 * B.g[gi].rec_stride, gi, 0});
                 rec_used += take * B.g[gi].rec_stride * 8;
                 next[gi] += take;
             }
@@ -1623,7 +1626,7 @@ int batch_plan_execute(ustd_batch_plan &P, double *const *d_diags, int64_t *cons
     if (timed) P.t_solve->start(side);
     USTD_TRY(enqueue_small_solves(P, cs, side));
 
-    int2 *pool = at<int2>(P.ws, B.off_rec);
+    int *pool = at<int>(P.ws, B.off_rec);
     long long *steps = at<long long>(P.ws, B.off_steps), *draws = at<long long>(P.ws, B.off_draws);
     int *queue = at<int>(P.ws, B.off_queue);
     for (size_t f = 0; f < P.fills.size(); ++f) {
@@ -1984,8 +1987,8 @@ int ustd_sample_trees(const ustd_problem *prob, int64_t tree_begin, int64_t tree
     USTD_TRY(setup(c, nullptr));
     if (tree_count == 0) return USTD_OK;
     long long *steps = d_steps ? (long long *)d_steps : at<long long>(c.ws, c.L.off_steps);
-    USTD_TRY(sample_batch(c, tree_begin, (int)tree_count, steps, at<long long>(c.ws, c.L.off_draws)));
-    HIP_TRY(launch_extract_parents(c.L.n, (int)tree_count, at<int2>(c.ws, c.L.off_rec), c.L.rec_stride, d_parents, c.st));
+    USTD_TRY(sample_batch(c, tree_begin, (int)tree_count, steps, at<long long>(c.ws, c.L.off_draws), true));
+    HIP_TRY(launch_extract_parents(c.L.n, (int)tree_count, at<int>(c.ws, c.L.off_rec), c.L.rec_stride, d_parents, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
     return USTD_OK;
 }
@@ -2040,7 +2043,7 @@ int ustd_tree_counts(const ustd_problem *prob, const int32_t *d_parents, int64_t
         ia.u = c.pivot;
         ia.par = d_parents + b0 * c.L.n;
         ia.par_stride = c.L.n;
-        ia.rec = at<int2>(c.ws, c.L.off_rec);
+        ia.rec = at<int>(c.ws, c.L.off_rec);
         ia.rec_stride = c.L.rec_stride;
         ia.scratch = at<int>(c.ws, c.L.off_rec + cnt * rec_bytes);
         ia.scratch_stride = word_bytes / 4;

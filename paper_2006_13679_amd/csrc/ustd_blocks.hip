@@ -400,15 +400,15 @@ __global__ void fill_i32_kernel(long long n, int *__restrict__ a, int v) {
 // Re-root every block's tree at its top vertex's slot: thread per (tree, block); the path from
 // the top slot up to the block's root is reversed (at most the block's size steps).
 __global__ void bc_reroot_kernel(int ntop, const int *__restrict__ tops, int ntrees, int nslots,
-                                 int2 *__restrict__ recs, long long stride) {
+                                 int *__restrict__ recs, long long stride) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)ntop * ntrees) return;
     const long long t = i / ntop;
-    int *par = reinterpret_cast<int *>(recs + t * stride);  // par[2 s] = parent slot of s
+    int *par = recs + (2 * t + 1) * stride;  // parent slots
     int x = tops[i - t * ntop], prev = -1;
     for (int steps = 0; x >= 0 && x < nslots && steps < nslots; ++steps) {  // a path of a tree: bounded
-        const int up = par[2 * x];
-        par[2 * x] = prev;
+        const int up = par[x];
+        par[x] = prev;
         prev = x;
         x = up;
     }
@@ -416,28 +416,28 @@ __global__ void bc_reroot_kernel(int ntop, const int *__restrict__ tops, int ntr
 
 // parent in G of every vertex v != u: the vertex of the parent slot of v's slot in its own block
 __global__ void bc_map_parents_kernel(int n, int u, int ntrees, const int *__restrict__ slotPar,
-                                      const int *__restrict__ vtx, const int2 *__restrict__ recs, long long sstride,
-                                      int2 *__restrict__ rec, long long stride) {
+                                      const int *__restrict__ vtx, const int *__restrict__ recs, long long sstride,
+                                      int *__restrict__ rec, long long stride) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * ntrees) return;
     const long long t = i / n;
     const int v = (int)(i - t * n);
-    int *out = reinterpret_cast<int *>(rec + t * stride);
-    const int ps = v == u ? -1 : recs[t * sstride + slotPar[v]].x;
-    out[2 * v] = ps >= 0 ? vtx[ps] : -1;
+    int *out = rec + (2 * t + 1) * stride;
+    const int ps = v == u ? -1 : recs[(2 * t + 1) * sstride + slotPar[v]];
+    out[v] = ps >= 0 ? vtx[ps] : -1;
 }
 
-// the {nba | marks} half of each vertex's record for Algorithm 2, from the parents: the marks
+// the word nba | flags of each vertex's record for Algorithm 2, from the parents: the marks
 // of v and its tree edge, and the nearest marked strict ancestor nba(v) (u if none).  A vertex
 // y is marked when its own tree edge (y, parent(y)) is an edge of B_u.
 __device__ __forceinline__ int bf_parent_b(int f) { return (int)((unsigned)f & 0x7FFFFFFFu) - 1; }
 __device__ __forceinline__ int marks_of(int x, int fx, int px, int fpx) {
     const unsigned fwd = px == bf_parent_b(fx), bwd = bf_parent_b(fpx) == x;
     const unsigned m = ((unsigned)fx >> 31) & (fwd | bwd);
-    return (int)((m << 31) | ((m & fwd) << 30));
+    return (int)((m << 31) | (fwd << 30));
 }
 
-// nba by pointer jumping, in place in the record's second word: jw(v) = J | done << 31, where J
+// nba by pointer jumping, in place in the record's word: jw(v) = J | done << 31, where J
 // is an ancestor of v such that every vertex from parent(v) up to J is unmarked and not u
 // (not done), or J = nba(v) (done).  Start: J = parent(v), done when parent(v) is u or marked.
 // A step replaces jw(v) by jw(J): nba(v) = nba(J) when J is unmarked, and the path covered
@@ -445,32 +445,33 @@ __device__ __forceinline__ int marks_of(int x, int fx, int px, int fpx) {
 // steps run concurrently without ordering; the words are single 32-bit loads and stores.
 constexpr unsigned kJumpDone = 0x80000000u;
 
-__global__ void bc_nba_init_kernel(int n, int u, int ntrees, const int *__restrict__ bflag, int2 *__restrict__ rec,
+__global__ void bc_nba_init_kernel(int n, int u, int ntrees, const int *__restrict__ bflag, int *__restrict__ rec,
                                    long long stride) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * ntrees) return;
     const long long t = i / n;
     const int v = (int)(i - t * n);
-    int *r = reinterpret_cast<int *>(rec + t * stride);
-    const int pv = v == u ? -1 : r[2 * v];
+    int *r = rec + 2 * t * stride;
+    const int *par = r + stride;
+    const int pv = v == u ? -1 : par[v];
     unsigned jw;
     if (pv < 0 || pv >= n || pv == u) {  // out-of-range never for a joined tree; keeps accesses in bounds
         jw = (unsigned)u | kJumpDone;
     } else {
-        const int ppv = r[2 * pv];
-        const bool marked = ppv >= 0 && ppv < n && marks_of(pv, bflag[pv], ppv, bflag[ppv]) != 0;
+        const int ppv = par[pv];
+        const bool marked = ppv >= 0 && ppv < n && marks_of(pv, bflag[pv], ppv, bflag[ppv]) < 0;
         jw = (unsigned)pv | (marked ? kJumpDone : 0u);
     }
-    r[2 * v + 1] = (int)jw;
+    r[v] = (int)jw;
 }
 
-__global__ void bc_nba_jump_kernel(int n, int ntrees, int2 *__restrict__ rec, long long stride) {
+__global__ void bc_nba_jump_kernel(int n, int ntrees, int *__restrict__ rec, long long stride) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * ntrees) return;
     const long long t = i / n;
     const int v = (int)(i - t * n);
-    int *r = reinterpret_cast<int *>(rec + t * stride);
-    unsigned jw = __hip_atomic_load(r + 2 * v + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    int *r = rec + 2 * t * stride;
+    unsigned jw = __hip_atomic_load(r + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // each step moves J at least one vertex up the tree: at most n steps
     for (int steps = 0; !(jw & kJumpDone) && steps < n; ++steps) {
         const int x = (int)(jw & ~kJumpDone);
@@ -478,29 +479,29 @@ __global__ void bc_nba_jump_kernel(int n, int ntrees, int2 *__restrict__ rec, lo
             jw = kJumpDone;  // never for a joined tree
             break;
         }
-        jw = __hip_atomic_load(r + 2 * x + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(r + 2 * v + 1, (int)jw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        jw = __hip_atomic_load(r + x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(r + v, (int)jw, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
 // the final record word: nba(v) | marks of v
-__global__ void bc_records_kernel(int n, int u, int ntrees, const int *__restrict__ bflag, int2 *__restrict__ rec,
+__global__ void bc_records_kernel(int n, int u, int ntrees, const int *__restrict__ bflag, int *__restrict__ rec,
                                   long long stride) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * ntrees) return;
     const long long t = i / n;
     const int v = (int)(i - t * n);
-    int *r = reinterpret_cast<int *>(rec + t * stride);
+    int *r = rec + 2 * t * stride;
     if (v == u) {
-        r[2 * v + 1] = u;
+        r[v] = u;
         return;
     }
-    const int pv = r[2 * v];
-    const unsigned jw = (unsigned)r[2 * v + 1];
+    const int pv = r[stride + v];
+    const unsigned jw = (unsigned)r[v];
     int y = (int)(jw & ~kJumpDone);
     if (!(jw & kJumpDone) || y >= n) y = u;  // never for a joined tree
     const int mv = pv >= 0 && pv < n ? marks_of(v, bflag[v], pv, bflag[pv]) : 0;
-    r[2 * v + 1] = y | mv;
+    r[v] = y | mv;
 }
 
 // ======================================================================================
@@ -568,7 +569,7 @@ hipError_t launch_fill_i32(long long n, int *a, int v, hipStream_t st) {
 }
 
 hipError_t launch_bc_join(int n, int u, int ntrees, int ntop, int nslots, const int *tops, const int *slotPar,
-                          const int *vtx, int2 *recs, long long sstride, int2 *rec, long long stride,
+                          const int *vtx, int *recs, long long sstride, int *rec, long long stride,
                           const int *bflag, hipStream_t st) {
     if (ntrees <= 0) return hipSuccess;
     // One work-item per (vertex, tree), and a dispatch counts its work-items in 32 bits: the
@@ -577,8 +578,8 @@ hipError_t launch_bc_join(int n, int u, int ntrees, int ntop, int nslots, const 
     const int chunk = (int)std::max(1ll, std::min<long long>(ntrees, (1ll << 31) / per));
     for (int t0 = 0; t0 < ntrees; t0 += chunk) {
         const int nt = std::min(chunk, ntrees - t0);
-        int2 *rs = recs + (long long)t0 * sstride;
-        int2 *rr = rec + (long long)t0 * stride;
+        int *rs = recs + (long long)t0 * 2 * sstride;
+        int *rr = rec + (long long)t0 * 2 * stride;
         bc_reroot_kernel<<<bgrid((long long)ntop * nt, 256), 256, 0, st>>>(ntop, tops, nt, nslots, rs, sstride);
         bc_map_parents_kernel<<<bgrid((long long)n * nt, 256), 256, 0, st>>>(n, u, nt, slotPar, vtx, rs, sstride,
                                                                              rr, stride);

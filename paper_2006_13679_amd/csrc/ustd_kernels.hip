@@ -245,7 +245,8 @@ __global__ void count_unreached_kernel(int n, const int *__restrict__ dist, int 
 // fewer trees than SIMDs), 8.58 to 5.36 ms (R-MAT 16 edge counts), 13.1 to 11.2 ms (R-MAT 16),
 // 316 to 243 ms (hyperbolic, 200k vertices) and 5.1 to 3.9 ms (32 x 32 grid).
 //
-// Output per vertex x: rec[x] = {parent_T(x), nba(x) | flags} (see "Marked vertices").
+// Output per vertex x: the word nba(x) | flags and, where the caller or Algorithm 2 reads it,
+// parent_T(x) (see "Marked vertices").
 // Launches are persistent: each block takes tree after tree from a queue.
 // ======================================================================================
 namespace {
@@ -276,8 +277,8 @@ static_assert(kWin == 4 * kWave, "four vertices of the window per lane");
 constexpr int kFree = 0x3FFFFFFF;  // nba of a vertex not in the tree; vertex IDs are below it
 
 // the {nba | flags} word of a record another lane of the wave may have written
-__device__ __forceinline__ int load_nbx(const int *recw, int v) {
-    return __hip_atomic_load(recw + 2 * v + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+__device__ __forceinline__ int load_nbx(const int *nbw, int v) {
+    return __hip_atomic_load(nbw + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 template <bool LDS>
@@ -297,18 +298,13 @@ struct TreeState<true> {
 
 template <>
 struct TreeState<false> {
-    int *recw;  // int pairs {parent, nba | flags}
-    __device__ __forceinline__ int nbx(int v) const { return load_nbx(recw, v); }
+    int *nbw;  // the tree's nba words
+    __device__ __forceinline__ int nbx(int v) const { return load_nbx(nbw, v); }
     __device__ __forceinline__ uint32_t free4(int base, int lane, int n) const {
         const int v = base + 4 * lane;
         if (v >= n) return 0u;
-        int w[4];  // the records of a tree are padded to 32 vertices
-#pragma unroll
-        for (int b = 0; b < 4; ++b) w[b] = nbx(v + b);
-        uint32_t m = 0u;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) m |= w[b] == kFree ? 1u << b : 0u;
-        return m;
+        const int4 w = *reinterpret_cast<const int4 *>(nbw + v);  // padded to 32 vertices
+        return (w.x == kFree ? 1u : 0u) | (w.y == kFree ? 2u : 0u) | (w.z == kFree ? 4u : 0u) | (w.w == kFree ? 8u : 0u);
     }
     __device__ __forceinline__ bool test(int v) const { return nbx(v) != kFree; }
     __device__ __forceinline__ void set(int) const {}
@@ -329,19 +325,20 @@ struct TreeState<false> {
 // bflag[x] = (parB(x) + 1) | (1 << 31 if x is internal in B_u), so parB(u) = -1.
 __device__ __forceinline__ int bf_parent(int f) { return (int)((unsigned)f & 0x7FFFFFFFu) - 1; }
 __device__ __forceinline__ bool bf_internal(int f) { return (unsigned)f >> 31; }
-// A record is {parent_T(x), nba(x) | flags}: bit 31 = x is marked, bit 30 = its tree edge
-// is a forward B_u edge (parent_T(x) = parB(x)), else it is a backward one
-// (parB(parent_T(x)) = x).  Vertex IDs are < 2^30 (a connected graph with nnz < 2^31).
-// cv(x) follows from the record.
+// A record is the word nba(x) | flags and parent_T(x), in two arrays per tree: what a walk that
+// ends at x and Algorithm 2 read is the word, so a line holds 32 vertices of it.  Bit 31 = x is
+// marked, bit 30 = its tree edge is a forward B_u edge (parent_T(x) = parB(x), marked or not); a
+// marked vertex without it has a backward one (parB(parent_T(x)) = x).  Vertex IDs are < 2^30 (a
+// connected graph with nnz < 2^31).  cv(x) follows from the word.
 constexpr int kMarkBit = (int)0x80000000u;
 constexpr int kFwdBit = 0x40000000;
-__device__ __forceinline__ int cv_of(int x, int nbx) { return (nbx & kMarkBit) ? x : nbx; }
 __device__ __forceinline__ int nba_of(int nbx) { return nbx & 0x3FFFFFFF; }
+__device__ __forceinline__ int cv_of(int x, int nbx) { return (nbx & kMarkBit) ? x : nba_of(nbx); }
 // the flag bits of vertex x (B_u flag word fx) whose tree parent is px (flag word fpx)
 __device__ __forceinline__ int mark_bits(int x, int fx, int px, int fpx) {
     const unsigned fwd = px == bf_parent(fx), bwd = bf_parent(fpx) == x;
     const unsigned m = (unsigned)bf_internal(fx) & (fwd | bwd);
-    return (int)((m << 31) | ((m & fwd) << 30));
+    return (int)((m << 31) | (fwd << 30));
 }
 // The same two bits in the low bits, for a walk step x -> y: the walk records them with y,
 // since a vertex kept by the loop erasure has as its tree edge the step after its last visit.
@@ -435,11 +432,11 @@ __device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, const doub
 // (k0 = 0, x0 = s0 for a whole walk; otherwise the Next pointers of steps 0..k0-1 are already
 // written).  Every lane calls both.
 //
-// Next pointers: the parent field of the records (it becomes the parent when the vertex joins).
+// Next pointers: the parents of the records (a Next becomes the parent when the vertex joins).
 struct NextRec {
-    int *recw;
-    __device__ __forceinline__ void set(int x, int y) const { recw[2 * x] = y; }
-    __device__ __forceinline__ int get(int x) const { return recw[2 * x]; }
+    int *par;
+    __device__ __forceinline__ void set(int x, int y) const { par[x] = y; }
+    __device__ __forceinline__ int get(int x) const { return par[x]; }
 };
 
 __device__ __forceinline__ long long uniform_ll(long long k) {
@@ -541,7 +538,7 @@ __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, con
 // a piece's last marked one on wait for the next piece that has one (or for the tree): they are
 // written with a placeholder and completed by lane 0 then.
 template <bool LDS, typename Next>
-__device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw, const int *__restrict__ bflag, int u,
+__device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *nbw, int *par, const int *__restrict__ bflag, int u,
                         int s0, int *buf, int *stamps, int round) {
     constexpr int kPiece = 2 * kHashSlots;
     const int lane = threadIdx.x;
@@ -564,7 +561,7 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw,
         cnt = __builtin_amdgcn_readfirstlane(cnt);
         fin = __builtin_amdgcn_readfirstlane(fin);
         z = __builtin_amdgcn_readfirstlane(z);
-        int carry = fin ? cv_of(z, load_nbx(recw, z)) : -1;
+        int carry = fin ? cv_of(z, load_nbx(nbw, z)) : -1;
         const int first = cnt ? buf[0] : z;
         int last = -1;  // the piece's last marked vertex
         for (int c = (cnt - 1) >> 6; c >= 0; --c) {  // cnt = 0: no piece
@@ -577,8 +574,7 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw,
             const int up = __shfl(v, above ? __builtin_ctzll(above) : 0, kWave);
             const int nba = above ? up : carry;
             if (mine) {
-                recw[2 * v] = nx;
-                recw[2 * v + 1] = (nba >= 0 ? nba : u) | mb;
+                nbw[v] = (nba >= 0 ? nba : u) | mb;  // the Next pointer is the parent
                 bits.set(v);
                 if constexpr (!LDS) stamps[stamp_slot(v)] = round;
             }
@@ -590,9 +586,9 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw,
         wave_sync();
         if (pend >= 0 && carry >= 0) {
             if (lane == 0)
-                for (int w = pend; w != first; w = recw[2 * w]) {
-                    const int old = load_nbx(recw, w);
-                    recw[2 * w + 1] = carry | (old & ~kVertexMask);
+                for (int w = pend; w != first; w = par[w]) {
+                    const int old = load_nbx(nbw, w);
+                    nbw[w] = carry | (old & ~kVertexMask);
                 }
             pend = -1;
             wave_sync();
@@ -605,8 +601,9 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *recw,
 
 }  // namespace
 
+// five waves a SIMD (96 registers): one register more and the compiler drops to four
 template <bool LDS, typename CT, bool WT, bool GL = false, bool BV = false>
-__global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
+__global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     // Reorder buffer.  Vertex IDs take the column type (16 bits when n <= 65536): 14 bytes an
     // entry, so that with the tree bitmap a block of R-MAT scale 16 fits 18 to a CU at 128
     // entries.  A recorded step keeps the vertex and the step's edge bits (below).
@@ -665,27 +662,27 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     if (tile >= a.ntiles) break;
     WilsonGraph g;
     long long t;
-    int2 *rec;
+    int *nbw;  // the tree's records: nba words, then parents
     if (a.tiles) {
         const WilsonTile tl = a.tiles[tile];
         g = a.graphs[tl.graph];
         t = tl.tree;
-        rec = a.rec + tl.rec_off;
+        nbw = a.rec + tl.rec_off;
     } else {
         g = a.g;
         t = a.tree_begin + tile;
-        rec = a.rec + (long long)tile * a.rec_stride;
+        nbw = a.rec + (long long)tile * 2 * g.rec_stride;
     }
     const int n = g.n;
     const int nwords = g.nwords;
     const int rob = min(g.rob, kRobMax);  // power of two
     const int robm = rob - 1;
     const uint32_t tlo = (uint32_t)(unsigned long long)t, thi = (uint32_t)((unsigned long long)t >> 32);
-    int *recw = reinterpret_cast<int *>(rec);  // recw[2x] = parent (Next while walking)
+    int *par = nbw + g.rec_stride;  // (Next while walking)
     TreeState<LDS> bits;
     if constexpr (LDS) bits.w = lds_bits;
-    else bits.recw = recw;
-    const NextRec next{recw};
+    else bits.nbw = nbw;
+    const NextRec next{par};
     const int *__restrict__ bflag = GL ? lbf : g.bflag;
     const int4 *__restrict__ vrow = g.vrow;
     const int4 *__restrict__ edge = g.edge;  // set when the tree state is in global memory
@@ -698,7 +695,8 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     if constexpr (LDS) {
         for (int i = lane; i < nwords; i += kWave) bits.w[i] = 0u;
     } else {
-        for (int i = lane; i < n; i += kWave) rec[i] = make_int2(-1, kFree);
+        int4 *w4 = reinterpret_cast<int4 *>(nbw);  // padded to 32 vertices
+        for (int i = lane; 4 * i < n; i += kWave) w4[i] = make_int4(kFree, kFree, kFree, kFree);
     }
     for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
     if constexpr (!LDS)
@@ -708,11 +706,13 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
         for (int i = lane; i < a.nroots; i += kWave) {
             const int r = a.roots[i];
             bits.set(r);
-            rec[r] = make_int2(-1, r);
+            nbw[r] = r;
+            par[r] = -1;
         }
     } else if (lane == 0) {
         bits.set(u);
-        rec[u] = make_int2(-1, u);
+        nbw[u] = u;
+        par[u] = -1;
     }
     wave_sync();
 
@@ -724,6 +724,11 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
     uint4 ph = make_uint4(0, 0, 0, 0);
     int4 vx = make_int4(0, 0, 0, 0);  // tree state in the records: x's entry {row begin, row end, B_u flag, 0}
     long long steps = 0, draws = 0;
+
+    // whether a vertex's parent is written, given the edge bits of its tree edge in the low two
+    // bits: always, or where Algorithm 2 may read it (marked by a backward edge)
+    const bool all_parents = a.parents != 0;
+    auto keeps_parent = [&](int eb) { return all_parents || (eb & 3) == 2; };
 
     // Marks the pending entries whose start has joined the tree (state 0).  With the LDS bitmap
     // the commit tests the start itself; with the tree state in the records that would be a
@@ -835,7 +840,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 in = bits.test(y);
                 gone = bits.test(s);  // the start has been absorbed: the walk never counts
                 if (in) {
-                    cvy = load_nbx(recw, y);
+                    cvy = load_nbx(nbw, y);
                 } else {
                     ny0 = rp[y];
                     ny1 = rp[y + 1];
@@ -901,7 +906,8 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 const int x1 = (int)st.v[0];
                 if (multi == 0ull) {  // single steps only: no two of them interfere
                     if (K > 0) {
-                        rec[s0] = make_int2(x1, carry | (int)((unsigned)pb << 30));
+                        nbw[s0] = carry | (int)((unsigned)pb << 30);
+                        if (keeps_parent(pb)) par[s0] = x1;
                         bits.set(s0);
                         ++steps;
                     }
@@ -940,7 +946,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     if constexpr (LDS) {
                         const bool need = istar < K;  // ya joined T after the walk passed it
                         if (__ballot(need)) {
-                            if (need) carry = cv_of(ya, load_nbx(recw, ya));
+                            if (need) carry = cv_of(ya, load_nbx(nbw, ya));
                         }
                     } else {
                         if (nt != kFree) carry = cv_of(ya, nt);
@@ -991,12 +997,13 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                     auto put = [&](int j, int v) {
                         if ((keep >> j) & 1u) {
                             const int mb = (int)((unsigned)(pb >> (2 * j)) << 30);
-                            rec[v] = make_int2(pv, carry | mb);
+                            nbw[v] = carry | mb;
+                            if (keeps_parent(pb >> (2 * j))) par[v] = pv;
                             bits.set(v);
                             if constexpr (!LDS) {
                                 if (j > 0) stamps[stamp_slot(v)] = round;
                             }
-                            carry = mb ? v : carry;
+                            carry = mb < 0 ? v : carry;  // v is marked
                             pv = v;
                         }
                     };
@@ -1071,7 +1078,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                 if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
                 const long long kk = walk_next<LDS, CT, WT>(bits, next, rp, col, edge, vrow, cw, guide, wk0, xs, k0, tlo, thi,
                                                             g.key0, g.key1, reinterpret_cast<uint32_t *>(htab));
-                retrace<LDS>(bits, next, recw, bflag, u, s0, htab, stamps, round);
+                retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
                 if (lane == 0) {
                     steps += kk;
@@ -1119,7 +1126,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
             };
             const int ya = xat(istar);
             int carry;
-            if constexpr (LDS) carry = ended && istar == K ? (int)rob_e[hsl].cv : cv_of(ya, load_nbx(recw, ya));
+            if constexpr (LDS) carry = ended && istar == K ? (int)rob_e[hsl].cv : cv_of(ya, load_nbx(nbw, ya));
             else carry = cv_of(ya, nt);
             carry = __builtin_amdgcn_readfirstlane(carry);
             // loop erasure: from b, jump past b's last visit before istar; kept positions per chunk
@@ -1169,11 +1176,12 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
                         nb = hib;
                     }
                     const bool mine = (kept[c] >> lane) & 1ull;
-                    const uint64_t m = __ballot(mine && nb != 0);
+                    const uint64_t m = __ballot(mine && (nb & 2));
                     const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
                     const int up = __shfl(xv[c], above ? __builtin_ctzll(above) : 0, kWave);
                     if (mine) {
-                        rec[xv[c]] = make_int2(nx, (above ? up : carry) | (nb << 30));
+                        nbw[xv[c]] = (above ? up : carry) | (nb << 30);
+                        if (keeps_parent(nb)) par[xv[c]] = nx;
                         bits.set(xv[c]);
                         if constexpr (!LDS) stamps[stamp_slot(xv[c])] = round;
                         inr = inr || (xv[c] > s0 && xv[c] <= shi);
@@ -1200,8 +1208,7 @@ __global__ __launch_bounds__(64) void wilson_kernel(WilsonArgs a) {
 }
 
 // ======================================================================================
-// Records of caller-supplied trees.  The sampler writes each vertex's record {parent,
-// nba | flags} as it commits; for trees given as parent arrays the same records are built
+// Records of caller-supplied trees.  The sampler writes each vertex's record as it commits; for trees given as parent arrays the same records are built
 // here by pointer jumping, a thread per (vertex, tree).  Two words per vertex are doubled
 // side by side: anc(v), an ancestor of v (u once reached), whose end tells whether v reaches the
 // pivot; and jw(v) = J | done << 31, where J is an ancestor of v such that every vertex
@@ -1239,7 +1246,9 @@ __global__ __launch_bounds__(256) void tree_jump_init_kernel(IntervalArgs a) {
         }
     }
     a.scratch[(long long)blockIdx.y * a.scratch_stride + v] = anc;
-    a.rec[(long long)blockIdx.y * a.rec_stride + v] = make_int2(pv, (int)jw);
+    int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
+    rec[v] = (int)jw;
+    rec[a.rec_stride + v] = pv;
 }
 
 // one round; open[0]: the round before left something open, open[1]: this one did
@@ -1249,17 +1258,17 @@ __global__ __launch_bounds__(256) void tree_jump_kernel(IntervalArgs a, int *__r
     bool more = false;
     if (v < a.n) {
         int *anc = a.scratch + (long long)blockIdx.y * a.scratch_stride;
-        int2 *rec = a.rec + (long long)blockIdx.y * a.rec_stride;
+        int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
         int x = anc[v];
         if (x != a.u) {
             for (int i = 0; i < kJumps && x != a.u; ++i) x = anc[x];
             anc[v] = x;
             more = x != a.u;
         }
-        unsigned w = (unsigned)rec[v].y;
+        unsigned w = (unsigned)rec[v];
         if (!(w & kJumpDone)) {
-            for (int i = 0; i < kJumps && !(w & kJumpDone); ++i) w = (unsigned)rec[w].y;
-            rec[v].y = (int)w;
+            for (int i = 0; i < kJumps && !(w & kJumpDone); ++i) w = (unsigned)rec[w];
+            rec[v] = (int)w;
             more = more || !(w & kJumpDone);
         }
     }
@@ -1269,33 +1278,35 @@ __global__ __launch_bounds__(256) void tree_jump_kernel(IntervalArgs a, int *__r
 __global__ __launch_bounds__(256) void tree_records_kernel(IntervalArgs a) {
     const int v = blockIdx.x * 256 + threadIdx.x;
     if (v >= a.n) return;
-    int2 *rec = a.rec + (long long)blockIdx.y * a.rec_stride;
+    int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
     if (v == a.u) {
-        rec[v] = make_int2(-1, v);
+        rec[v] = v;
         return;
     }
     if (a.scratch[(long long)blockIdx.y * a.scratch_stride + v] != a.u) atomicOr(a.err, 64);
-    const int pv = rec[v].x;
-    const unsigned w = (unsigned)rec[v].y;
+    const int pv = rec[a.rec_stride + v];
+    const unsigned w = (unsigned)rec[v];
     const int nba = (w & kJumpDone) ? (int)(w & ~kJumpDone) : a.u;  // not done: on or below a cycle
     const int mb = in_tree_ids(pv, a.n) ? mark_bits(v, a.bflag[v], pv, a.bflag[pv]) : 0;
-    rec[v].y = nba | mb;
+    rec[v] = nba | mb;
 }
 
 // ======================================================================================
-// Aggregation (Algorithm 2), on the {parent, chain} records: for v != u,
+// Aggregation (Algorithm 2), on the records: for v != u,
 //   c_T(v) = [parent_T(v) = parB(v)]
 //          + sum over marked strict T-ancestors x of v lying on P(v) of
 //              +1 if parent_T(x) = parB(x),  -1 if parB(parent_T(x)) = x and parent_T(x) on P(v),
 // which equals Algorithm 2's signed count term by term.  Thread per vertex over a chunk of
-// resident trees; one int64 atomic per vertex and chunk, skipped when the sum is zero.
+// resident trees; one int64 atomic per vertex and chunk, skipped when the sum is zero.  A chain
+// step reads the word nba(x) | flags alone; parent_T(x) only for a backward x on P(v).
 //
 // "On P(v)", two forms.  PL > 0 (shallow B_u): P(v) has at most ecc(u) - 1 <= PL vertices p_1 ..
 // beside v and u, which the thread keeps in registers, p_0 = v: x is on P(v) if it is one of
 // them, and a backward x = p_i counts if parent_T(x) = p_{i-1}, its B_u child towards v.  PL = 0:
 // the B_u subtree test pre_B(x) <= pre_B(v) < pre_B(x) + size_B(x).  What bounds the kernel is
-// its gathers, one per lane and chain vertex for the record and, with PL = 0, one more for the
-// interval.
+// its gathers, one per lane and chain vertex for the word and, with PL = 0, one more for the
+// interval, and the instructions around them: with the records as pairs {parent, word}, 24 vector
+// instructions a chain step, half of the vector issue rate at R-MAT scale 22.
 // ======================================================================================
 // WT: weighted graph, the edge (parB(b), b) of P(v) counts +-F[b] (Ohm's-law factor in fixed
 // point) instead of +-1.
@@ -1305,48 +1316,61 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
     if (v >= a.n || v == a.u) return;
     const int t0 = blockIdx.y * CH;
     const int nt = min(a.ntrees - t0, CH);
-    const int u = a.u;
+    const unsigned u = (unsigned)a.u;
     const int2 *__restrict__ bint = a.bint;
     const int *__restrict__ parB = a.parB;
-    const int pbv = parB[v];
     const int pv = PL ? 0 : bint[v].x;
-    const int2 *__restrict__ rec0 = a.rec + (long long)t0 * a.rec_stride;
+    const int *__restrict__ rec0 = a.rec + (long long)t0 * 2 * a.rec_stride;  // uniform
+    // word and parent of x in tree i: a uniform base and a 32-bit offset (4 x < 2^32)
+    auto word = [&](int i, unsigned x) {
+        return *reinterpret_cast<const int *>(reinterpret_cast<const char *>(rec0 + (long long)i * 2 * a.rec_stride) +
+                                              (x << 2));
+    };
+    auto parent = [&](int i, unsigned x) {
+        return *reinterpret_cast<const int *>(
+            reinterpret_cast<const char *>(rec0 + (long long)(2 * i + 1) * a.rec_stride) + (x << 2));
+    };
     // The chains of the chunk's trees are walked in lockstep, one step of every unfinished
     // chain per round, so their independent loads are in flight together.
     using Acc = typename std::conditional<WT, long long, int>::type;
     const long long *__restrict__ F = a.F;
     const Acc fv = WT ? (Acc)F[v] : (Acc)1;
-    int x[CH];
+    unsigned x[CH];
     Acc sum = 0;
+    {
+        int w[CH];
 #pragma unroll
-    for (int i = 0; i < CH; ++i) {
-        x[i] = u;
-        if (i < nt) {
-            const int2 rv = rec0[(long long)i * a.rec_stride + v];
-            sum += (rv.x == pbv) ? fv : (Acc)0;
-            x[i] = nba_of(rv.y);
-            if (x[i] >= a.n) x[i] = u;
+        for (int i = 0; i < CH; ++i) {
+            w[i] = (int)u;  // no such tree: nothing to add, no chain
+            if (i < nt) w[i] = word(i, (unsigned)v);
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            if constexpr (WT) sum += (w[i] & kFwdBit) ? fv : (Acc)0;
+            else sum += (w[i] >> 30) & 1;
+            x[i] = (unsigned)nba_of(w[i]);
         }
     }
     int p[PL + 1];  // p_0 = v, p_1 = parB(v), ..; -1 from u on
     p[0] = v;
     if constexpr (PL > 0) {
-        int b = pbv;
+        int b = parB[v];
 #pragma unroll
         for (int i = 1; i <= PL; ++i) {
-            p[i] = b != u ? b : -1;
-            if (i < PL && b != u) b = parB[b];
+            p[i] = b != a.u ? b : -1;
+            if (i < PL && b != a.u) b = parB[b];
         }
     }
-    // a chain visits each T-ancestor at most once: n rounds bound it even on broken records
+    // a chain visits each T-ancestor at most once: n rounds bound it
     for (int round = 0; round < a.n; ++round) {
-        int2 rx[CH], bx[CH];
+        int w[CH];
+        int2 bx[CH];
         bool act = false;
 #pragma unroll
         for (int i = 0; i < CH; ++i) {
             if (x[i] != u) {
                 act = true;
-                rx[i] = rec0[(long long)i * a.rec_stride + x[i]];
+                w[i] = word(i, x[i]);
                 if constexpr (PL == 0) bx[i] = bint[x[i]];
             }
         }
@@ -1356,34 +1380,35 @@ __global__ __launch_bounds__(256) void aggregate_kernel(AggregateArgs a) {
             if (x[i] != u) {
                 // a forward x counts +1 if x is on P(v); a backward x counts -1 if parent_T(x),
                 // a B_u child of x, is on P(v), which needs x on P(v) first
-                const bool fwd = rx[i].y & kFwdBit;
+                bool on;
                 if constexpr (PL > 0) {
-                    bool on = false, below = false;
+                    on = (int)x[i] == p[1];
 #pragma unroll
-                    for (int j = 1; j <= PL; ++j) {
-                        const bool e = x[i] == p[j];
-                        on |= e;
-                        below |= e & (rx[i].x == p[j - 1]);
-                    }
-                    if constexpr (WT) {
-                        if (fwd ? on : below) sum += fwd ? F[x[i]] : -F[rx[i].x];
-                    } else {
-                        sum += fwd ? (int)on : -(int)below;
-                    }
-                } else if (bx[i].x <= pv && pv < bx[i].x + bx[i].y) {
-                    if (fwd) {
+                    for (int j = 2; j <= PL; ++j) on |= (int)x[i] == p[j];
+                } else {
+                    on = bx[i].x <= pv && pv < bx[i].x + bx[i].y;
+                }
+                if (on) {
+                    if (w[i] & kFwdBit) {
                         if constexpr (WT) sum += F[x[i]];
                         else ++sum;
                     } else {
-                        const int2 bp = bint[rx[i].x];
-                        if (bp.x <= pv && pv < bp.x + bp.y) {
-                            if constexpr (WT) sum -= F[rx[i].x];
+                        const int q = parent(i, x[i]);
+                        bool below = false;
+                        if constexpr (PL > 0) {
+#pragma unroll
+                            for (int j = 1; j <= PL; ++j) below |= (int)x[i] == p[j] && q == p[j - 1];
+                        } else {
+                            const int2 bp = bint[q];
+                            below = bp.x <= pv && pv < bp.x + bp.y;
+                        }
+                        if (below) {
+                            if constexpr (WT) sum -= F[q];
                             else --sum;
                         }
                     }
                 }
-                x[i] = nba_of(rx[i].y);
-                if (x[i] >= a.n) x[i] = u;  // never for sampled trees; keeps reads in bounds
+                x[i] = (unsigned)nba_of(w[i]);
             }
         }
     }
@@ -1654,12 +1679,12 @@ __global__ __launch_bounds__(kSetupThreads) void setup_small_kernel(RowMap m, in
 
 
 // parents[i][v] = rec_i[v].parent
-__global__ void extract_parents_kernel(int n, int ntrees, const int2 *__restrict__ rec, long long rec_stride,
+__global__ void extract_parents_kernel(int n, int ntrees, const int *__restrict__ rec, long long rec_stride,
                                        int *__restrict__ out) {
     const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (long long)n * ntrees) return;
     const long long t = i / n, v = i - t * n;
-    out[i] = rec[t * rec_stride + v].x;
+    out[i] = rec[(2 * t + 1) * rec_stride + v];
 }
 
 // ======================================================================================
@@ -1745,7 +1770,7 @@ __global__ __launch_bounds__(256) void edge_count_kernel(EdgeCountArgs a) {
     long long cur = -1;
     int c = 0;
     for (int t = t0; t < t1; ++t) {
-        const int p = a.rec[(long long)t * a.rec_stride + v].x;
+        const int p = a.rec[(2ll * t + 1) * a.rec_stride + v];
         int lo = a.rp[v], hi = a.rp[v + 1];
         const int end = hi;
         while (lo < hi) {
@@ -2179,13 +2204,13 @@ hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hip
     tree_records_kernel<<<grid, 256, 0, st>>>(a);
     return hipGetLastError();
 }
-hipError_t launch_extract_parents(int n, int ntrees, const int2 *rec, long long rec_stride, int *out, hipStream_t st) {
+hipError_t launch_extract_parents(int n, int ntrees, const int *rec, long long rec_stride, int *out, hipStream_t st) {
     // a dispatch counts its work-items in 32 bits: at most 2^31 (vertex, tree) items per launch
     const int chunk = (int)std::max(1ll, std::min<long long>(ntrees, (1ll << 31) / std::max(n, 1)));
     for (int t0 = 0; t0 < ntrees; t0 += chunk) {
         const int nt = std::min(chunk, ntrees - t0);
         extract_parents_kernel<<<blocks_for((long long)n * nt, 256), 256, 0, st>>>(
-            n, nt, rec + (long long)t0 * rec_stride, rec_stride, out + (long long)t0 * n);
+            n, nt, rec + (long long)t0 * 2 * rec_stride, rec_stride, out + (long long)t0 * n);
     }
     return hipGetLastError();
 }

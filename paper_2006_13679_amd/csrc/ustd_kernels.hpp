@@ -21,6 +21,7 @@ namespace ustd {
 // One graph as the sampler sees it (read-only while sampling).
 struct WilsonGraph {
     int n, u, nwords, rob;
+    int rec_stride;         // entries of each array of a tree's records
     const int *rp;
     const void *colv;       // column indices: int32, or uint16 when the launch says so
     const int *bflag;       // [n] (parB + 1) | (internal in B_u) << 31
@@ -33,7 +34,7 @@ struct WilsonGraph {
 };
 
 // One unit of sampler work in a batched launch: tree `tree` of graph `graph`, whose
-// records go to rec + rec_off.
+// records go to rec + rec_off (ints).
 struct WilsonTile {
     long long tree, rec_off;
     int graph, pad;
@@ -41,15 +42,16 @@ struct WilsonTile {
 
 // Persistent sampler launch: every block repeatedly takes the next tile index from
 // *queue until all `ntiles` are taken.  Tile i is tree tree_begin + i of `g` with
-// records at rec + i * rec_stride, or tiles[i] of the graph table when `tiles` is set.
+// records at rec + 2 i g.rec_stride, or tiles[i] of the graph table when `tiles` is set.
 struct WilsonArgs {
     WilsonGraph g;
     const WilsonGraph *graphs;  // batched launches: graph table (device)
     const WilsonTile *tiles;    // batched launches: tile table (device); null = single graph
     int ntiles;
     long long tree_begin;
-    int2 *rec;                  // records {parent_T, nba | marked << 31}
-    long long rec_stride;
+    int *rec;                   // records: per tree the words nba | flags, then the parents
+    int parents;                // 0: only the parents that Algorithm 2 reads are written (marked
+                                // vertices whose tree edge is a backward B_u edge)
     int *path;                  // [blocks][kSamplerPathSlot] recorded steps beyond the LDS part
     int *queue;                 // tile counter, zero at launch
     long long *steps;           // [ntiles], nullable
@@ -68,7 +70,7 @@ struct IntervalArgs {
     long long par_stride;
     int *scratch;           // [ntrees][scratch_stride], scratch_stride >= n
     long long scratch_stride;
-    int2 *rec;              // [ntrees][rec_stride] {parent, nba | flags} records out
+    int *rec;               // [ntrees][2][rec_stride] records out: words nba | flags, parents
     long long rec_stride;
     const int *bflag;       // [n] B_u flag words
     int *err;
@@ -84,7 +86,7 @@ struct AggregateArgs {
     int ecc;                // ecc(u): the form of the path test
     const int *parB;        // [n] B_u parents
     const int2 *bint;       // [n] {pre_B, size_B} subtree intervals of B_u
-    const int2 *rec;
+    const int *rec;         // [ntrees][2][rec_stride] tree records
     long long rec_stride;
     long long *counts;
     const long long *F;     // [n] fixed-point 1/w of each vertex's B_u edge; null = unit weights
@@ -94,7 +96,7 @@ struct AggregateArgs {
 struct EdgeCountArgs {
     int n, u, ntrees, trees_per_chunk;
     const int *rp, *col;        // int32 row pointers, ascending rows
-    const int2 *rec;            // [ntrees][rec_stride] tree records
+    const int *rec;             // [ntrees][2][rec_stride] tree records
     long long rec_stride;
     long long *counts;          // [nnz], accumulated
 };
@@ -209,7 +211,7 @@ hipError_t launch_col_to_u16(long long nnz, const int *col, unsigned short *col1
 constexpr int kTreeJumpRounds = 11;
 hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hipStream_t st);
 hipError_t launch_aggregate(const AggregateArgs &a, hipStream_t st);
-hipError_t launch_extract_parents(int n, int ntrees, const int2 *rec, long long rec_stride, int *out, hipStream_t st);
+hipError_t launch_extract_parents(int n, int ntrees, const int *rec, long long rec_stride, int *out, hipStream_t st);
 hipError_t launch_centralities(long long n, const double *diag, double *farness, double *closeness, double *nrwb,
                                double *scalars, hipStream_t st);
 hipError_t launch_edge_counts(const EdgeCountArgs &a, hipStream_t st);
@@ -261,7 +263,7 @@ hipError_t launch_bc_roots(int nslots, const int *rps, const int *vtx, const int
 hipError_t launch_bc_top_flags(int nslots, const int *sblk, const int *slotTop, int *flag, hipStream_t st);
 hipError_t launch_bc_compact(int nslots, const int *flag, const int *pos, int *list, hipStream_t st);
 hipError_t launch_bc_join(int n, int u, int ntrees, int ntop, int nslots, const int *tops, const int *slotPar,
-                          const int *vtx, int2 *recs, long long sstride, int2 *rec, long long stride,
+                          const int *vtx, int *recs, long long sstride, int *rec, long long stride,
                           const int *bflag, hipStream_t st);
 // a[0..n) = v; b[0..n) += a[0..n) (int64)
 hipError_t launch_fill_i64(long long n, long long *a, long long v, hipStream_t st);
