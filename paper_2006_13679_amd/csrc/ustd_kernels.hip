@@ -276,9 +276,18 @@ static_assert(kWin == 4 * kWave, "four vertices of the window per lane");
 // whose loads and stores the vector L1 keeps in order.
 constexpr int kFree = 0x3FFFFFFF;  // nba of a vertex not in the tree; vertex IDs are below it
 
-// the {nba | flags} word of a record another lane of the wave may have written
+// entry v of an array of 4-byte entries, one per vertex: a 32-bit offset from a uniform base (4 v <
+// 2^32) takes one register and no 64-bit address arithmetic
+template <typename T>
+__device__ __forceinline__ T &vertex_at(T *base, int v) {
+    static_assert(sizeof(T) == 4, "4-byte entries");
+    using C = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return *reinterpret_cast<T *>(reinterpret_cast<C *>(base) + ((uint32_t)v << 2));
+}
+
+// the word nba | flags of a vertex, which another lane of the wave may have written
 __device__ __forceinline__ int load_nbx(const int *nbw, int v) {
-    return __hip_atomic_load(nbw + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
+    return __hip_atomic_load(&vertex_at(nbw, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WAVEFRONT);
 }
 
 template <bool LDS>
@@ -400,6 +409,11 @@ static_assert(kHashSlots == 128, "the hashes give seven bits");
 constexpr int kStamps = 256;
 __device__ __forceinline__ int stamp_slot(int v) { return (int)(((unsigned)v * 2654435761u) >> 24); }
 static_assert(kStamps == 256, "the hash gives eight bits");
+// Rounds are kept modulo 2^16: whether `stamp` is round r or later.  A walk ends, and a window's
+// last start is taken, well within 2^15 rounds (a walk takes at most kPath steps, a window's starts
+// pass through the reorder buffer in a few lifetimes of one), so a later stamp is never taken for an
+// earlier one; an older stamp that looks later costs a load.
+__device__ __forceinline__ bool since(uint16_t stamp, int r) { return (int16_t)(uint16_t)(stamp - r) >= 0; }
 
 // Neighbour index (0 .. deg-1) of a walk step with word w from the row [r0, r1).  Unit
 // weights: floor(w deg / 2^32).  Weighted (Section "Generalizations"): the first j with
@@ -435,8 +449,8 @@ __device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, const doub
 // Next pointers: the parents of the records (a Next becomes the parent when the vertex joins).
 struct NextRec {
     int *par;
-    __device__ __forceinline__ void set(int x, int y) const { par[x] = y; }
-    __device__ __forceinline__ int get(int x) const { return par[x]; }
+    __device__ __forceinline__ void set(int x, int y) const { vertex_at(par, x) = y; }
+    __device__ __forceinline__ int get(int x) const { return vertex_at(par, x); }
 };
 
 __device__ __forceinline__ long long uniform_ll(long long k) {
@@ -539,7 +553,7 @@ __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, con
 // written with a placeholder and completed by lane 0 then.
 template <bool LDS, typename Next>
 __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *nbw, int *par, const int *__restrict__ bflag, int u,
-                        int s0, int *buf, int *stamps, int round) {
+                        int s0, int *buf, uint16_t *stamps, int round) {
     constexpr int kPiece = 2 * kHashSlots;
     const int lane = threadIdx.x;
     int z = s0, pend = -1;  // pend: first vertex whose nba is not known yet
@@ -574,9 +588,9 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *nbw, 
             const int up = __shfl(v, above ? __builtin_ctzll(above) : 0, kWave);
             const int nba = above ? up : carry;
             if (mine) {
-                nbw[v] = (nba >= 0 ? nba : u) | mb;  // the Next pointer is the parent
+                vertex_at(nbw, v) = (nba >= 0 ? nba : u) | mb;  // the Next pointer is the parent
                 bits.set(v);
-                if constexpr (!LDS) stamps[stamp_slot(v)] = round;
+                if constexpr (!LDS) stamps[stamp_slot(v)] = (uint16_t)round;
             }
             if (m) {
                 if (last < 0) last = __builtin_amdgcn_readlane(v, 63 - __builtin_clzll(m));
@@ -588,7 +602,7 @@ __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *nbw, 
             if (lane == 0)
                 for (int w = pend; w != first; w = par[w]) {
                     const int old = load_nbx(nbw, w);
-                    nbw[w] = carry | (old & ~kVertexMask);
+                    vertex_at(nbw, w) = carry | (old & ~kVertexMask);
                 }
             pend = -1;
             wave_sync();
@@ -617,7 +631,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     __shared__ uint8_t rob_pb[kRobMax];  // edge bits of steps 1..kPathLds, 2 bits each
     __shared__ uint16_t rob_r[LDS ? 1 : kRobMax];  // round of a finished walk's last step (low 16 bits)
     __shared__ alignas(16) int htab[2 * kHashSlots + 4];  // a word past the end is read, not used
-    __shared__ int stamps[LDS ? 1 : kStamps];
+    __shared__ uint16_t stamps[LDS ? 1 : kStamps];
     __shared__ uint8_t win[kWin];  // free vertices of the window, as offsets
     int *const hslot = htab;                // first conflict table
     int *const hslot2 = htab + kHashSlots;  // second conflict table; together the one-lane walk's
@@ -700,7 +714,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     }
     for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
     if constexpr (!LDS)
-        for (int i = lane; i < kStamps; i += kWave) stamps[i] = -1;
+        for (int i = lane; i < kStamps; i += kWave) stamps[i] = 0xFFFF;  // before round 0
     wave_sync();
     if constexpr (BV) {  // several roots (one per block of the block-split graph)
         for (int i = lane; i < a.nroots; i += kWave) {
@@ -720,10 +734,12 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     int wend = 0, wpos = 0, wcnt = 0;     // the window is [wend - kWin, wend); list position and length
     int wround = 0, shi = -1;             // the round that read the window; the last start taken
     int mode = 0;                         // 0 idle, 1 speculative walk
-    int my_e = 0, x = 0, s = 0, wkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
+    int my_e = 0, x = 0, s = 0, bkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
     uint4 ph = make_uint4(0, 0, 0, 0);
     int4 vx = make_int4(0, 0, 0, 0);  // tree state in the records: x's entry {row begin, row end, B_u flag, 0}
-    long long steps = 0, draws = 0;
+    // steps and draws of this lane (a tree has fewer rounds than 2^30) and of the one-lane walks
+    uint32_t steps = 0u, draws = 0u;
+    long long wsteps = 0, wdraws = 0;
 
     // whether a vertex's parent is written, given the edge bits of its tree edge in the low two
     // bits: always, or where Algorithm 2 may read it (marked by a backward edge)
@@ -790,19 +806,18 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
             if (mode0 && rank < got) {
                 my_e = tail + rank;
                 s = mys;
-                wkey = s;
-                if constexpr (BV) wkey = a.skey[s];
+                if constexpr (BV) bkey = a.skey[s];
                 x = s;
                 k = 0;
                 bool gone;  // joined the tree since the window was read
                 if constexpr (LDS) {
-                    r0 = rp[s];
-                    r1 = rp[s + 1];
-                    fx = bflag[s];
+                    r0 = vertex_at(rp, s);
+                    r1 = vertex_at(rp, s + 1);
+                    fx = vertex_at(bflag, s);
                     gone = bits.test(s);
                 } else {
                     vx = vrow[s];  // in flight until the step's random words are there
-                    gone = stamps[stamp_slot(s)] >= myr && bits.test(s);
+                    gone = since(stamps[stamp_slot(s)], myr) && bits.test(s);
                 }
                 pbits = 0;
                 mode = gone ? 0 : 1;
@@ -820,7 +835,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         if (mode == 1) {
             const int sl = my_e & robm;
             if ((k & 3) == 0)
-                ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), (uint32_t)wkey, tlo, thi), g.key0, g.key1);
+                ph = philox4x32_10(make_uint4((uint32_t)(k >> 2), (uint32_t)(BV ? bkey : s), tlo, thi), g.key0, g.key1);
             const int q = k & 3;
             const uint32_t w = q == 0 ? ph.x : (q == 1 ? ph.y : (q == 2 ? ph.z : ph.w));
             if constexpr (!LDS) {
@@ -836,18 +851,18 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
             bool in, gone = false;
             int cvy = 0, fy = 0, ny0 = 0, ny1 = 0;
             if constexpr (LDS) {
-                fy = bflag[y];
+                fy = vertex_at(bflag, y);
                 in = bits.test(y);
                 gone = bits.test(s);  // the start has been absorbed: the walk never counts
                 if (in) {
                     cvy = load_nbx(nbw, y);
                 } else {
-                    ny0 = rp[y];
-                    ny1 = rp[y + 1];
+                    ny0 = vertex_at(rp, y);
+                    ny1 = vertex_at(rp, y + 1);
                 }
             } else {
                 cvy = bits.nbx(y);  // membership and chain value in one load
-                if (bf_internal(fx)) fy = bflag[y];
+                if (bf_internal(fx)) fy = vertex_at(bflag, y);
                 in = cvy != kFree;
             }
             consume(fy, cvy, ny0, ny1);  // no load may stay in flight into the commit phase
@@ -906,8 +921,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                 const int x1 = (int)st.v[0];
                 if (multi == 0ull) {  // single steps only: no two of them interfere
                     if (K > 0) {
-                        nbw[s0] = carry | (int)((unsigned)pb << 30);
-                        if (keeps_parent(pb)) par[s0] = x1;
+                        vertex_at(nbw, s0) = carry | (int)((unsigned)pb << 30);
+                        if (keeps_parent(pb)) vertex_at(par, s0) = x1;
                         bits.set(s0);
                         ++steps;
                     }
@@ -928,8 +943,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                         if (any4 && K >= 4 && bits.test(x3)) n3 = 0;
                     } else {
                         // x_j was read free in round fin - (K - j); a load only if it may have joined
-                        const int fin = round - ((round - (int)rob_r[sl]) & 0xFFFF);
-                        auto stale = [&](int v, int r) { return v < slo || stamps[stamp_slot(v)] >= r; };
+                        const int fin = (int)rob_r[sl];
+                        auto stale = [&](int v, int r) { return v < slo || since(stamps[stamp_slot(v)], r); };
                         const bool t1 = K >= 2 && stale(x1, fin - K + 1);
                         const bool t2 = any3 && K >= 3 && stale(x2, fin - K + 2);
                         const bool t3 = any4 && K >= 4 && stale(x3, fin - K + 3);
@@ -997,11 +1012,11 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     auto put = [&](int j, int v) {
                         if ((keep >> j) & 1u) {
                             const int mb = (int)((unsigned)(pb >> (2 * j)) << 30);
-                            nbw[v] = carry | mb;
-                            if (keeps_parent(pb >> (2 * j))) par[v] = pv;
+                            vertex_at(nbw, v) = carry | mb;
+                            if (keeps_parent(pb >> (2 * j))) vertex_at(par, v) = pv;
                             bits.set(v);
                             if constexpr (!LDS) {
-                                if (j > 0) stamps[stamp_slot(v)] = round;
+                                if (j > 0) stamps[stamp_slot(v)] = (uint16_t)round;
                             }
                             carry = mb < 0 ? v : carry;  // v is marked
                             pv = v;
@@ -1080,10 +1095,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                                                             g.key0, g.key1, reinterpret_cast<uint32_t *>(htab));
                 retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
-                if (lane == 0) {
-                    steps += kk;
-                    draws += kk - k0;
-                }
+                wsteps += kk;
+                wdraws += kk - k0;
                 ++head;
                 wave_sync();
                 if constexpr (!LDS) remark();
@@ -1180,10 +1193,10 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
                     const int up = __shfl(xv[c], above ? __builtin_ctzll(above) : 0, kWave);
                     if (mine) {
-                        nbw[xv[c]] = (above ? up : carry) | (nb << 30);
-                        if (keeps_parent(nb)) par[xv[c]] = nx;
+                        vertex_at(nbw, xv[c]) = (above ? up : carry) | (nb << 30);
+                        if (keeps_parent(nb)) vertex_at(par, xv[c]) = nx;
                         bits.set(xv[c]);
-                        if constexpr (!LDS) stamps[stamp_slot(xv[c])] = round;
+                        if constexpr (!LDS) stamps[stamp_slot(xv[c])] = (uint16_t)round;
                         inr = inr || (xv[c] > s0 && xv[c] <= shi);
                     }
                     if (m) carry = __builtin_amdgcn_readlane(xv[c], __builtin_ctzll(m));
@@ -1198,11 +1211,11 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         }
     }
 
-    steps = wave_sum(steps);
-    draws = wave_sum(draws);
+    const long long sum_steps = wsteps + (long long)wave_sum((unsigned long long)steps);
+    const long long sum_draws = wdraws + (long long)wave_sum((unsigned long long)draws);
     if (lane == 0) {
-        if (a.steps) a.steps[tile] = steps;
-        if (a.draws) a.draws[tile] = draws;
+        if (a.steps) a.steps[tile] = sum_steps;
+        if (a.draws) a.draws[tile] = sum_draws;
     }
     }  // next tile
 }
