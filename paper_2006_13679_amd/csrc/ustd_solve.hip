@@ -65,6 +65,55 @@ __device__ __forceinline__ T row_sum(T acc, const int *__restrict__ col, const d
     return acc;
 }
 
+// the light rows; R rows of a group in flight
+template <typename T, int G, int R, typename Emit>
+__device__ __forceinline__ void lap_light_rows(const RowMap &m, const T *__restrict__ p, Emit emit, int blk, int nblk,
+                                               int bs) {
+    const double *__restrict__ w = m.w;
+    const int rows_per_tile = bs / G;
+    const int g = threadIdx.x / G, l = threadIdx.x % G;
+    for (int tile = blk; tile * rows_per_tile < m.n; tile += R * nblk) {
+        int lo[R], deg[R], len[R];
+        int c[R][2];
+        T q[R][2];
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const int v = (tile + i * nblk) * rows_per_tile + g;
+            lo[i] = v < m.n ? m.rp[v] : 0;
+            deg[i] = v < m.n ? m.rp[v + 1] : -1;
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            deg[i] = deg[i] < 0 ? -1 : deg[i] - lo[i];
+            len[i] = deg[i] <= m.heavy_thresh ? deg[i] : 0;  // heavy rows are done above
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                c[i][s] = -1;
+                if (l + s * G < len[i]) c[i][s] = m.col[lo[i] + l + s * G];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                q[i][s] = (T)0;
+                if (c[i][s] >= 0) q[i][s] = w ? (T)w[lo[i] + l + s * G] * p[c[i][s]] : p[c[i][s]];
+            }
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            if ((tile + i * nblk) * rows_per_tile >= m.n) break;  // no row left for any group
+            T acc = q[i][0] + q[i][1];
+            if (len[i] > 2 * G) acc = row_sum<T, 4>(acc, m.col, w, p, lo[i] + l + 2 * G, lo[i] + len[i], G);
+#pragma unroll
+            for (int dd = G / 2; dd > 0; dd >>= 1) acc += __shfl_xor(acc, dd, G);
+            if (deg[i] >= 0 && deg[i] <= m.heavy_thresh && l == 0) {
+                const int v = (tile + i * nblk) * rows_per_tile + g;
+                emit(v, (w ? (T)m.wdeg[v] : (T)deg[i]) * p[v] - acc);
+            }
+        }
+    }
+}
+
 template <typename T, int G, int BS = 256, typename Emit>
 __device__ __forceinline__ void lap_apply_rows(const RowMap &m, const T *__restrict__ p, Emit emit, int blk,
                                                int nblk, int bs = BS) {
@@ -78,47 +127,8 @@ __device__ __forceinline__ void lap_apply_rows(const RowMap &m, const T *__restr
         acc = block_sum_t<T>(acc, shr, bs);
         if (threadIdx.x == 0) emit(v, (w ? (T)m.wdeg[v] : (T)(hi - lo)) * p[v] - acc);
     }
-    const int rows_per_tile = bs / G;
-    const int g = threadIdx.x / G, l = threadIdx.x % G;
-    for (int tile = blk; tile * rows_per_tile < m.n; tile += kRowsInFlight * nblk) {
-        int lo[kRowsInFlight], deg[kRowsInFlight], len[kRowsInFlight];
-        int c[kRowsInFlight][2];
-        T q[kRowsInFlight][2];
-#pragma unroll
-        for (int i = 0; i < kRowsInFlight; ++i) {
-            const int v = (tile + i * nblk) * rows_per_tile + g;
-            lo[i] = v < m.n ? m.rp[v] : 0;
-            deg[i] = v < m.n ? m.rp[v + 1] : -1;
-        }
-#pragma unroll
-        for (int i = 0; i < kRowsInFlight; ++i) {
-            deg[i] = deg[i] < 0 ? -1 : deg[i] - lo[i];
-            len[i] = deg[i] <= m.heavy_thresh ? deg[i] : 0;  // heavy rows are done above
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                c[i][s] = -1;
-                if (l + s * G < len[i]) c[i][s] = m.col[lo[i] + l + s * G];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kRowsInFlight; ++i)
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                q[i][s] = (T)0;
-                if (c[i][s] >= 0) q[i][s] = w ? (T)w[lo[i] + l + s * G] * p[c[i][s]] : p[c[i][s]];
-            }
-#pragma unroll
-        for (int i = 0; i < kRowsInFlight; ++i) {
-            T acc = q[i][0] + q[i][1];
-            if (len[i] > 2 * G) acc = row_sum<T, 4>(acc, m.col, w, p, lo[i] + l + 2 * G, lo[i] + len[i], G);
-#pragma unroll
-            for (int dd = G / 2; dd > 0; dd >>= 1) acc += __shfl_xor(acc, dd, G);
-            if (deg[i] >= 0 && deg[i] <= m.heavy_thresh && l == 0) {
-                const int v = (tile + i * nblk) * rows_per_tile + g;
-                emit(v, (w ? (T)m.wdeg[v] : (T)deg[i]) * p[v] - acc);
-            }
-        }
-    }
+    if (m.n <= bs / G) lap_light_rows<T, G, 1>(m, p, emit, blk, nblk, bs);  // one row a group at most: four in flight cost 4% there (16 x 16 grid)
+    else lap_light_rows<T, G, kRowsInFlight>(m, p, emit, blk, nblk, bs);
 }
 
 // Jacobi diagonal: the degree, or the conductance sum of a weighted Laplacian's row
@@ -410,16 +420,19 @@ __global__ __launch_bounds__(256) void solve_direction_kernel(SolveArgs<T> a) {
 // reliable updates and end rule, with no kernel boundary or host poll between iterations.
 // Ends with the scalars the multi-kernel path leaves.
 // ---------------------------------------------------------------------------------------
-// Up to 1024 rows four waves do the work and the others leave at once (a barrier counts the waves
-// that are left): an iteration is a chain of a dozen barriers, which cost less among four.  The
-// choice depends on n alone, so a batch member's solve is that of a single call.
-constexpr int kFewRows = 1024, kFewThreads = 256;
+// Where the rows' lane groups fill less than the workgroup, four waves do the work and the others
+// leave at once (a barrier counts the waves that are left): an iteration is a chain of a dozen
+// barriers, which cost less among four (column of a 13 x 11 grid 306 us against 333, 8 x 8 grid 267
+// against 279).  Beyond that the product grows by more than the barriers save: 20 x 30 grid 1643 us
+// against 1109, R-MAT scale 10 1709 against 764.  The choice depends on the graph alone, so a batch
+// member's solve is that of a single call.
+constexpr int kFewThreads = 256;
 
 template <typename T, int G>
 __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double tol2, double delta2, int maxit,
                                  double *sh) {
     const int n = a.n, tid = threadIdx.x, u = a.u;
-    const int nt = n <= kFewRows ? kFewThreads : kSmallThreads;
+    const int nt = n * G < kSmallThreads ? kFewThreads : kSmallThreads;
     if (tid >= nt) return;
     const double inv_n = 1.0 / (double)n;
     double rz = 0.0, rr = 0.0, bb = 0.0;
