@@ -76,19 +76,20 @@ struct Misc {                      // small zero-initialised block at the front 
 struct Plan {
     int n, nnz, K, slots, pools, rob, nwords, G, heavy_thresh;
     bool lds_bits, col16, weighted;
-    bool edges;  // edge entries for the sampler (tree state in global memory)
+    bool vrows;  // vertex entries for the sampler (tree state in global memory)
+    bool hops;   // rows per slot for the sampler's lone walks
     long long rec_stride;
-    long long off_misc, off_rp32, off_col16, off_dist, off_parB, off_bint, off_bflag, off_vrow, off_edge, off_heavy, off_bcount, off_counts, off_steps,
+    long long off_misc, off_rp32, off_col16, off_dist, off_parB, off_bint, off_bflag, off_vrow, off_hops, off_heavy, off_bcount, off_counts, off_steps,
         off_draws, off_rec, off_path, off_scr, off_part, off_x64, off_r64, off_z64, off_p64, off_q64,
         off_res64, off_x32, off_r32, off_z32, off_p32, off_q32, off_cw, off_guide, off_wdeg, off_wB, off_F;
     // Wilson per biconnected component: the block-split graph G* (at most 2n slots) and its
     // sampler layout, decided for the upper bound of slots
-    bool bv, s_lds, s_col16, s_edges;
+    bool bv, s_lds, s_col16, s_vrows;
     int s_nmax, s_nwords;
     long long s_rec_stride;
     long long off_bc_lo, off_bc_hi, off_uf, off_fpar, off_ftop, off_spar, off_stop, off_rkey, off_eblk, off_flag,
         off_sid, off_svtx, off_skey, off_sblk, off_sdeg, off_rps, off_cur, off_scol, off_scol16, off_sbflag,
-        off_rflag, off_rpos, off_roots, off_tops, off_tiles, off_svrow, off_sedge, off_srec;
+        off_rflag, off_rpos, off_roots, off_tops, off_tiles, off_svrow, off_shops, off_srec;
     long long total;
 };
 
@@ -122,16 +123,17 @@ int check_problem(const ustd_problem *p) {
 
 // Workspace layout of one problem.  Without trees (a batch member's own region) the tree
 // records and sampler slots are left out: a batch keeps them in a shared pool.
-Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges = false) {
+Plan make_plan(const ustd_problem *p, bool with_trees = true, bool in_records = false, bool hops = true) {
     Plan L{};
     L.n = (int)p->n;
     L.nnz = (int)p->nnz;
     L.nwords = (L.n + 31) / 32;
     L.lds_bits = L.nwords <= kLdsBitsMaxWords;
     L.col16 = L.n <= 65536;  // 16-bit column copy for the sampler (half the cache footprint)
-    L.edges = !L.lds_bits || force_edges;
+    L.vrows = !L.lds_bits || in_records;
+    L.hops = hops || !L.lds_bits;
     L.weighted = p->d_weight != nullptr;
-    L.rob = std::min(L.lds_bits && !force_edges ? kSamplerRobLds : kSamplerRobMax, next_pow2(std::max(L.n, 2)));
+    L.rob = std::min(L.lds_bits && !in_records ? kSamplerRobLds : kSamplerRobMax, next_pow2(std::max(L.n, 2)));
     const double avg = (double)L.nnz / (double)L.n;
     L.G = avg <= 6.0 ? 4 : (avg <= 16.0 ? 8 : (avg <= 48.0 ? 16 : 32));
     L.heavy_thresh = 32 * L.G;
@@ -147,9 +149,9 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
         L.s_nwords = (L.s_nmax + 31) / 32;
         L.s_lds = L.s_nwords <= kLdsBitsMaxWords;
         L.s_col16 = L.s_nmax <= 65536;
-        L.s_edges = !L.s_lds;
+        L.s_vrows = !L.s_lds;
         L.s_rec_stride = align_up((long long)L.s_nmax * 8) / 8;
-        L.edges = false;  // the sampler runs on G*, not on G
+        L.vrows = false;  // the sampler runs on G*, not on G
     }
     const long long per_tree = L.rec_stride * 8 + 16 + (L.bv ? L.s_rec_stride * 8 : 0);
     const long long per_slot = kSamplerPathSlot * 4;
@@ -178,8 +180,8 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     L.off_parB = take(n * 4);
     L.off_bint = take(n * 8);
     L.off_bflag = take(n * 4);
-    L.off_vrow = take(L.edges ? n * 16 : 0);
-    L.off_edge = take(L.edges ? (long long)L.nnz * 16 : 0);
+    L.off_vrow = take(L.vrows ? n * 16 : 0);
+    L.off_hops = take(L.hops && !L.bv ? (long long)L.nnz * 8 : 0);
     L.off_heavy = take(n * 4);
     L.off_bcount = take((n / 256 + 2) * 4);
     L.off_counts = take(n * 8);
@@ -235,8 +237,8 @@ Plan make_plan(const ustd_problem *p, bool with_trees = true, bool force_edges =
     L.off_roots = take(bn * 4);
     L.off_tops = take(bn * 4);
     L.off_tiles = take(L.bv ? (std::max(bnnz, bs) / 1024 + 2) * 4 : 0);
-    L.off_svrow = take(L.bv && L.s_edges ? bs * 16 : 0);
-    L.off_sedge = take(L.bv && L.s_edges ? bnnz * 16 : 0);
+    L.off_svrow = take(L.bv && L.s_vrows ? bs * 16 : 0);
+    L.off_shops = take(L.hops ? bnnz * 8 : 0);
     L.off_srec = take(L.bv ? (long long)L.pools * L.K * L.s_rec_stride * 8 : 0);
     L.total = o;
     return L;
@@ -394,6 +396,7 @@ struct Ctx {
     long long tau = 0;     // weighted: the problem's tau (fixes the shift)
     int shift = 0;         // weighted: fixed-point shift k of the counts
     int nslots = 0, nblocks = 0;  // per-block variant: slots of G*, blocks of G
+    bool hops_ready = false;  // the rows per slot have been queued
 };
 
 // tau of the problem set up in c
@@ -414,6 +417,36 @@ int check_ws(void *ws, size_t ws_bytes, long long need) {
     if (!ws) return fail(USTD_EINVAL, "workspace is NULL");
     if ((reinterpret_cast<uintptr_t>(ws) & (kAlign - 1)) != 0) return fail(USTD_EINVAL, "workspace must be 256-byte aligned");
     if ((long long)ws_bytes < need) return fail(USTD_ENOMEM, "workspace %zu bytes < required %lld", ws_bytes, need);
+    return USTD_OK;
+}
+
+// LDS bytes of a graph that the sampler holds there (0: it does not): a small unweighted one, when
+// that leaves `blocks` trees running at once; hops: with the packed rows of the lone walks (32 x 32
+// grid, 1000 trees: 2.9 ms with them, 3.9 ms without).
+long long graph_in_lds(const Plan &L, int blocks, bool *hops) {
+    *hops = false;
+    if (!L.lds_bits || !L.col16 || L.weighted || L.bv) return 0;
+    for (bool h : {true, false}) {
+        const long long gb = wilson_graph_lds_bytes(L.n, L.nnz, h);
+        if (gb <= kGraphLdsMaxBytes && wilson_resident_blocks_graph_lds(L.nwords, gb) >= blocks) {
+            *hops = h;
+            return gb;
+        }
+    }
+    return 0;
+}
+
+// The rows per slot that the sampler's lone walks read (the columns have been validated).
+int queue_hops(Ctx &c, hipStream_t st) {
+    c.hops_ready = true;
+    HIP_TRY(launch_hops(c.L.nnz, c.p->d_col, c.rp32, at<unsigned long long>(c.ws, c.L.off_hops), st));
+    return USTD_OK;
+}
+// In the set-up where every sampler launch reads them or several streams sample; a graph within the
+// LDS bitmap (one pool, one stream) builds them before its first launch that reads them, if any:
+// calls without trees and graphs held in LDS do without.
+int setup_hops(Ctx &c) {
+    if (c.L.hops && !c.L.bv && (!c.L.lds_bits || c.L.K == 0)) return queue_hops(c, c.st);
     return USTD_OK;
 }
 
@@ -652,10 +685,8 @@ int setup_graph(Ctx &c, ustd_report *rep) {
         HIP_TRY(hipStreamSynchronize(c.st));
         if (out[1]) return fail(USTD_EGRAPH, "graph is not connected");
         c.ecc = out[0];
-        if (c.L.edges) {
-            HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(c.ws, c.L.off_bflag), at<int4>(c.ws, c.L.off_vrow), c.st));
-            HIP_TRY(launch_edge_rows(c.L.nnz, c.p->d_col, at<int4>(c.ws, c.L.off_vrow), at<int4>(c.ws, c.L.off_edge), c.st));
-        }
+        if (c.L.vrows) HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(c.ws, c.L.off_bflag), at<int4>(c.ws, c.L.off_vrow), c.st));
+        USTD_TRY(setup_hops(c));
         USTD_TRY(setup_weighted(c));
         if (rep) {
             setup_report(c, rep);
@@ -672,10 +703,8 @@ int setup_graph(Ctx &c, ustd_report *rep) {
     // subtree intervals of B_u (fixed for every tree): bint[x] = {pre_B, size_B}
     HIP_TRY(launch_b_intervals(n, c.pivot, c.ecc, dist, parB, at<int>(c.ws, c.L.off_scr), at<int2>(c.ws, c.L.off_bint),
                                at<int>(c.ws, c.L.off_bflag), c.st));
-    if (c.L.edges) {  // the sampler's vertex and edge entries
-        HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(c.ws, c.L.off_bflag), at<int4>(c.ws, c.L.off_vrow), c.st));
-        HIP_TRY(launch_edge_rows(c.L.nnz, c.p->d_col, at<int4>(c.ws, c.L.off_vrow), at<int4>(c.ws, c.L.off_edge), c.st));
-    }
+    if (c.L.vrows) HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(c.ws, c.L.off_bflag), at<int4>(c.ws, c.L.off_vrow), c.st));
+    USTD_TRY(setup_hops(c));
     USTD_TRY(setup_weighted(c));
     if (rep) {
         setup_report(c, rep);
@@ -728,10 +757,8 @@ int setup_blocks(Ctx &c) {
     int *sbflag = at<int>(ws, L.off_sbflag);
     HIP_TRY(launch_fill_i32(ns, sbflag, 0, st));
     if (L.s_col16) HIP_TRY(launch_col_to_u16(nnz, scol, at<unsigned short>(ws, L.off_scol16), st));
-    if (L.s_edges) {
-        HIP_TRY(launch_vertex_rows(ns, rps, sbflag, at<int4>(ws, L.off_svrow), st));
-        HIP_TRY(launch_edge_rows(nnz, scol, at<int4>(ws, L.off_svrow), at<int4>(ws, L.off_sedge), st));
-    }
+    if (L.s_vrows) HIP_TRY(launch_vertex_rows(ns, rps, sbflag, at<int4>(ws, L.off_svrow), st));
+    if (L.hops) HIP_TRY(launch_hops(nnz, scol, rps, at<unsigned long long>(ws, L.off_shops), st));
     int cnt[2] = {0, 0};
     HIP_TRY(hipMemcpyAsync(&cnt[0], &c.misc->nroots, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipMemcpyAsync(&cnt[1], &c.misc->ntops, sizeof(int), hipMemcpyDeviceToHost, st));
@@ -753,8 +780,8 @@ WilsonGraph wilson_graph(const Ctx &c) {
     g.rp = c.rp32;
     g.colv = c.L.col16 ? (const void *)at<unsigned short>(c.ws, c.L.off_col16) : (const void *)c.p->d_col;
     g.bflag = at<int>(c.ws, c.L.off_bflag);
-    g.vrow = c.L.edges ? at<int4>(c.ws, c.L.off_vrow) : nullptr;
-    g.edge = c.L.edges ? at<int4>(c.ws, c.L.off_edge) : nullptr;
+    g.vrow = c.L.vrows ? at<int4>(c.ws, c.L.off_vrow) : nullptr;
+    g.hops = c.L.hops ? at<unsigned long long>(c.ws, c.L.off_hops) : nullptr;
     g.cw = c.L.weighted ? at<double>(c.ws, c.L.off_cw) : nullptr;
     g.guide = c.L.weighted ? at<int>(c.ws, c.L.off_guide) : nullptr;
     g.key0 = (uint32_t)(c.p->seed & 0xFFFFFFFFull);
@@ -784,8 +811,8 @@ int sample_batch_blocks(Ctx &c, long long tree_begin, int ntrees, long long *ste
     g.rp = at<int>(c.ws, L.off_rps);
     g.colv = L.s_col16 ? (const void *)at<unsigned short>(c.ws, L.off_scol16) : (const void *)at<int>(c.ws, L.off_scol);
     g.bflag = at<int>(c.ws, L.off_sbflag);
-    g.vrow = L.s_edges ? at<int4>(c.ws, L.off_svrow) : nullptr;
-    g.edge = L.s_edges ? at<int4>(c.ws, L.off_sedge) : nullptr;
+    g.vrow = L.s_vrows ? at<int4>(c.ws, L.off_svrow) : nullptr;
+    g.hops = L.hops ? at<unsigned long long>(c.ws, L.off_shops) : nullptr;
     g.key0 = (uint32_t)(c.p->seed & 0xFFFFFFFFull);
     g.key1 = (uint32_t)(c.p->seed >> 32);
     a.ntiles = ntrees;
@@ -830,12 +857,10 @@ int sample_batch(Ctx &c, long long tree_begin, int ntrees, long long *steps, lon
     int blocks = std::min(ntrees, c.L.slots);
     const int resident = wilson_resident_blocks(c.L.lds_bits, c.L.col16, c.L.weighted, c.L.nwords);
     if (resident > 0) blocks = std::min(blocks, resident);
-    // a small unweighted graph also goes into LDS when that leaves as many trees running at once
-    long long gl = 0;
-    if (c.L.lds_bits && c.L.col16 && !c.L.weighted) {
-        const long long gb = wilson_graph_lds_bytes(c.L.n, c.L.nnz);
-        if (gb <= kGraphLdsMaxBytes && wilson_resident_blocks_graph_lds(c.L.nwords, gb) >= blocks) gl = gb;
-    }
+    bool lds_hops = false;
+    const long long gl = graph_in_lds(c.L, blocks, &lds_hops);
+    a.lds_hops = lds_hops ? 1 : 0;
+    if (gl == 0 && c.L.hops && !c.hops_ready) USTD_TRY(queue_hops(c, st));
     HIP_TRY(hipMemsetAsync(&c.misc->queue[pool], 0, sizeof(int), st));
     HIP_TRY(launch_wilson(a, blocks, c.L.lds_bits, c.L.col16, c.L.weighted, c.L.nwords, st, gl));
     return USTD_OK;
@@ -1287,10 +1312,8 @@ int setup_replay(Ctx &c) {
         HIP_TRY(launch_b_intervals(n, c.pivot, c.ecc, dist, parB, at<int>(ws, L.off_scr), at<int2>(ws, L.off_bint),
                                    at<int>(ws, L.off_bflag), st));
     }
-    if (L.edges) {
-        HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(ws, L.off_bflag), at<int4>(ws, L.off_vrow), st));
-        HIP_TRY(launch_edge_rows(L.nnz, p->d_col, at<int4>(ws, L.off_vrow), at<int4>(ws, L.off_edge), st));
-    }
+    if (L.vrows) HIP_TRY(launch_vertex_rows(n, c.rp32, at<int>(ws, L.off_bflag), at<int4>(ws, L.off_vrow), st));
+    USTD_TRY(setup_hops(c));
     if (L.weighted) {
         double *wB = at<double>(ws, L.off_wB);
         HIP_TRY(launch_fill_i64(1, reinterpret_cast<long long *>(&c.misc->rho_max_bits), 0, st));
@@ -1924,13 +1947,19 @@ int fit_static(const ustd_problem *prob, ustd_problem *q, Plan *L) {
     q->solve_engine = USTD_ENGINE_WORKGROUP;
     if (prob->trees_per_batch > 0) {
         *L = make_plan(q);
+        if ((size_t)L->total > kStaticScratchBytes) *L = make_plan(q, true, false, false);
         if ((size_t)L->total > kStaticScratchBytes)
             return fail(USTD_ENOMEM, "the problem needs %lld bytes of scratch at %d trees per batch; the static "
                                      "scratch holds %zu", L->total, prob->trees_per_batch, kStaticScratchBytes);
         return USTD_OK;
     }
     q->trees_per_batch = 1;
+    bool hops = true;
     *L = make_plan(q);
+    if ((size_t)L->total > kStaticScratchBytes) {
+        hops = false;
+        *L = make_plan(q, true, false, false);
+    }
     if ((size_t)L->total > kStaticScratchBytes)
         return fail(USTD_ENOMEM, "the problem needs %lld bytes of scratch even at one tree per batch; the static "
                                  "scratch holds %zu", L->total, kStaticScratchBytes);
@@ -1938,11 +1967,11 @@ int fit_static(const ustd_problem *prob, ustd_problem *q, Plan *L) {
     while (lo < hi) {
         const int mid = lo + (hi - lo + 1) / 2;
         q->trees_per_batch = mid;
-        if ((size_t)make_plan(q).total <= kStaticScratchBytes) lo = mid;
+        if ((size_t)make_plan(q, true, false, hops).total <= kStaticScratchBytes) lo = mid;
         else hi = mid - 1;
     }
     q->trees_per_batch = lo;
-    *L = make_plan(q);
+    *L = make_plan(q, true, false, hops);
     return USTD_OK;
 }
 

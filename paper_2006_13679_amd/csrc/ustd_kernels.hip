@@ -425,9 +425,8 @@ __device__ __forceinline__ bool since(uint16_t stamp, int r) { return (int16_t)(
 // first j with C[j] > t(w_i), w_i the bucket's smallest word.  t is non-decreasing in w, so
 // that j never passes the answer, and a forward scan ends on it; buckets are equally wide
 // in t, so the scan takes one probe on average for any weights (deg boundaries, deg buckets).
-template <bool WT>
-__device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, const double *__restrict__ cw,
-                                          const int *__restrict__ guide) {
+template <bool WT, typename Sums, typename Guide>
+__device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, Sums cw, Guide guide) {
     const int bucket = (int)__umulhi(w, (uint32_t)(r1 - r0));
     if constexpr (!WT) {
         return bucket;
@@ -440,8 +439,8 @@ __device__ __forceinline__ int step_index(uint32_t w, int r0, int r1, const doub
     }
 }
 
-// ---- the one-lane walk: the sequential algorithm for one start against the current tree, in
-// two parts: a walk that writes Next pointers until it reaches the tree, then the retrace of the
+// ---- the lone walk: the sequential algorithm for one start against the current tree, in two
+// parts: a walk that writes Next pointers until it reaches the tree, then the retrace of the
 // loop erasure that writes the branch's records.  The walk resumes at step k0 from vertex x0
 // (k0 = 0, x0 = s0 for a whole walk; otherwise the Next pointers of steps 0..k0-1 are already
 // written).  Every lane calls both.
@@ -459,89 +458,119 @@ __device__ __forceinline__ long long uniform_ll(long long k) {
     return (long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo);
 }
 
-// Lane 0 walks; the wave computes its Philox words 256 at a time (lane i the block of steps
-// 4 (b0 + i) .. + 3) into wbuf (LDS), so that a step reads a word instead of running a ten-round
-// block on one lane every fourth step.  Graphs past the LDS bitmap read the edge entries {y, row
-// of y, B_u flag of y}: the entry of step k gives everything step k + 1 needs, so step k + 1's
-// entry is loaded together with the tree test of y (before its answer is known) and a step waits
-// for one load, not two in a row; the Next pointer is stored after both loads are issued, so a
-// step does not wait for the store.  Graphs within it read the compact column and row arrays.
-// Returns the walk's total step count (on every lane).
-template <bool LDS, typename CT, bool WT, typename Next>
-__device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, const int *__restrict__ rp,
-                               const CT *__restrict__ col, const int4 *__restrict__ edge,
-                               const int4 *__restrict__ vrow, const double *__restrict__ cw,
-                               const int *__restrict__ guide, uint32_t wkey, int x0, long long k0, uint32_t tlo,
-                               uint32_t thi, uint32_t key0, uint32_t key1, uint32_t *wbuf) {
+// Tables that no kernel writes while the sampler runs, read at wave-uniform addresses through the
+// scalar cache.
+template <typename T>
+using scalar_ptr = const __attribute__((address_space(4))) T *;
+template <typename T>
+__device__ __forceinline__ scalar_ptr<T> scalar(const T *p) {
+    return (scalar_ptr<T>)(uintptr_t)uniform_ll((long long)(uintptr_t)p);
+}
+// column of a CSR slot at a wave-uniform address (scalar loads take whole words; nnz is even)
+__device__ __forceinline__ int scalar_col(const int *col, int slot) { return scalar(col)[slot]; }
+__device__ __forceinline__ int scalar_col(const unsigned short *col, int slot) {
+    const uint32_t two = scalar(reinterpret_cast<const uint32_t *>(col))[slot >> 1];
+    return (int)((slot & 1) ? two >> 16 : two & 0xFFFFu);
+}
+
+// A lone walk is a chain of dependent loads and, on deep graphs, the critical path of the launch
+// (160 x 160 grid: 619,000 steps of the slowest tree), so the chain holds nothing but the next
+// row: the wave steps through a window of up to 64 steps without looking at the tree, every value
+// wave-uniform (a step's word is read from a lane's Philox block by readlane, the row of the
+// slot's vertex by one scalar load from `hops`), and keeps the slots, a lane each.  The lanes then
+// look up their steps' vertices and test them together; steps past the first tree vertex are
+// dropped.  Next pointers: the last step out of a vertex counts, found by comparing all pairs.
+//   graph in LDS (GL): the row comes from the packed entries `lhops` {begin, degree << 16}, or
+//   from the columns and row pointers where those do not fit;
+//   no `hops` (they did not fit the workspace): from the columns and row pointers, two loads.
+// Cycles a step, one lane stepping with the tree test and the store in its chain -> this: rows from
+// L2 (160 x 160 grid) 589 -> 227, graph in LDS (32 x 32) 277 -> 161, rows past L2 with the GPU full
+// (hyperbolic, n = 200k) 1812 -> 1200.
+// Returns the walk's total step count.
+template <bool LDS, typename CT, bool WT, bool GL, typename Next>
+__device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, const int *rp, const CT *col,
+                               const unsigned long long *hops, const uint32_t *lhops, const double *cw, const int *guide,
+                               uint32_t wkey, int x0, long long k0, uint32_t tlo, uint32_t thi, uint32_t key0,
+                               uint32_t key1) {
     const int lane = threadIdx.x;
-    long long k = k0;  // wave-uniform between word blocks
+    long long k = k0;
     int xw = x0;
-    int r0 = 0, r1 = 0;  // LDS bitmap: the row of xw
-    int4 e = make_int4(-1, 0, 0, 0);  // else: the entry of step k - 1, the step to take from xw
-    if (lane == 0) {
-        if constexpr (LDS) {
-            r0 = rp[x0];
-            r1 = rp[x0 + 1];
-        } else {
-            const int4 v0 = vrow[x0];
-            r0 = v0.x;
-            r1 = v0.y;
-        }
+    int r0 = __builtin_amdgcn_readfirstlane(rp[x0]);  // the row of xw: begin, degree
+    int deg = __builtin_amdgcn_readfirstlane(rp[x0 + 1]) - r0;
+    if constexpr (GL) {  // LDS answers in vector registers: the chain stays there
+        asm volatile("" : "+v"(r0));
+        asm volatile("" : "+v"(deg));
     }
     for (;;) {
-        const long long b0 = k >> 2;
-        const uint4 ph = philox4x32_10(make_uint4((uint32_t)(b0 + lane), wkey, tlo, thi), key0, key1);
-        reinterpret_cast<uint4 *>(wbuf)[lane] = ph;
-        wave_sync();
-        int fin = 0;
-        if (lane == 0) {
-            const uint32_t *wk = wbuf + (int)(k - b0 * 4);
-            int left = 4 * kWave - (int)(k - b0 * 4);
-            uint32_t w = *wk;
-            if constexpr (LDS) {
-                for (;;) {
-                    ++wk;
-                    const int y = (int)col[r0 + step_index<WT>(w, r0, r1, cw, guide)];
-                    w = *wk;  // the next step's word (past the last one: never used)
-                    --left;
-                    r0 = rp[y];
-                    r1 = rp[y + 1];
-                    const bool in = bits.test(y);
-                    next.set(xw, y);
-                    if (in) {
-                        fin = 1;
-                        break;
-                    }
-                    xw = y;
-                    if (left == 0) break;
+        // lane i: the words of steps 4 (k / 4 + i) .. + 3; a window is 64 of them from a multiple of 64
+        const uint4 ph = philox4x32_10(make_uint4((uint32_t)((k >> 2) + lane), wkey, tlo, thi), key0, key1);
+        int j0 = (int)(k & 3);  // first step of the window
+        for (int win = 0; win < 4; ++win) {
+            int slots = 0;
+            auto chase = [&](auto row) {
+                auto step = [&](uint32_t w, int j) {
+                    const int slot = r0 + step_index<WT>(w, r0, r0 + deg, scalar(cw), scalar(guide));
+                    slots = lane == j ? slot : slots;
+                    row(slot);
+                };
+                int j = j0;
+                for (; j & 3; ++j) {
+                    const uint32_t w = (j & 3) == 1 ? ph.y : ((j & 3) == 2 ? ph.z : ph.w);
+                    step((uint32_t)__builtin_amdgcn_readlane((int)w, 16 * win + (j >> 2)), j);
                 }
+                for (; j < kWave; j += 4) {
+                    const int l = 16 * win + (j >> 2);
+                    step((uint32_t)__builtin_amdgcn_readlane((int)ph.x, l), j);
+                    step((uint32_t)__builtin_amdgcn_readlane((int)ph.y, l), j + 1);
+                    step((uint32_t)__builtin_amdgcn_readlane((int)ph.z, l), j + 2);
+                    step((uint32_t)__builtin_amdgcn_readlane((int)ph.w, l), j + 3);
+                }
+            };
+            if constexpr (GL) {
+                if (lhops)
+                    chase([&](int slot) {
+                        const uint32_t h = lhops[slot];
+                        r0 = (int)(h & 0xFFFFu);
+                        deg = (int)(h >> 16);
+                    });
+                else
+                    chase([&](int slot) {
+                        const int y = col[slot];
+                        r0 = rp[y];
+                        deg = rp[y + 1] - r0;
+                    });
+            } else if (hops) {
+                chase([&](int slot) {
+                    const unsigned long long h = scalar(hops)[(uint32_t)slot];
+                    r0 = (int)(uint32_t)h;
+                    deg = (int)(uint32_t)(h >> 32);
+                });
             } else {
-                if (e.x < 0) {
-                    e = edge[r0 + step_index<WT>(w, r0, r1, cw, guide)];
-                    ++wk;
-                    --left;
-                    w = *wk;
-                }
-                while (left > 0) {
-                    ++wk;
-                    const int4 en = edge[e.y + step_index<WT>(w, e.y, e.z, cw, guide)];
-                    const int t = bits.nbx(e.x);
-                    w = *wk;
-                    next.set(xw, e.x);
-                    if (t != kFree) {
-                        fin = 1;
-                        break;
-                    }
-                    --left;
-                    xw = e.x;
-                    e = en;
-                }
+                chase([&](int slot) {
+                    const int y = scalar_col(col, slot);
+                    r0 = scalar(rp)[y];
+                    deg = scalar(rp)[y + 1] - r0;
+                });
             }
-            k = (b0 + kWave) * 4 - left;
+            const bool on = lane >= j0;
+            const int y = on ? (int)col[slots] : 0;
+            const uint64_t in = __ballot(on && bits.test(y));
+            const int end = in ? __builtin_ctzll(in) : kWave - 1;  // the last step taken
+            int x = __shfl_up(y, 1, kWave);
+            if (lane == j0) x = xw;
+            const bool taken = on && lane <= end;
+            const int xt = taken ? x : -1;
+            uint64_t again = 0ull;  // x is left again further on
+#pragma unroll
+            for (int j = 1; j < kWave; ++j)
+                again |= __ballot(xt == __builtin_amdgcn_readlane(xt, j)) & ((1ull << j) - 1ull);
+            if (taken && !((again >> lane) & 1ull)) next.set(x, y);
+            wave_sync();
+            k += end + 1 - j0;
+            if (in) return k;
+            xw = __builtin_amdgcn_readlane(y, kWave - 1);
+            j0 = 0;
         }
-        wave_sync();  // the words are read before they are overwritten
-        k = uniform_ll(k);
-        if (__builtin_amdgcn_readfirstlane(fin)) return k;
     }
 }
 
@@ -630,35 +659,45 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     __shared__ uint8_t rob_k[kRobMax];
     __shared__ uint8_t rob_pb[kRobMax];  // edge bits of steps 1..kPathLds, 2 bits each
     __shared__ uint16_t rob_r[LDS ? 1 : kRobMax];  // round of a finished walk's last step (low 16 bits)
-    __shared__ alignas(16) int htab[2 * kHashSlots + 4];  // a word past the end is read, not used
+    __shared__ alignas(16) int htab[2 * kHashSlots];
     __shared__ uint16_t stamps[LDS ? 1 : kStamps];
     __shared__ uint8_t win[kWin];  // free vertices of the window, as offsets
     int *const hslot = htab;                // first conflict table
-    int *const hslot2 = htab + kHashSlots;  // second conflict table; together the one-lane walk's
-                                            // words and pieces (then cleared again)
-    static_assert(kPath + 1 <= 2 * kHashSlots && 4 * kWave <= 2 * kHashSlots, "a record, and the words, fit the tables");
+    int *const hslot2 = htab + kHashSlots;  // second conflict table; together the record of an
+                                            // overflowed walk and a retrace's pieces (then cleared)
+    static_assert(kPath + 1 <= 2 * kHashSlots, "a record fits the tables");
     static_assert(kPathLds * 2 <= 8, "edge bits fit rob_pb");
 
     const int lane = threadIdx.x;
     int *__restrict__ gpath = a.path + (long long)blockIdx.x * kSamplerPathSlot;
 
     // GL (small graphs, single-graph launches): the row pointers, B_u flags and 16-bit columns
-    // are copied into LDS after the tree bitmap, once per block, so that walk steps (above all
-    // the one-lane walks) read LDS instead of the L1/L2.
+    // are copied into LDS after the tree bitmap, once per block, so that walk steps read LDS
+    // instead of the L1/L2; with a.lds_hops also the rows of the lone walk, packed.
     const int *lrp = nullptr, *lbf = nullptr;
+    const uint32_t *lhops = nullptr;
     const CT *lcol = nullptr;
     if constexpr (GL) {
         static_assert(LDS && !WT && sizeof(CT) == 2, "graph in LDS: small unweighted graphs");
         const int n0 = a.g.n;
         int *srp = reinterpret_cast<int *>(lds_bits + a.g.nwords);
         int *sbf = srp + n0 + 1;
-        CT *scol = reinterpret_cast<CT *>(sbf + n0);
         const int nnz0 = a.g.rp[n0];
+        uint32_t *shop = reinterpret_cast<uint32_t *>(sbf + n0);
+        CT *scol = reinterpret_cast<CT *>(shop + (a.lds_hops ? nnz0 : 0));
         const CT *gcol = reinterpret_cast<const CT *>(a.g.colv);
         for (int i = lane; i <= n0; i += kWave) srp[i] = a.g.rp[i];
         for (int i = lane; i < n0; i += kWave) sbf[i] = a.g.bflag[i];
         for (int i = lane; i < nnz0; i += kWave) scol[i] = gcol[i];
         wave_sync();
+        if (a.lds_hops) {
+            for (int i = lane; i < nnz0; i += kWave) {
+                const int y = (int)scol[i];
+                shop[i] = (uint32_t)srp[y] | ((uint32_t)(srp[y + 1] - srp[y]) << 16);
+            }
+            wave_sync();
+            lhops = shop;
+        }
         lrp = srp;
         lbf = sbf;
         lcol = scol;
@@ -699,7 +738,6 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     const NextRec next{par};
     const int *__restrict__ bflag = GL ? lbf : g.bflag;
     const int4 *__restrict__ vrow = g.vrow;
-    const int4 *__restrict__ edge = g.edge;  // set when the tree state is in global memory
     const int u = g.u;
     const int *__restrict__ rp = GL ? lrp : g.rp;
     const CT *__restrict__ col = GL ? lcol : reinterpret_cast<const CT *>(g.colv);  // int32, or uint16 when n <= 65536
@@ -1072,7 +1110,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                 }
             }
             if (hs == kContinue || hs == kRewalk) {
-                // lane 0 runs the sequential algorithm for this start against the current tree
+                // the sequential algorithm for this start against the current tree
                 // (all earlier starts are committed).  An overflowed walk whose record misses
                 // the tree resumes after its record: the recorded steps become Next pointers.
                 const long long k0 = hs == kContinue ? kPath : 0;
@@ -1091,8 +1129,9 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                 }
                 uint32_t wk0 = (uint32_t)s0;  // the walk's Philox key
                 if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
-                const long long kk = walk_next<LDS, CT, WT>(bits, next, rp, col, edge, vrow, cw, guide, wk0, xs, k0, tlo, thi,
-                                                            g.key0, g.key1, reinterpret_cast<uint32_t *>(htab));
+                const long long kk = walk_next<LDS, CT, WT, GL>(bits, next, rp, col, g.hops, lhops, cw, guide, wk0,
+                                                                __builtin_amdgcn_readfirstlane(xs), k0, tlo, thi, g.key0,
+                                                                g.key1);
                 retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
                 wsteps += kk;
@@ -2163,8 +2202,8 @@ int wilson_resident_blocks(bool lds_bits, bool col16, bool weighted, int nwords,
     if (!ok) return 0;
     return std::max(1, per_cu) * std::max(1, cus);
 }
-long long wilson_graph_lds_bytes(int n, long long nnz) {
-    return ((long long)(n + 1) * 4 + (long long)n * 4 + nnz * 2 + 3) / 4 * 4;
+long long wilson_graph_lds_bytes(int n, long long nnz, bool hops) {
+    return ((long long)(n + 1) * 4 + (long long)n * 4 + (hops ? nnz * 4 : 0) + nnz * 2 + 3) / 4 * 4;
 }
 int wilson_resident_blocks_graph_lds(int nwords, long long graph_bytes) {
     int dev = 0, cus = 0, per_cu = 0;
@@ -2348,16 +2387,15 @@ hipError_t launch_vertex_rows(int n, const int *rp, const int *bflag, int4 *vrow
     vertex_rows_kernel<<<blocks_for(n, 256), 256, 0, st>>>(n, rp, bflag, vrow);
     return hipGetLastError();
 }
-__global__ void edge_rows_kernel(long long nnz, const int *__restrict__ col, const int4 *__restrict__ vrow,
-                                 int4 *__restrict__ edge) {
+__global__ void hops_kernel(long long nnz, const int *__restrict__ col, const int *__restrict__ rp,
+                            unsigned long long *__restrict__ hops) {
     for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < nnz; i += (long long)gridDim.x * blockDim.x) {
         const int y = col[i];
-        const int4 r = vrow[y];
-        edge[i] = make_int4(y, r.x, r.y, r.z);
+        hops[i] = (uint32_t)rp[y] | ((unsigned long long)(uint32_t)(rp[y + 1] - rp[y]) << 32);
     }
 }
-hipError_t launch_edge_rows(long long nnz, const int *col, const int4 *vrow, int4 *edge, hipStream_t st) {
-    edge_rows_kernel<<<(int)std::min<long long>(blocks_for(nnz, 256), 16384), 256, 0, st>>>(nnz, col, vrow, edge);
+hipError_t launch_hops(long long nnz, const int *col, const int *rp, unsigned long long *hops, hipStream_t st) {
+    hops_kernel<<<(int)std::min<long long>(blocks_for(nnz, 256), 16384), 256, 0, st>>>(nnz, col, rp, hops);
     return hipGetLastError();
 }
 hipError_t launch_check_weights(int n, const int *rp, const int *col, const double *w, int *err, hipStream_t st) {

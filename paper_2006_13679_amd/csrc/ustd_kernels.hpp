@@ -25,9 +25,9 @@ struct WilsonGraph {
     const int *rp;
     const void *colv;       // column indices: int32, or uint16 when the launch says so
     const int *bflag;       // [n] (parB + 1) | (internal in B_u) << 31
-    // graphs whose tree state is in global memory (past the LDS bitmap):
-    const int4 *vrow;       // [n] {rp[v], rp[v+1], bflag[v], 0}
-    const int4 *edge;       // [nnz] entry (x, y): {y, rp[y], rp[y+1], bflag[y]}: a walk step's loads
+    const int4 *vrow;       // [n] {rp[v], rp[v+1], bflag[v], 0} (tree state in the records)
+    // [nnz] slot (x, y): rp[y] | deg(y) << 32, a lone walk's step; null: columns and row pointers
+    const unsigned long long *hops;
     const double *cw;       // [nnz] running conductance sums of each row (weighted launches)
     const int *guide;       // [nnz] start of the weighted step search per (row, bucket)
     uint32_t key0, key1;    // Philox key (seed)
@@ -50,6 +50,7 @@ struct WilsonArgs {
     int ntiles;
     long long tree_begin;
     int *rec;                   // records: per tree the words nba | flags, then the parents
+    int lds_hops;               // graph in LDS: the packed rows of its slots too
     int parents;                // 0: only the parents that Algorithm 2 reads are written (marked
                                 // vertices whose tree edge is a backward B_u edge)
     int *path;                  // [blocks][kSamplerPathSlot] recorded steps beyond the LDS part
@@ -185,7 +186,7 @@ int wilson_resident_blocks(bool lds_bits, bool col16, bool weighted, int nwords,
 // Small unweighted graphs (16-bit columns, LDS tree bitmap) may keep the graph in LDS as well:
 // its bytes there (row pointers, B_u flags, columns), and the resident blocks of such a
 // launch by the LDS residency measured on gfx950 (two 80 KB halves, 256-byte units).
-long long wilson_graph_lds_bytes(int n, long long nnz);
+long long wilson_graph_lds_bytes(int n, long long nnz, bool hops);
 int wilson_resident_blocks_graph_lds(int nwords, long long graph_bytes);
 // graph_lds_bytes > 0 (single-graph launches only): the graph-in-LDS variant
 // block_split: the block-split graph of the per-block variant (several roots, keyed starts)
@@ -202,7 +203,7 @@ hipError_t launch_row_cumsum(int n, int nnz, const int *rp, const double *w, int
                              const int *nheavy, double *cw, double *wdeg, int *guide, hipStream_t st);
 hipError_t launch_check_weights(int n, const int *rp, const int *col, const double *w, int *err, hipStream_t st);
 hipError_t launch_vertex_rows(int n, const int *rp, const int *bflag, int4 *vrow, hipStream_t st);
-hipError_t launch_edge_rows(long long nnz, const int *col, const int4 *vrow, int4 *edge, hipStream_t st);
+hipError_t launch_hops(long long nnz, const int *col, const int *rp, unsigned long long *hops, hipStream_t st);
 hipError_t launch_bpath(int n, int u, const int *rp, const int *col, const double *w, const int *parB, double *wB,
                         unsigned long long *rmax_bits, hipStream_t st);
 hipError_t launch_fixed_weights(int n, int u, const double *wB, int shift, long long *F, hipStream_t st);
