@@ -405,10 +405,10 @@ static_assert(kHashSlots == 128, "the hashes give seven bits");
 // lately without a global load: an inner vertex of a walk committed in round r (commits of a round
 // follow its steps) leaves r at its slot, so a vertex read as free in round q is still free if
 // its slot holds less than q and it is not a start that has been committed since.  A collision
-// only costs the load.
-constexpr int kStamps = 256;
-__device__ __forceinline__ int stamp_slot(int v) { return (int)(((unsigned)v * 2654435761u) >> 24); }
-static_assert(kStamps == 256, "the hash gives eight bits");
+// only costs the load (a long walk's commit leaves a dozen rounds, so 256 slots answered few).
+constexpr int kStamps = 1024;
+__device__ __forceinline__ int stamp_slot(int v) { return (int)(((unsigned)v * 2654435761u) >> 22); }
+static_assert(kStamps == 1024, "the hash gives ten bits");
 // Rounds are kept modulo 2^16: whether `stamp` is round r or later.  A walk ends, and a window's
 // last start is taken, well within 2^15 rounds (a walk takes at most kPath steps, a window's starts
 // pass through the reorder buffer in a few lifetimes of one), so a later stamp is never taken for an
@@ -1087,6 +1087,68 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
             // whole record, K = kPath): lane j holds x_{j+64c} and the edge bits of the step into it
             const bool ended = hs <= kPath;  // the walk reached the tree it saw
             const int K = ended ? hs : kPath;
+            if (ended && K < kWave) {
+                // nearly every long commit (hyperbolic, n = 200k: 8,300 a tree, 13 steps on average):
+                // one chunk and, the rounds table permitting, no look at the tree in global memory.
+                // With the four-chunk form below for all: hyperbolic 206 ms -> 197, R-MAT 19 trees
+                // 31.8 -> 30.9, all edges of R-MAT 16 5.44 -> 5.31
+                int xv = -1, xb = 0;
+                if (lane > kPathLds && lane <= K) {
+                    const int e = gpath[hsl * kSamplerPathGlobal + (lane - 1 - kPathLds)];
+                    xb = (int)((unsigned)e >> 30);
+                    xv = e & kVertexMask;
+                } else if (lane == 0) {
+                    xv = s0;
+                } else if (lane <= kPathLds) {
+                    xv = (int)rob_p[hsl].v[lane - 1];
+                    xb = ((int)rob_pb[hsl] >> (2 * (lane - 1))) & 3;
+                }
+                // the first vertex in T: x_K is; of the others those below s0 (all earlier starts are
+                // in T), and with the tree state in the records a load only where one may have joined
+                bool in = lane == K;
+                if constexpr (LDS) {
+                    in = lane >= 1 && lane <= K && bits.test(xv);
+                } else {
+                    const bool inner = lane >= 1 && lane < K;
+                    const bool look = inner && xv >= s0 && since(stamps[stamp_slot(xv)], (int)rob_r[hsl] - K + lane);
+                    in = in || (inner && xv < s0);
+                    if (__ballot(look)) {
+                        if (look) in = bits.test(xv);
+                    }
+                }
+                const int istar = __builtin_ctzll(__ballot(in));
+                const int ya = __builtin_amdgcn_readlane(xv, istar);
+                int carry = (int)rob_e[hsl].cv;
+                if (istar < K) carry = cv_of(ya, load_nbx(nbw, ya));
+                // loop erasure: from b, jump past b's last visit before istar
+                const uint64_t before = (1ull << istar) - 1ull;
+                uint64_t kept = 0ull;
+                int q = 0;
+                do {
+                    const uint64_t mm = __ballot(xv == __builtin_amdgcn_readlane(xv, q)) & before;  // holds q
+                    q = 63 - __builtin_clzll(mm);
+                    kept |= 1ull << q;
+                    ++q;
+                } while (q < istar);
+                const int nx = __shfl_down(xv, 1, kWave), nb = __shfl_down(xb, 1, kWave);
+                const bool mine = (kept >> lane) & 1ull;
+                const uint64_t m = __ballot(mine && (nb & 2));
+                const uint64_t above = lane < kWave - 1 ? (m & (~0ull << (lane + 1))) : 0ull;
+                const int up = __shfl(xv, above ? __builtin_ctzll(above) : 0, kWave);
+                if (mine) {
+                    vertex_at(nbw, xv) = (above ? up : carry) | (nb << 30);
+                    if (keeps_parent(nb)) vertex_at(par, xv) = nx;
+                    bits.set(xv);
+                    if constexpr (!LDS) stamps[stamp_slot(xv)] = (uint16_t)round;
+                }
+                if (lane == 0) steps += istar;
+                ++head;
+                wave_sync();
+                if constexpr (!LDS) {
+                    if (__ballot(mine && xv > s0 && xv <= shi)) remark();
+                }
+                continue;
+            }
             int xv[4] = {-1, -1, -1, -1}, xb[4] = {0, 0, 0, 0};
             if (hs != kRewalk) {
 #pragma unroll
