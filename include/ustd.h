@@ -285,7 +285,7 @@ typedef struct {
 
 enum {
     USTD_LAYOUT_AUTO = 0,    /* sampler tree state in an LDS bitmap when every member fits it */
-    USTD_LAYOUT_RECORDS = 1  /* tree state in the tree records and per-edge entries, for every member */
+    USTD_LAYOUT_RECORDS = 1  /* tree state in the tree records and per-vertex entries, for every member */
 };
 
 typedef struct ustd_batch_plan ustd_batch_plan; /* opaque */
