@@ -101,4 +101,33 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
     return block_sum_t<T>(v, sh, (int)blockDim.x);
 }
 
+// ---- CSR rows.  Slots are below 2^31 (nnz < 2^31), and a loop over a row in strides looks past the
+// row's end by up to a stride, so it counts in unsigned slots: a row that ends just below 2^31 does
+// not wrap.  (Host code too: the tests walk such rows on the CPU.)
+
+// acc + sum of the entries lo + first, lo + first + step, ... below hi, in that order, U loads at a
+// time; weighted entries with w
+template <typename T, int U>
+__host__ __device__ __forceinline__ T row_sum(T acc, const int *__restrict__ col, const double *__restrict__ w,
+                                              const T *__restrict__ p, int lo, int hi, uint32_t first, uint32_t step) {
+    const uint32_t end = (uint32_t)hi;
+    for (uint32_t e = (uint32_t)lo + first; e < end; e += U * step) {
+        int c[U];
+        T q[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            c[k] = -1;
+            if (e + k * step < end) c[k] = col[e + k * step];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            q[k] = (T)0;
+            if (c[k] >= 0) q[k] = w ? (T)w[e + k * step] * p[c[k]] : p[c[k]];
+        }
+#pragma unroll
+        for (int k = 0; k < U; ++k) acc += q[k];
+    }
+    return acc;
+}
+
 }  // namespace ustd

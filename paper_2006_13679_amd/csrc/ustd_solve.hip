@@ -42,29 +42,6 @@ static_assert(kSolveGrid <= kMaxSolveGrid, "partial results fit the workspace");
 // R-MAT scale 22 kept one workgroup busy for 1.0 ms of a 1.2 ms product.)
 constexpr int kRowsInFlight = 4;
 
-// acc + sum of the entries first, first + step, ... below end, in that order, U loads at a time
-template <typename T, int U>
-__device__ __forceinline__ T row_sum(T acc, const int *__restrict__ col, const double *__restrict__ w,
-                                     const T *__restrict__ p, int first, int end, int step) {
-    for (int e = first; e < end; e += U * step) {
-        int c[U];
-        T q[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            c[k] = -1;
-            if (e + k * step < end) c[k] = col[e + k * step];
-        }
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            q[k] = (T)0;
-            if (c[k] >= 0) q[k] = w ? (T)w[e + k * step] * p[c[k]] : p[c[k]];
-        }
-#pragma unroll
-        for (int k = 0; k < U; ++k) acc += q[k];
-    }
-    return acc;
-}
-
 // the light rows; R rows of a group in flight
 template <typename T, int G, int R, typename Emit>
 __device__ __forceinline__ void lap_light_rows(const RowMap &m, const T *__restrict__ p, Emit emit, int blk, int nblk,
@@ -103,7 +80,7 @@ __device__ __forceinline__ void lap_light_rows(const RowMap &m, const T *__restr
         for (int i = 0; i < R; ++i) {
             if ((tile + i * nblk) * rows_per_tile >= m.n) break;  // no row left for any group
             T acc = q[i][0] + q[i][1];
-            if (len[i] > 2 * G) acc = row_sum<T, 4>(acc, m.col, w, p, lo[i] + l + 2 * G, lo[i] + len[i], G);
+            if (len[i] > 2 * G) acc = row_sum<T, 4>(acc, m.col, w, p, lo[i], lo[i] + len[i], l + 2 * G, G);
 #pragma unroll
             for (int dd = G / 2; dd > 0; dd >>= 1) acc += __shfl_xor(acc, dd, G);
             if (deg[i] >= 0 && deg[i] <= m.heavy_thresh && l == 0) {
@@ -123,7 +100,7 @@ __device__ __forceinline__ void lap_apply_rows(const RowMap &m, const T *__restr
     for (int h = blk; h < nh; h += nblk) {
         const int v = m.heavy[h];
         const int lo = m.rp[v], hi = m.rp[v + 1];
-        T acc = row_sum<T, 8>((T)0, m.col, w, p, lo + threadIdx.x, hi, bs);
+        T acc = row_sum<T, 8>((T)0, m.col, w, p, lo, hi, threadIdx.x, bs);
         acc = block_sum_t<T>(acc, shr, bs);
         if (threadIdx.x == 0) emit(v, (w ? (T)m.wdeg[v] : (T)(hi - lo)) * p[v] - acc);
     }

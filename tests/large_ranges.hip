@@ -1,0 +1,74 @@
+// CPU driver of tests/test_large_ranges.py: functions of the kernels, compiled for the host, at the
+// largest sizes the API accepts.  Prints "ok" when every result is right.
+#include <sys/mman.h>
+
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "ustd_device.hpp"
+
+using namespace ustd;
+
+constexpr long long kEnd = (1ll << 31) - 2;  // one past the last slot: nnz is even and below 2^31
+constexpr long long kRow = 8192;             // readable slots below it
+constexpr int kVerts = 1000;
+
+// The column and weight arrays are reserved address space of the largest size, readable only at the
+// row itself, so an access outside ends the process.
+// entries [kEnd - kRow, kEnd) of an array that is addressed from its entry 0; 2^31 entries below
+// entry 0 are reserved too, where a wrapped index would land
+template <typename T>
+T *reserve() {
+    const size_t half = sizeof(T) << 31;
+    char *m = static_cast<char *>(mmap(nullptr, 2 * half, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
+    if (m == MAP_FAILED) exit(2);
+    T *base = reinterpret_cast<T *>(m + half);
+    const size_t page = 4096, lo = (size_t)(kEnd - kRow) * sizeof(T) / page * page;
+    if (mprotect(reinterpret_cast<char *>(base) + lo, half - lo, PROT_READ | PROT_WRITE) != 0) exit(2);
+    return base;
+}
+
+void check(bool ok, const char *what, long long a, long long b) {
+    if (ok) return;
+    printf("wrong: %s %lld %lld\n", what, a, b);
+    exit(1);
+}
+
+template <int U>
+void sums(const int *col, const double *w, const std::vector<double> &p, uint32_t threads) {
+    for (long long len : {1ll, 31ll, 129ll, 255ll, 256ll, 257ll, 1000ll, 2047ll, 2048ll, 2049ll, 5000ll, kRow}) {
+        const long long lo = kEnd - len;
+        for (const double *wt : {(const double *)nullptr, w}) {
+            double want = 0, got = 0;
+            for (long long e = lo; e < kEnd; ++e) want += (wt ? wt[e] : 1.0) * p[col[e]];
+            for (uint32_t t = 0; t < threads; ++t)
+                got += row_sum<double, U>(0.0, col, wt, p.data(), (int)lo, (int)kEnd, t, threads);
+            check(got == want, "row_sum", U, len);
+        }
+    }
+}
+
+// the row sums of the product on rows that end at the largest slot
+void row_sums() {
+    int *col = reserve<int>();
+    double *w = reserve<double>();
+    for (long long e = kEnd - kRow; e < kEnd; ++e) {
+        col[e] = (int)(e * 7 % kVerts);
+        w[e] = (double)(1 + e % 3);
+    }
+    std::vector<double> p(kVerts);  // small integers: sums are exact in any order
+    for (int v = 0; v < kVerts; ++v) p[v] = v - 400;
+    sums<8>(col, w, p, 256);   // heavy rows of the multi-kernel engine
+    sums<8>(col, w, p, 1024);  // and of the one-workgroup engine
+    for (uint32_t g : {4u, 8u, 16u, 32u}) sums<4>(col, w, p, g);  // light rows
+}
+
+int main(int argc, char **argv) {
+    const char *what = argc > 1 ? argv[1] : "";
+    if (!strcmp(what, "row_sums")) row_sums();
+    else return 2;
+    puts("ok");
+    return 0;
+}

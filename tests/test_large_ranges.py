@@ -1,0 +1,24 @@
+"""Functions of the kernels at the largest sizes the API accepts (rows that end just below 2^31
+slots), compiled for the host and run on the CPU (large_ranges.hip)."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2006_13679_amd import build
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("large_ranges") / "driver")
+    subprocess.check_call([build.hipcc(), "--offload-host-only", "-O2", "-std=c++17", "-I", build.CSRC,
+                           os.path.join(HERE, "large_ranges.hip"), "-o", exe])
+    return exe
+
+
+@pytest.mark.parametrize("what", ["row_sums"])
+def test_on_the_host(driver, what):
+    r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
+    assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
