@@ -104,11 +104,11 @@ __global__ __launch_bounds__(256) void bc_local_kernel(RowMap m, const int2 *__r
     for (int h = blockIdx.x; h < nh; h += gridDim.x) {
         const int v = m.heavy[h];
         int a = INT_MAX, b = INT_MIN;
-        for (int e = m.rp[v] + threadIdx.x; e < m.rp[v + 1]; e += blockDim.x) {
+        row_each(m.rp[v], m.rp[v + 1], threadIdx.x, blockDim.x, [&](uint32_t e) {
             const int p = bint[m.col[e]].x;
             a = min(a, p);
             b = max(b, p);
-        }
+        });
         for (int d = kWave / 2; d > 0; d >>= 1) {
             a = min(a, __shfl_xor(a, d, kWave));
             b = max(b, __shfl_xor(b, d, kWave));
@@ -139,11 +139,11 @@ __global__ __launch_bounds__(256) void bc_local_kernel(RowMap m, const int2 *__r
         const bool light = ok && (r1 - r0 <= m.heavy_thresh);
         int a = INT_MAX, b = INT_MIN;
         if (light)
-            for (int e = r0 + l; e < r1; e += G) {
+            row_each(r0, r1, l, G, [&](uint32_t e) {
                 const int p = bint[m.col[e]].x;
                 a = min(a, p);
                 b = max(b, p);
-            }
+            });
 #pragma unroll
         for (int d = G / 2; d > 0; d >>= 1) {
             a = min(a, __shfl_xor(a, d, G));
@@ -226,7 +226,7 @@ __global__ __launch_bounds__(256) void bc_union_kernel(RowMap m, int u, const in
     const int nh = *m.nheavy;
     for (int h = blockIdx.x; h < nh; h += gridDim.x) {
         const int a = m.heavy[h];
-        for (int e = m.rp[a] + threadIdx.x; e < m.rp[a + 1]; e += blockDim.x) entry(a, m.col[e]);
+        row_each(m.rp[a], m.rp[a + 1], threadIdx.x, blockDim.x, [&](uint32_t e) { entry(a, m.col[e]); });
     }
     const int rows_per_tile = 256 / G;
     const int g = threadIdx.x / G, l = threadIdx.x % G;
@@ -235,7 +235,7 @@ __global__ __launch_bounds__(256) void bc_union_kernel(RowMap m, int u, const in
         if (a >= m.n) continue;
         const int r0 = m.rp[a], r1 = m.rp[a + 1];
         if (r1 - r0 > m.heavy_thresh) continue;
-        for (int e = r0 + l; e < r1; e += G) entry(a, m.col[e]);
+        row_each(r0, r1, l, G, [&](uint32_t e) { entry(a, m.col[e]); });
     }
 }
 
@@ -331,9 +331,9 @@ __global__ __launch_bounds__(64) void bc_columns_kernel(int n, int u, const int 
     const int lane = threadIdx.x;
     for (int a = blockIdx.x; a < n; a += gridDim.x) {
         const int r0 = rp[a], r1 = rp[a + 1];
-        for (int base = r0; base < r1; base += kWave) {
-            const int e = base + lane;
-            const bool act = e < r1;
+        row_each(r0, r1, 0, kWave, [&](uint32_t base) {
+            const uint32_t e = base + lane;
+            const bool act = e < (uint32_t)r1;
             int key = -1, target = 0;
             if (act) {
                 const int blk = eblk[e], b = col[e];
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(64) void bc_columns_kernel(int n, int u, const int 
             if (act && leader == lane) start = atomicAdd(&cursor[key], cnt);
             start = __shfl(start, leader, kWave);
             if (act) cols[rps[key] + start + rank] = target;
-        }
+        });
     }
 }
 

@@ -105,6 +105,35 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
 // row's end by up to a stride, so it counts in unsigned slots: a row that ends just below 2^31 does
 // not wrap.  (Host code too: the tests walk such rows on the CPU.)
 
+// f(slot) for the slots lo + first, lo + first + step, ... below hi
+template <typename F>
+__host__ __device__ __forceinline__ void row_each(int lo, int hi, uint32_t first, uint32_t step, F f) {
+    const uint32_t end = (uint32_t)hi;
+    for (uint32_t e = (uint32_t)lo + first; e < end; e += step) f(e);
+}
+
+// run = the sum of w[lo .. hi) from left to right, cw[e] the sums up to each entry
+__host__ __device__ __forceinline__ double row_running_sums(const double *__restrict__ w, double *__restrict__ cw,
+                                                            int lo, int hi) {
+    double run = 0.0;
+    int e = lo;
+    for (; hi - e >= 8; e += 8) {  // eight loads in flight, the additions still in order
+        double wv[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) wv[k] = w[e + k];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            run += wv[k];
+            cw[e + k] = run;
+        }
+    }
+    for (; e < hi; ++e) {
+        run += w[e];
+        cw[e] = run;
+    }
+    return run;
+}
+
 // acc + sum of the entries lo + first, lo + first + step, ... below hi, in that order, U loads at a
 // time; weighted entries with w
 template <typename T, int U>

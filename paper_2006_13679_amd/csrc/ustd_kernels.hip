@@ -133,19 +133,20 @@ __global__ __launch_bounds__(256) void bfs_level_kernel(RowMap m, int d, int *__
                                                         const int *__restrict__ prev) {
     if (prev && *prev == 0) return;  // uniform over the grid
     int any = 0;
+    auto offer = [&](int v, uint32_t e) {
+        const int y = m.col[e];
+        const int dy = dist[y];
+        if (dy > d) {
+            atomicMin(&parB[y], v);
+            if (dy != d + 1) dist[y] = d + 1;
+            any = 1;
+        }
+    };
     const int nh = *m.nheavy;
     for (int h = blockIdx.x; h < nh; h += gridDim.x) {
         const int v = m.heavy[h];
         if (dist[v] != d) continue;  // uniform in the block
-        for (int e = m.rp[v] + threadIdx.x; e < m.rp[v + 1]; e += blockDim.x) {
-            const int y = m.col[e];
-            const int dy = dist[y];
-            if (dy > d) {
-                atomicMin(&parB[y], v);
-                if (dy != d + 1) dist[y] = d + 1;
-                any = 1;
-            }
-        }
+        row_each(m.rp[v], m.rp[v + 1], threadIdx.x, blockDim.x, [&](uint32_t e) { offer(v, e); });
     }
     const int rows_per_tile = 256 / G;
     const int g = threadIdx.x / G, l = threadIdx.x % G;
@@ -154,15 +155,7 @@ __global__ __launch_bounds__(256) void bfs_level_kernel(RowMap m, int d, int *__
         if (v >= m.n || dist[v] != d) continue;
         const int lo = m.rp[v], hi = m.rp[v + 1];
         if (hi - lo > m.heavy_thresh) continue;
-        for (int e = lo + l; e < hi; e += G) {
-            const int y = m.col[e];
-            const int dy = dist[y];
-            if (dy > d) {
-                atomicMin(&parB[y], v);
-                if (dy != d + 1) dist[y] = d + 1;
-                any = 1;
-            }
-        }
+        row_each(lo, hi, l, G, [&](uint32_t e) { offer(v, e); });
     }
     if (__any(any) && lane_id() == 0) atomicOr(found, 1);
 }
@@ -1991,25 +1984,9 @@ __global__ __launch_bounds__(256) void row_cumsum_kernel(int n, const int *__res
                                                          int heavy_thresh, double *__restrict__ cw,
                                                          double *__restrict__ wdeg) {
     for (int v = blockIdx.x * blockDim.x + threadIdx.x; v < n; v += gridDim.x * blockDim.x) {
-        double run = 0.0;
-        int e = rp[v];
-        const int end = rp[v + 1];
-        if (end - e > heavy_thresh) continue;
-        for (; e + 8 <= end; e += 8) {  // eight loads in flight, the additions still in order
-            double wv[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) wv[k] = w[e + k];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                run += wv[k];
-                cw[e + k] = run;
-            }
-        }
-        for (; e < end; ++e) {
-            run += w[e];
-            cw[e] = run;
-        }
-        wdeg[v] = run;
+        const int lo = rp[v], end = rp[v + 1];
+        if (end - lo > heavy_thresh) continue;
+        wdeg[v] = row_running_sums(w, cw, lo, end);
     }
 }
 
@@ -2025,11 +2002,13 @@ __global__ __launch_bounds__(64) void row_cumsum_heavy_kernel(const int *__restr
         const int v = heavy[h];
         const int r0 = rp[v], end = rp[v + 1];
         double run = 0.0;
-        double wn = r0 + lane < end ? w[r0 + lane] : 0.0;
-        for (int base = r0; base < end; base += kWave) {
+        const uint32_t rend = (uint32_t)end;
+        auto chunk = [&](uint32_t base) { return base + lane < rend ? w[base + lane] : 0.0; };
+        double wn = chunk((uint32_t)r0);
+        row_each(r0, end, 0, kWave, [&](uint32_t base) {
             const double wc = wn;
-            wn = base + kWave + lane < end ? w[base + kWave + lane] : 0.0;
-            const int cnt = min(kWave, end - base);
+            wn = chunk(base + kWave);
+            const int cnt = (int)min((uint32_t)kWave, rend - base);
             const long long bits = __double_as_longlong(wc);
             const int lo = (int)(bits & 0xFFFFFFFFll), hi = (int)(bits >> 32);
             double mine = 0.0;
@@ -2040,7 +2019,7 @@ __global__ __launch_bounds__(64) void row_cumsum_heavy_kernel(const int *__restr
                 if (lane == k) mine = run;
             }
             if (lane < cnt) cw[base + lane] = mine;
-        }
+        });
         if (lane == 0) wdeg[v] = run;
     }
 }
@@ -2050,7 +2029,8 @@ __global__ __launch_bounds__(64) void row_cumsum_heavy_kernel(const int *__restr
 // smallest word of bucket i.  The row is found by a binary search over the row pointers.
 __global__ __launch_bounds__(256) void step_guide_kernel(int n, int nnz, const int *__restrict__ rp,
                                                          const double *__restrict__ cw, int *__restrict__ guide) {
-    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nnz; e += gridDim.x * blockDim.x) {
+    row_each(0, nnz, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x, [&](uint32_t slot) {
+        const int e = (int)slot;
         int lo = 0, hi = n - 1;  // the last v with rp[v] <= e
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
@@ -2067,7 +2047,7 @@ __global__ __launch_bounds__(256) void step_guide_kernel(int n, int nnz, const i
             else a = mid + 1;
         }
         guide[e] = a;
-    }
+    });
 }
 
 // position of x in the ascending row [lo, hi), or -1

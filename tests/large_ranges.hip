@@ -65,9 +65,48 @@ void row_sums() {
     for (uint32_t g : {4u, 8u, 16u, 32u}) sums<4>(col, w, p, g);  // light rows
 }
 
+// every slot of a row that ends at the largest slot once, by threads in strides; a grid of threads over
+// all slots
+void row_loops() {
+    for (uint32_t step : {4u, 64u, 256u, 1024u})
+        for (long long len : {1ll, 63ll, 64ll, 65ll, 255ll, 257ll, 3000ll}) {
+            const long long lo = kEnd - len;
+            std::vector<int> seen(len, 0);
+            for (uint32_t t = 0; t < step; ++t)
+                row_each((int)lo, (int)kEnd, t, step, [&](uint32_t e) {
+                    check((long long)e >= lo && (long long)e < kEnd, "row_each slot", e, len);
+                    ++seen[(long long)e - lo];
+                });
+            for (long long i = 0; i < len; ++i) check(seen[i] == 1, "row_each count", i, len);
+        }
+    const uint32_t grid = 8192u * 256u;
+    for (uint32_t first : {0u, 1u, grid - 2, grid - 1}) {
+        long long count = 0, want = (kEnd - first + grid - 1) / grid;
+        row_each(0, (int)kEnd, first, grid, [&](uint32_t e) {
+            check((long long)e < kEnd && e % grid == first, "grid slot", e, first);
+            check(++count <= want, "grid count", count, first);
+        });
+        check(count == want, "grid count", count, first);
+    }
+}
+
+// running sums of a weighted row that ends at the largest slot
+void running_sums() {
+    double *w = reserve<double>(), *cw = reserve<double>();
+    for (long long e = kEnd - kRow; e < kEnd; ++e) w[e] = 1.0 + 1.0 / (double)(e % 97 + 1);
+    for (long long len : {1ll, 7ll, 8ll, 9ll, 15ll, 16ll, 1024ll}) {
+        double want = 0;
+        const double run = row_running_sums(w, cw, (int)(kEnd - len), (int)kEnd);
+        for (long long e = kEnd - len; e < kEnd; ++e) check(cw[e] == (want += w[e]), "running sum", e, len);
+        check(run == want, "row total", 0, len);
+    }
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
+    else if (!strcmp(what, "row_loops")) row_loops();
+    else if (!strcmp(what, "running_sums")) running_sums();
     else return 2;
     puts("ok");
     return 0;
