@@ -105,6 +105,31 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
 // row's end by up to a stride, so it counts in unsigned slots: a row that ends just below 2^31 does
 // not wrap.  (Host code too: the tests walk such rows on the CPU.)
 
+// The sum of two slots takes 32 bits unsigned (rows behind slot 2^30).
+__host__ __device__ __forceinline__ int mid_slot(int lo, int hi) { return (int)(((uint32_t)lo + (uint32_t)hi) >> 1); }
+
+// first slot of the ascending row [lo, hi) whose column is x or above (hi: none)
+__host__ __device__ __forceinline__ int row_lower_bound(const int *__restrict__ col, int lo, int hi, int x) {
+    while (lo < hi) {
+        const int mid = mid_slot(lo, hi);
+        if (col[mid] < x) lo = mid + 1;
+        else hi = mid;
+    }
+    return lo;
+}
+
+// slot of x in the ascending row [lo, hi), or -1
+__host__ __device__ __forceinline__ int find_in_row(const int *__restrict__ col, int lo, int hi, int x) {
+    while (lo < hi) {
+        const int mid = mid_slot(lo, hi);
+        const int c = col[mid];
+        if (c == x) return mid;
+        if (c < x) lo = mid + 1;
+        else hi = mid;
+    }
+    return -1;
+}
+
 // f(slot) for the slots lo + first, lo + first + step, ... below hi
 template <typename F>
 __host__ __device__ __forceinline__ void row_each(int lo, int hi, uint32_t first, uint32_t step, F f) {

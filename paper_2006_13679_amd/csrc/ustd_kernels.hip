@@ -1879,13 +1879,7 @@ __global__ __launch_bounds__(256) void edge_count_kernel(EdgeCountArgs a) {
     int c = 0;
     for (int t = t0; t < t1; ++t) {
         const int p = a.rec[(2ll * t + 1) * a.rec_stride + v];
-        int lo = a.rp[v], hi = a.rp[v + 1];
-        const int end = hi;
-        while (lo < hi) {
-            const int mid = (lo + hi) >> 1;
-            if (a.col[mid] < p) lo = mid + 1;
-            else hi = mid;
-        }
+        const int end = a.rp[v + 1], lo = row_lower_bound(a.col, a.rp[v], end, p);
         if (lo == end || a.col[lo] != p) continue;  // not a neighbour: never for a sampled tree
         if (lo == cur) {
             ++c;
@@ -1916,13 +1910,7 @@ __global__ __launch_bounds__(256) void edge_fold_kernel(int n, long long nnz, co
     }
     const int a = lo, b = col[e];
     if (b >= a) return;
-    int l = rp[b], h = rp[b + 1];
-    const int end = h;
-    while (l < h) {
-        const int mid = (l + h) >> 1;
-        if (col[mid] < a) l = mid + 1;
-        else h = mid;
-    }
+    const int end = rp[b + 1], l = row_lower_bound(col, rp[b], end, a);
     if (l == end || col[l] != a) return;  // asymmetric input: left where it is
     atomicAdd((unsigned long long *)&counts[l], (unsigned long long)c);
     counts[e] = 0;
@@ -2048,18 +2036,6 @@ __global__ __launch_bounds__(256) void step_guide_kernel(int n, int nnz, const i
         }
         guide[e] = a;
     });
-}
-
-// position of x in the ascending row [lo, hi), or -1
-__device__ __forceinline__ int find_in_row(const int *__restrict__ col, int lo, int hi, int x) {
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        const int c = col[mid];
-        if (c == x) return mid;
-        if (c < x) lo = mid + 1;
-        else hi = mid;
-    }
-    return -1;
 }
 
 // err |= 64 if a conductance is not positive and finite or differs from its mirror entry

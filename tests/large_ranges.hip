@@ -102,11 +102,27 @@ void running_sums() {
     }
 }
 
+// every column of an ascending row that ends at the largest slot, and columns it does not hold
+void row_searches() {
+    int *col = reserve<int>();
+    for (long long e = kEnd - kRow; e < kEnd; ++e) col[e] = (int)(2 * (e - (kEnd - kRow)) + 5);
+    for (long long len : {1ll, 2ll, 3ll, 100ll, kRow}) {
+        const int lo = (int)(kEnd - len), hi = (int)kEnd;
+        for (long long e = lo; e < kEnd; ++e) {
+            check(find_in_row(col, lo, hi, col[e]) == e, "find_in_row", e, len);
+            check(row_lower_bound(col, lo, hi, col[e]) == e, "row_lower_bound", e, len);
+            check(find_in_row(col, lo, hi, col[e] + 1) == -1, "find_in_row absent", e, len);
+            check(row_lower_bound(col, lo, hi, col[e] + 1) == (int)(e + 1), "row_lower_bound absent", e, len);
+        }
+    }
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
     else if (!strcmp(what, "row_loops")) row_loops();
     else if (!strcmp(what, "running_sums")) running_sums();
+    else if (!strcmp(what, "row_searches")) row_searches();
     else return 2;
     puts("ok");
     return 0;
