@@ -1940,8 +1940,31 @@ int static_scratch(void **out) {
     return USTD_OK;
 }
 
+// the plan of the most trees per batch (at most kMaxTreesPerBatch) that fit the static scratch; false:
+// not one tree fits (*L: the plan of one)
+bool most_static_trees(ustd_problem *q, bool hops, Plan *L) {
+    auto fits = [&](int trees) {
+        q->trees_per_batch = trees;
+        *L = make_plan(q, true, false, hops);
+        return (size_t)L->total <= kStaticScratchBytes;
+    };
+    if (!fits(1)) return false;
+    int lo = 1, hi = kMaxTreesPerBatch;
+    while (lo < hi) {
+        const int mid = lo + (hi - lo + 1) / 2;
+        if (fits(mid)) lo = mid;
+        else hi = mid - 1;
+    }
+    return fits(lo);
+}
+
 // the problem as the allocation-free entry point runs it: the one-workgroup solve engine and
-// the most trees per batch (at most kMaxTreesPerBatch) whose workspace fits the static scratch
+// the most trees per batch.  The rows per slot of the lone walks take room from the trees, and with
+// fewer trees than SIMDs a batch costs its slowest tree, so they are kept only where they leave nine
+// trees in ten.  With them against without, ms of a call: grid 128 x 128 163 and 207 (249 and 251
+// trees), 360 x 360 1086 and 1244 (40 and 44), hyperbolic graphs at 0.92 and 0.82 of the trees even;
+// below, they lose what their batches cost: circulant of 40,000 vertices and 5.5 million entries 753
+// and 176 (15 and 114 trees), R-MAT 16 of 4.1 million entries 42 and 24 (34 and 93).
 int fit_static(const ustd_problem *prob, ustd_problem *q, Plan *L) {
     *q = *prob;
     q->solve_engine = USTD_ENGINE_WORKGROUP;
@@ -1953,25 +1976,15 @@ int fit_static(const ustd_problem *prob, ustd_problem *q, Plan *L) {
                                      "scratch holds %zu", L->total, prob->trees_per_batch, kStaticScratchBytes);
         return USTD_OK;
     }
-    q->trees_per_batch = 1;
-    bool hops = true;
-    *L = make_plan(q);
-    if ((size_t)L->total > kStaticScratchBytes) {
-        hops = false;
-        *L = make_plan(q, true, false, false);
-    }
-    if ((size_t)L->total > kStaticScratchBytes)
+    if (!most_static_trees(q, false, L))
         return fail(USTD_ENOMEM, "the problem needs %lld bytes of scratch even at one tree per batch; the static "
                                  "scratch holds %zu", L->total, kStaticScratchBytes);
-    int lo = 1, hi = kMaxTreesPerBatch;  // largest K whose plan fits
-    while (lo < hi) {
-        const int mid = lo + (hi - lo + 1) / 2;
-        q->trees_per_batch = mid;
-        if ((size_t)make_plan(q, true, false, hops).total <= kStaticScratchBytes) lo = mid;
-        else hi = mid - 1;
+    ustd_problem qh = *q;
+    Plan Lh;
+    if (most_static_trees(&qh, true, &Lh) && 10ll * Lh.K >= 9ll * L->K) {
+        *q = qh;
+        *L = Lh;
     }
-    q->trees_per_batch = lo;
-    *L = make_plan(q, true, false, hops);
     return USTD_OK;
 }
 
