@@ -101,6 +101,34 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
     return block_sum_t<T>(v, sh, (int)blockDim.x);
 }
 
+// Walk steps and draws of a tree, counted by the lanes of its wave.  A lane's own counters have 32 bits:
+//   steps: of the walks it commits in batches, at most kBatchSteps a start, and a tree has fewer than
+//   2^30 starts;
+//   draws: at most kWalkDraws a start it walks, moved to the wave's counter once every kDrawWindow
+//   starts of the tree (another kDrawWindow bounds the starts then in flight).
+// What the whole wave commits (longer walks, any number of steps) goes to the wave's 64-bit counters.
+struct WalkCounts {
+    static constexpr unsigned kBatchSteps = 4, kWalkDraws = 250, kDrawWindow = 1u << 22;
+    static_assert((1ull << 30) * kBatchSteps <= 1ull << 32, "a lane's steps fit (fewer than 2^30 starts)");
+    static_assert(2ull * kDrawWindow * kWalkDraws < 1ull << 32, "a lane's draws between two moves fit");
+    uint32_t steps = 0u, draws = 0u;
+    long long wave_steps = 0, wave_draws = 0;  // uniform
+    __host__ __device__ __forceinline__ void batch_walk(int k) { steps += (uint32_t)k; }
+    __host__ __device__ __forceinline__ void draw() { ++draws; }
+    __host__ __device__ __forceinline__ void wave_walk(long long k, long long drawn = 0) {
+        wave_steps += k;
+        wave_draws += drawn;
+    }
+    __host__ __device__ __forceinline__ static bool move_due(int start) {
+        return start != 0 && (start & (int)(kDrawWindow - 1)) == 0;
+    }
+    // all: the sum of the lanes' draws
+    __host__ __device__ __forceinline__ void move_draws(long long all) {
+        wave_draws += all;
+        draws = 0u;
+    }
+};
+
 // ---- CSR rows.  Slots are below 2^31 (nnz < 2^31), and a loop over a row in strides looks past the
 // row's end by up to a stride, so it counts in unsigned slots: a row that ends just below 2^31 does
 // not wrap.  (Host code too: the tests walk such rows on the CPU.)

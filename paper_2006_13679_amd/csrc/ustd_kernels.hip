@@ -248,6 +248,7 @@ template <bool LDS>
 constexpr int rob_cap() { return LDS ? kSamplerRobLds : kSamplerRobMax; }
 constexpr int kPathLds = 4;    // recorded steps kept in LDS per entry (x_1..x_4)
 constexpr int kPath = 250;     // recorded steps per speculative walk (x_1..x_250)
+static_assert(kPathLds <= (int)WalkCounts::kBatchSteps && kPath <= (int)WalkCounts::kWalkDraws, "the counters' bounds");
 static_assert(kPath - kPathLds == kSamplerPathGlobal, "path split");
 // reorder-buffer entry states (a byte) besides a finished walk's step count (<= kPath; 0: the
 // start was absorbed, nothing to commit):
@@ -406,7 +407,7 @@ static_assert(kStamps == 1024, "the hash gives ten bits");
 // last start is taken, well within 2^15 rounds (a walk takes at most kPath steps, a window's starts
 // pass through the reorder buffer in a few lifetimes of one), so a later stamp is never taken for an
 // earlier one; an older stamp that looks later costs a load.
-__device__ __forceinline__ bool since(uint16_t stamp, int r) { return (int16_t)(uint16_t)(stamp - r) >= 0; }
+__device__ __forceinline__ bool since(uint16_t stamp, uint32_t r) { return (int16_t)(uint16_t)(stamp - r) >= 0; }
 
 // Neighbour index (0 .. deg-1) of a walk step with word w from the row [r0, r1).  Unit
 // weights: floor(w deg / 2^32).  Weighted (Section "Generalizations"): the first j with
@@ -575,7 +576,7 @@ __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, con
 // written with a placeholder and completed by lane 0 then.
 template <bool LDS, typename Next>
 __device__ void retrace(const TreeState<LDS> &bits, const Next &next, int *nbw, int *par, const int *__restrict__ bflag, int u,
-                        int s0, int *buf, uint16_t *stamps, int round) {
+                        int s0, int *buf, uint16_t *stamps, uint32_t round) {
     constexpr int kPiece = 2 * kHashSlots;
     const int lane = threadIdx.x;
     int z = s0, pend = -1;  // pend: first vertex whose nba is not known yet
@@ -763,14 +764,13 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
 
     int head = 0, tail = 0;               // wave-uniform
     int wend = 0, wpos = 0, wcnt = 0;     // the window is [wend - kWin, wend); list position and length
-    int wround = 0, shi = -1;             // the round that read the window; the last start taken
+    uint32_t wround = 0;                  // the round that read the window
+    int shi = -1;                         // the last start taken
     int mode = 0;                         // 0 idle, 1 speculative walk
     int my_e = 0, x = 0, s = 0, bkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
     uint4 ph = make_uint4(0, 0, 0, 0);
     int4 vx = make_int4(0, 0, 0, 0);  // tree state in the records: x's entry {row begin, row end, B_u flag, 0}
-    // steps and draws of this lane (a tree has fewer rounds than 2^30) and of the one-lane walks
-    uint32_t steps = 0u, draws = 0u;
-    long long wsteps = 0, wdraws = 0;
+    WalkCounts walked;
 
     // whether a vertex's parent is written, given the edge bits of its tree edge in the low two
     // bits: always, or where Algorithm 2 may read it (marked by a backward edge)
@@ -789,7 +789,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         wave_sync();
     };
 
-    for (int round = 0;; ++round) {
+    for (uint32_t round = 0;; ++round) {  // used modulo 2^16 (a large tree takes more than 2^31)
         if constexpr (!LDS) {  // walks whose start has been absorbed end (before their slot is given away)
             if (mode == 1 && rob_k[my_e & robm] == 0) mode = 0;
         }
@@ -805,10 +805,15 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         if (want > 0 && (4 * want >= min(rob, kWave) || (round & 3) == 0 || head == tail) && (wpos < wcnt || wend < n)) {
             const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(idle >> 32),
                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)idle, 0u));
-            int got = 0, mys = 0, myr = 0;  // myr: the round that read the window of mys
+            int got = 0, mys = 0;
+            uint32_t myr = 0;  // the round that read the window of mys
             do {
                 if (wpos == wcnt) {
                     if (wend >= n) break;
+                    if constexpr (!LDS) {  // never due on a graph within the bitmap
+                        if (WalkCounts::move_due(wend))
+                            walked.move_draws(uniform_ll((long long)wave_sum((unsigned long long)walked.draws)));
+                    }
                     uint32_t fb = bits.free4(wend, lane, n);
                     const int left = n - (wend + 4 * lane);
                     if (left < 4) fb &= left > 0 ? (1u << left) - 1u : 0u;
@@ -899,7 +904,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
             consume(fy, cvy, ny0, ny1);  // no load may stay in flight into the commit phase
             if (in) cvy = cv_of(y, cvy);
             ++k;
-            ++draws;
+            walked.draw();
             const int eb = edge_bits(x, fx, y, fy);
             if (k <= kPathLds) {
                 rob_p[sl].v[k - 1] = (CT)y;
@@ -955,7 +960,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                         vertex_at(nbw, s0) = carry | (int)((unsigned)pb << 30);
                         if (keeps_parent(pb)) vertex_at(par, s0) = x1;
                         bits.set(s0);
-                        ++steps;
+                        walked.batch_walk(1);
                     }
                     head += r;
                     wave_sync();
@@ -1057,7 +1062,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     if (any3) put(2, x2);
                     put(1, x1);
                     put(0, s0);
-                    steps += istar;
+                    walked.batch_walk(istar);
                 }
                 head += jstar;
                 wave_sync();
@@ -1134,7 +1139,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     bits.set(xv);
                     if constexpr (!LDS) stamps[stamp_slot(xv)] = (uint16_t)round;
                 }
-                if (lane == 0) steps += istar;
+                walked.wave_walk(istar);
                 ++head;
                 wave_sync();
                 if constexpr (!LDS) {
@@ -1189,8 +1194,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                                                                 g.key1);
                 retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
-                wsteps += kk;
-                wdraws += kk - k0;
+                walked.wave_walk(kk, kk - k0);
                 ++head;
                 wave_sync();
                 if constexpr (!LDS) remark();
@@ -1296,7 +1300,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     if (m) carry = __builtin_amdgcn_readlane(xv[c], __builtin_ctzll(m));
                 }
             }
-            if (lane == 0) steps += istar;
+            walked.wave_walk(istar);
             ++head;
             wave_sync();
             if constexpr (!LDS) {
@@ -1305,8 +1309,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         }
     }
 
-    const long long sum_steps = wsteps + (long long)wave_sum((unsigned long long)steps);
-    const long long sum_draws = wdraws + (long long)wave_sum((unsigned long long)draws);
+    const long long sum_steps = walked.wave_steps + (long long)wave_sum((unsigned long long)walked.steps);
+    const long long sum_draws = walked.wave_draws + (long long)wave_sum((unsigned long long)walked.draws);
     if (lane == 0) {
         if (a.steps) a.steps[tile] = sum_steps;
         if (a.draws) a.draws[tile] = sum_draws;

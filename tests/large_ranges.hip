@@ -117,12 +117,32 @@ void row_searches() {
     }
 }
 
+// walk counts of a tree past 2^32 steps: long commits, batch commits of one lane, draws of one lane
+void walk_counts() {
+    WalkCounts c;
+    const long long longs = 20000000;
+    for (long long i = 0; i < longs; ++i) c.wave_walk(250);
+    check(c.wave_steps + c.steps == 250 * longs, "long commits", c.wave_steps, c.steps);
+    const long long starts = (1ll << 30) - 3;  // the largest tree, every batch walk by one lane
+    for (long long i = 0; i < starts; ++i) c.batch_walk(4);
+    check(c.wave_steps + c.steps == 250 * longs + 4 * starts, "batch commits", c.wave_steps, c.steps);
+    long long draws = 0;
+    for (int w = 0; w < 1 << 25; w += 256) {  // a window of starts, each walked to its last recorded step
+        if (WalkCounts::move_due(w)) c.move_draws(c.draws);
+        for (int k = 0; k < 256 * 250; ++k, ++draws) c.draw();
+    }
+    c.wave_walk(1ll << 33, (1ll << 33) - 250);
+    check(c.wave_draws + c.draws == draws + (1ll << 33) - 250, "draws", c.wave_draws, c.draws);
+    check(c.wave_steps + c.steps == 250 * longs + 4 * starts + (1ll << 33), "lone walk", c.wave_steps, c.steps);
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
     else if (!strcmp(what, "row_loops")) row_loops();
     else if (!strcmp(what, "running_sums")) running_sums();
     else if (!strcmp(what, "row_searches")) row_searches();
+    else if (!strcmp(what, "walk_counts")) walk_counts();
     else return 2;
     puts("ok");
     return 0;

@@ -1,5 +1,5 @@
 """Functions of the kernels at the largest sizes the API accepts (rows that end just below 2^31
-slots), compiled for the host and run on the CPU (large_ranges.hip)."""
+slots, trees of more than 2^32 steps), compiled for the host and run on the CPU (large_ranges.hip)."""
 import os
 import subprocess
 
@@ -18,7 +18,7 @@ def driver(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("what", ["row_sums", "row_loops", "running_sums", "row_searches"])
+@pytest.mark.parametrize("what", ["row_sums", "row_loops", "running_sums", "row_searches", "walk_counts"])
 def test_on_the_host(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
