@@ -129,6 +129,17 @@ struct WalkCounts {
     }
 };
 
+// Threads at work in the one-workgroup solve.  Where the rows' lane groups fill less than the
+// workgroup, four waves do the work and the others leave at once (a barrier counts the waves that
+// are left): an iteration is a chain of a dozen barriers, which cost less among four (column of a
+// 13 x 11 grid 306 us against 333, 8 x 8 grid 267 against 279).  Beyond that the product grows by more than the barriers save: 20 x 30 grid 1643 us
+// against 1109, R-MAT scale 10 1709 against 764.  The choice depends on the graph alone, so a batch
+// member's solve is that of a single call.
+constexpr int kSmallThreads = 1024, kFewThreads = 256;
+__host__ __device__ __forceinline__ int small_solve_threads(int n, int G) {
+    return (long long)n * G < kSmallThreads ? kFewThreads : kSmallThreads;
+}
+
 // ---- CSR rows.  Slots are below 2^31 (nnz < 2^31), and a loop over a row in strides looks past the
 // row's end by up to a stride, so it counts in unsigned slots: a row that ends just below 2^31 does
 // not wrap.  (Host code too: the tests walk such rows on the CPU.)

@@ -23,7 +23,6 @@
 
 namespace ustd {
 
-constexpr int kSmallThreads = 1024;
 // blocks of the multi-kernel engine: at most one resident set (8 per compute unit), since every
 // block adds a ticket and a partial result to its kernel's tail
 constexpr int kSolveGrid = 2048;
@@ -399,19 +398,11 @@ __global__ __launch_bounds__(256) void solve_direction_kernel(SolveArgs<T> a) {
 // reliable updates and end rule, with no kernel boundary or host poll between iterations.
 // Ends with the scalars the multi-kernel path leaves.
 // ---------------------------------------------------------------------------------------
-// Where the rows' lane groups fill less than the workgroup, four waves do the work and the others
-// leave at once (a barrier counts the waves that are left): an iteration is a chain of a dozen
-// barriers, which cost less among four (column of a 13 x 11 grid 306 us against 333, 8 x 8 grid 267
-// against 279).  Beyond that the product grows by more than the barriers save: 20 x 30 grid 1643 us
-// against 1109, R-MAT scale 10 1709 against 764.  The choice depends on the graph alone, so a batch
-// member's solve is that of a single call.
-constexpr int kFewThreads = 256;
-
 template <typename T, int G>
 __device__ void solve_small_body(const SolveArgs<T> &a, const RowMap &m, double tol2, double delta2, int maxit,
                                  double *sh) {
     const int n = a.n, tid = threadIdx.x, u = a.u;
-    const int nt = n * G < kSmallThreads ? kFewThreads : kSmallThreads;
+    const int nt = small_solve_threads(n, G);
     if (tid >= nt) return;
     const double inv_n = 1.0 / (double)n;
     double rz = 0.0, rr = 0.0, bb = 0.0;

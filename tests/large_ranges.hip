@@ -22,8 +22,9 @@ constexpr int kVerts = 1000;
 template <typename T>
 T *reserve() {
     const size_t half = sizeof(T) << 31;
-    char *m = static_cast<char *>(mmap(nullptr, 2 * half, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0));
-    if (m == MAP_FAILED) exit(2);
+    void *map = mmap(nullptr, 2 * half, PROT_NONE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
+    if (map == MAP_FAILED) exit(2);
+    char *m = static_cast<char *>(map);
     T *base = reinterpret_cast<T *>(m + half);
     const size_t page = 4096, lo = (size_t)(kEnd - kRow) * sizeof(T) / page * page;
     if (mprotect(reinterpret_cast<char *>(base) + lo, half - lo, PROT_READ | PROT_WRITE) != 0) exit(2);
@@ -136,6 +137,13 @@ void walk_counts() {
     check(c.wave_steps + c.steps == 250 * longs + 4 * starts + (1ll << 33), "lone walk", c.wave_steps, c.steps);
 }
 
+// the one-workgroup solve takes the whole workgroup from one workgroup of row lanes on, at any size
+void solve_threads() {
+    for (int G : {4, 8, 16, 32})
+        for (long long n : {2ll, 1024ll / G - 1, 1024ll / G, 16384ll, 1ll << 26, 1ll << 27, 1ll << 28, 1ll << 29})
+            check(small_solve_threads((int)n, G) == (n * G < 1024 ? 256 : 1024), "solve threads", n, G);
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
@@ -143,6 +151,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(what, "running_sums")) running_sums();
     else if (!strcmp(what, "row_searches")) row_searches();
     else if (!strcmp(what, "walk_counts")) walk_counts();
+    else if (!strcmp(what, "solve_threads")) solve_threads();
     else return 2;
     puts("ok");
     return 0;

@@ -12,13 +12,15 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
+    # -fwrapv: an int that overflows wraps, as it does in the kernels' registers
     exe = str(tmp_path_factory.mktemp("large_ranges") / "driver")
-    subprocess.check_call([build.hipcc(), "--offload-host-only", "-O2", "-std=c++17", "-I", build.CSRC,
-                           os.path.join(HERE, "large_ranges.hip"), "-o", exe])
+    subprocess.check_call([build.hipcc(), "--offload-host-only", "-O2", "-fwrapv", "-std=c++17", "-I",
+                           build.CSRC, os.path.join(HERE, "large_ranges.hip"), "-o", exe])
     return exe
 
 
-@pytest.mark.parametrize("what", ["row_sums", "row_loops", "running_sums", "row_searches", "walk_counts"])
+@pytest.mark.parametrize("what", ["row_sums", "row_loops", "running_sums", "row_searches", "walk_counts",
+                                  "solve_threads"])
 def test_on_the_host(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
