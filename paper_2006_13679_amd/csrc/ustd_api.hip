@@ -1070,11 +1070,9 @@ bool one_workgroup(const ustd_problem *p, int n, bool batch) {
 
 // PCG with reliable updates on the vectors of type T, in one workgroup or by iteration kernels.
 // The slots (an iteration, or the second half of a reliable update: at most two per iteration) are
-// enqueued in chunks of 8, 16, ... 64, each followed by an asynchronous copy of the scalars into
-// pinned memory; the host stays one chunk ahead and stops enqueueing once a copied `done` is
-// set, so the device never waits for the host (64 slots take it a millisecond or more; longer
-// chunks leave more empty slots behind the end).  Leaves x (not yet projected) and the final
-// scalars in *out.
+// enqueued in chunks (solve_chunk_after), each followed by an asynchronous copy of the scalars into
+// pinned memory; the host stays one chunk ahead and stops enqueueing once a copied `done` is set, so
+// the device does not wait for the host.  Leaves x (not yet projected) and the final scalars in *out.
 template <typename T>
 int solve_iterate(Ctx &c, double *x, double tol2, int maxit, SolveScalars *out) {
     const SolveArgs<T> a = solve_args<T>(c, c.ws, c.L, x);
@@ -1089,12 +1087,12 @@ int solve_iterate(Ctx &c, double *x, double tol2, int maxit, SolveScalars *out) 
         HIP_TRY(launch_solve_start<T>(a, tol2, delta2, maxit, c.st));
         const long long slots = 2ll * maxit + 2;
         long long launched = 0;
-        int chunk = 8, k = 0;
+        int chunk = kSolveChunkFirst, k = 0;
         for (;;) {
             const long long todo = std::min<long long>(chunk, slots - launched);
             for (long long i = 0; i < todo; ++i) HIP_TRY(launch_solve_slot<T>(a, c.rows, c.L.G, c.st));
             launched += todo;
-            chunk = std::min(2 * chunk, 64);
+            chunk = solve_chunk_after(chunk);
             HIP_TRY(hipMemcpyAsync(&hs[k & 1], a.sc, sizeof(SolveScalars), hipMemcpyDeviceToHost, c.st));
             HIP_TRY(hipEventRecord(ev[k & 1].e, c.st));
             if (launched >= slots) break;

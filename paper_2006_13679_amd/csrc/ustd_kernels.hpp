@@ -229,6 +229,16 @@ hipError_t launch_b_intervals(int n, int u, int ecc, const int *dist, const int 
 constexpr int kSmallSolveMaxN = 16384;
 template <typename T>
 hipError_t launch_solve_start(const SolveArgs<T> &a, double tol2, double delta2, int maxit, hipStream_t st);
+// Slots that the host enqueues at a time.  It learns of the end a chunk late, so up to two chunks of
+// empty slots (three kernels of 2 us each) run behind it, and a chunk costs a copy of the scalars (some
+// 12 us): 8, then 16 growing by 4 to 32, which take the device longer than the host takes to enqueue
+// the next.  With 8, 16, 32, 64, 64, ... a solve of 24 iterations, 26 slots with its updates, was
+// followed by 94 empty ones: weighted R-MAT 15 column 1.97 ms, now 1.74; weighted R-MAT 16 2.44, now
+// 2.14; unweighted R-MAT 16 1.33, now 1.29 (set-up included).
+constexpr int kSolveChunkFirst = 8, kSolveChunkMax = 32;
+constexpr int solve_chunk_after(int chunk) {
+    return chunk < 16 ? 16 : (chunk + 4 < kSolveChunkMax ? chunk + 4 : kSolveChunkMax);
+}
 template <typename T>
 hipError_t launch_solve_slot(const SolveArgs<T> &a, const RowMap &m, int G, hipStream_t st);
 template <typename T>

@@ -1,5 +1,5 @@
-// CPU driver of tests/test_large_ranges.py: functions of the kernels, compiled for the host, at the
-// largest sizes the API accepts.  Prints "ok" when every result is right.
+// CPU driver of tests/test_large_ranges.py: functions of the kernels and of their launches, compiled for
+// the host, over all sizes the API accepts.  Prints "ok" when every result is right.
 #include <sys/mman.h>
 
 #include <cstdio>
@@ -7,7 +7,7 @@
 #include <cstring>
 #include <vector>
 
-#include "ustd_device.hpp"
+#include "ustd_kernels.hpp"
 
 using namespace ustd;
 
@@ -144,6 +144,25 @@ void solve_threads() {
             check(small_solve_threads((int)n, G) == (n * G < 1024 ? 256 : 1024), "solve threads", n, G);
 }
 
+// kernels launched behind the end of a multi-kernel solve, when the host learns of the end one chunk
+// late.  They are to be no more than those of an engine of eight kernels an iteration, with the updates
+// inside, enqueued 8, 16, ... 256 iterations at a time (what the three kernels a slot took the place of).
+template <typename Next>
+long long launched(long long needed, int chunk, Next next) {
+    long long total = chunk;
+    for (; total < needed; total += chunk) chunk = next(chunk);
+    return total + next(chunk);
+}
+void solve_chunks() {
+    for (int it = 1; it <= 3000; ++it)
+        for (int updates = 1; updates <= 6 && updates <= it; ++updates) {
+            const long long slots = it + updates;
+            const long long now = 3 * (launched(slots, kSolveChunkFirst, solve_chunk_after) - slots);
+            const long long then = 8 * (launched(it, 8, [](int c) { return c < 128 ? 2 * c : 256; }) - it);
+            check(now <= then, "empty kernels", it, updates);
+        }
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
@@ -152,6 +171,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(what, "row_searches")) row_searches();
     else if (!strcmp(what, "walk_counts")) walk_counts();
     else if (!strcmp(what, "solve_threads")) solve_threads();
+    else if (!strcmp(what, "solve_chunks")) solve_chunks();
     else return 2;
     puts("ok");
     return 0;
