@@ -2068,16 +2068,17 @@ int ustd_tree_counts(const ustd_problem *prob, const int32_t *d_parents, int64_t
     HIP_TRY(launch_fill_i64(c.L.n, acc, 0, c.st));
     // A launch takes as many trees as fit: nothing is sampled here, and the record pool, the
     // sampler's path slots and the builder's scratch lie side by side in the workspace.  They hold
-    // the records of a launch's trees, then one word per vertex and tree.
+    // the records of a launch's trees, then one word per vertex and tree.  A batch costs a host wait
+    // and four launches or more, so trees_per_batch, which sizes the workspace, bounds a launch no
+    // further (five vertices, 8 trees, trees_per_batch 2: 0.347 ms a call in four batches, now 0.127).
     const long long rec_bytes = c.L.rec_stride * 8, word_bytes = align_up((long long)c.L.n * 4);
-    const long long per = std::max(1ll, std::min({(c.L.off_part - c.L.off_rec) / (rec_bytes + word_bytes), (long long)c.L.K,
-                                                  ((1ll << 31) - 1) / (c.L.n + 256)}));
+    const long long per =
+        std::max(1ll, std::min({(c.L.off_part - c.L.off_rec) / (rec_bytes + word_bytes), (long long)kMaxTreesPerBatch,
+                                ((1ll << 31) - 1) / (c.L.n + 256)}));
     int *open = c.misc->bfs_found;  // free after the set-up
     static_assert(sizeof(c.misc->bfs_found) >= (kTreeJumpRounds + 1) * sizeof(int), "one flag per round");
     for (long long b0 = 0; b0 < tree_count; b0 += per) {
         const int cnt = (int)std::min<long long>(per, tree_count - b0);
-        HIP_TRY(hipMemsetAsync(open, 0, (kTreeJumpRounds + 1) * sizeof(int), c.st));
-        HIP_TRY(launch_fill_i32(1, open, 1, c.st));
         IntervalArgs ia{};
         ia.n = c.L.n;
         ia.u = c.pivot;

@@ -1338,25 +1338,61 @@ constexpr int kJumps = 7;
 
 __device__ __forceinline__ bool in_tree_ids(int v, int n) { return v >= 0 && v < n; }
 
-__global__ __launch_bounds__(256) void tree_jump_init_kernel(IntervalArgs a) {
-    const int v = blockIdx.x * 256 + threadIdx.x;
-    if (v >= a.n) return;
+// the words of v at the start; *pv = its parent (-1 at u)
+__device__ __forceinline__ void jump_start(const IntervalArgs &a, const int *__restrict__ par, int v, int *anc,
+                                           unsigned *jw, int *pv) {
     const int n = a.n, u = a.u;
-    const int *__restrict__ par = a.par + (long long)blockIdx.y * a.par_stride;
-    int anc = u;
-    unsigned jw = (unsigned)u | kJumpDone;
-    int pv = -1;
-    if (v != u) {
-        pv = par[v];
-        if (!in_tree_ids(pv, n) || pv == v) {
-            atomicOr(a.err, 64);
-        } else if (pv != u) {
-            const int ppv = par[pv];
-            const bool marked = in_tree_ids(ppv, n) && (mark_bits(pv, a.bflag[pv], ppv, a.bflag[ppv]) & kMarkBit);
-            anc = pv;
-            jw = (unsigned)pv | (marked ? kJumpDone : 0u);
-        }
+    *anc = u;
+    *jw = (unsigned)u | kJumpDone;
+    *pv = -1;
+    if (v == u) return;
+    const int p = par[v];
+    *pv = p;
+    if (!in_tree_ids(p, n) || p == v) {
+        atomicOr(a.err, 64);
+    } else if (p != u) {
+        const int pp = par[p];
+        const bool marked = in_tree_ids(pp, n) && (mark_bits(p, a.bflag[p], pp, a.bflag[pp]) & kMarkBit);
+        *anc = p;
+        *jw = (unsigned)p | (marked ? kJumpDone : 0u);
     }
+}
+
+// a round of v on the words in memory; true if one of its words is still open
+template <typename W>
+__device__ __forceinline__ bool jump_round(int u, int v, int *anc, W *jw) {
+    bool more = false;
+    int x = anc[v];
+    if (x != u) {
+        for (int i = 0; i < kJumps && x != u; ++i) x = anc[x];
+        anc[v] = x;
+        more = x != u;
+    }
+    unsigned w = (unsigned)jw[v];
+    if (!(w & kJumpDone)) {
+        for (int i = 0; i < kJumps && !(w & kJumpDone); ++i) w = (unsigned)jw[w];
+        jw[v] = (W)w;
+        more = more || !(w & kJumpDone);
+    }
+    return more;
+}
+
+// the word nba | flags of v once the rounds are over
+__device__ __forceinline__ int jump_word(const IntervalArgs &a, int v, int anc, unsigned w, int pv) {
+    if (v == a.u) return v;
+    if (anc != a.u) atomicOr(a.err, 64);
+    const int nba = (w & kJumpDone) ? (int)(w & ~kJumpDone) : a.u;  // not done: on or below a cycle
+    return nba | (in_tree_ids(pv, a.n) ? mark_bits(v, a.bflag[v], pv, a.bflag[pv]) : 0);
+}
+
+// open[0] = 1, open[1 .. kTreeJumpRounds] = 0 for the rounds
+__global__ __launch_bounds__(256) void tree_jump_init_kernel(IntervalArgs a, int *__restrict__ open) {
+    const int v = blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.y == 0 && v <= kTreeJumpRounds) open[v] = v == 0;
+    if (v >= a.n) return;
+    int anc, pv;
+    unsigned jw;
+    jump_start(a, a.par + (long long)blockIdx.y * a.par_stride, v, &anc, &jw, &pv);
     a.scratch[(long long)blockIdx.y * a.scratch_stride + v] = anc;
     int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
     rec[v] = (int)jw;
@@ -1368,22 +1404,9 @@ __global__ __launch_bounds__(256) void tree_jump_kernel(IntervalArgs a, int *__r
     if (open[0] == 0) return;  // uniform over the grid
     const int v = blockIdx.x * 256 + threadIdx.x;
     bool more = false;
-    if (v < a.n) {
-        int *anc = a.scratch + (long long)blockIdx.y * a.scratch_stride;
-        int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
-        int x = anc[v];
-        if (x != a.u) {
-            for (int i = 0; i < kJumps && x != a.u; ++i) x = anc[x];
-            anc[v] = x;
-            more = x != a.u;
-        }
-        unsigned w = (unsigned)rec[v];
-        if (!(w & kJumpDone)) {
-            for (int i = 0; i < kJumps && !(w & kJumpDone); ++i) w = (unsigned)rec[w];
-            rec[v] = (int)w;
-            more = more || !(w & kJumpDone);
-        }
-    }
+    if (v < a.n)
+        more = jump_round(a.u, v, a.scratch + (long long)blockIdx.y * a.scratch_stride,
+                          a.rec + (long long)blockIdx.y * 2 * a.rec_stride);
     if (__any(more) && lane_id() == 0) open[1] = 1;
 }
 
@@ -1391,16 +1414,30 @@ __global__ __launch_bounds__(256) void tree_records_kernel(IntervalArgs a) {
     const int v = blockIdx.x * 256 + threadIdx.x;
     if (v >= a.n) return;
     int *rec = a.rec + (long long)blockIdx.y * 2 * a.rec_stride;
-    if (v == a.u) {
-        rec[v] = v;
-        return;
+    rec[v] = jump_word(a, v, a.scratch[(long long)blockIdx.y * a.scratch_stride + v], (unsigned)rec[v],
+                       rec[a.rec_stride + v]);
+}
+
+// A small graph: the same rounds in one launch, a block per tree, the words in LDS.  Below a
+// thousand vertices the launches were most of the call (path of two vertices, 8 trees two at a time:
+// 0.345 ms a call, 0.239 before the rounds had a launch each, now 0.129).
+constexpr int kTreeSmallMaxN = 1024;
+
+__global__ __launch_bounds__(256) void tree_records_small_kernel(IntervalArgs a, int rounds) {
+    __shared__ int anc[kTreeSmallMaxN], pv[kTreeSmallMaxN];
+    __shared__ unsigned jw[kTreeSmallMaxN];
+    const int *__restrict__ par = a.par + (long long)blockIdx.x * a.par_stride;
+    for (int v = threadIdx.x; v < a.n; v += 256) jump_start(a, par, v, &anc[v], &jw[v], &pv[v]);
+    for (int r = 0; r < rounds; ++r) {
+        __syncthreads();
+        for (int v = threadIdx.x; v < a.n; v += 256) jump_round(a.u, v, anc, jw);
     }
-    if (a.scratch[(long long)blockIdx.y * a.scratch_stride + v] != a.u) atomicOr(a.err, 64);
-    const int pv = rec[a.rec_stride + v];
-    const unsigned w = (unsigned)rec[v];
-    const int nba = (w & kJumpDone) ? (int)(w & ~kJumpDone) : a.u;  // not done: on or below a cycle
-    const int mb = in_tree_ids(pv, a.n) ? mark_bits(v, a.bflag[v], pv, a.bflag[pv]) : 0;
-    rec[v] = nba | mb;
+    __syncthreads();
+    int *rec = a.rec + (long long)blockIdx.x * 2 * a.rec_stride;
+    for (int v = threadIdx.x; v < a.n; v += 256) {
+        rec[v] = jump_word(a, v, anc[v], jw[v], pv[v]);
+        rec[a.rec_stride + v] = pv[v];
+    }
 }
 
 // ======================================================================================
@@ -2271,10 +2308,14 @@ hipError_t launch_wilson(const WilsonArgs &a, int blocks, bool lds_bits, bool co
     return hipGetLastError();
 }
 hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hipStream_t st) {
-    const dim3 grid(blocks_for(a.n, 256), ntrees);
-    tree_jump_init_kernel<<<grid, 256, 0, st>>>(a);
     int rounds = 1;  // 8^rounds >= n: then every path is covered (at most kTreeJumpRounds for n < 2^30)
     for (long long len = 8; len < a.n; len *= 8) ++rounds;
+    if (a.n <= kTreeSmallMaxN) {
+        tree_records_small_kernel<<<ntrees, 256, 0, st>>>(a, rounds);
+        return hipGetLastError();
+    }
+    const dim3 grid(blocks_for(a.n, 256), ntrees);
+    tree_jump_init_kernel<<<grid, 256, 0, st>>>(a, open);
     for (int r = 0; r < rounds; ++r) tree_jump_kernel<<<grid, 256, 0, st>>>(a, open + r);
     tree_records_kernel<<<grid, 256, 0, st>>>(a);
     return hipGetLastError();

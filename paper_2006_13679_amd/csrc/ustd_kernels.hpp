@@ -208,7 +208,7 @@ hipError_t launch_bpath(int n, int u, const int *rp, const int *col, const doubl
                         unsigned long long *rmax_bits, hipStream_t st);
 hipError_t launch_fixed_weights(int n, int u, const double *wB, int shift, long long *F, hipStream_t st);
 hipError_t launch_col_to_u16(long long nnz, const int *col, unsigned short *col16, hipStream_t st);
-// ntrees <= 65535 and ntrees * n < 2^31; open[0] = 1, open[1 .. kTreeJumpRounds] = 0 at launch
+// ntrees <= 65535 and ntrees * n < 2^31; open: kTreeJumpRounds + 1 flags, set by the launches
 constexpr int kTreeJumpRounds = 11;
 hipError_t launch_tree_records(const IntervalArgs &a, int ntrees, int *open, hipStream_t st);
 hipError_t launch_aggregate(const AggregateArgs &a, hipStream_t st);
