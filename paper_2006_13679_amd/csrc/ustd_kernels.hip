@@ -476,12 +476,12 @@ __device__ __forceinline__ int scalar_col(const unsigned short *col, int slot) {
 // dropped.  Next pointers: the last step out of a vertex counts, found by comparing all pairs.
 //   graph in LDS (GL): the row comes from the packed entries `lhops` {begin, degree << 16}, or
 //   from the columns and row pointers where those do not fit;
-//   no `hops` (they did not fit the workspace): from the columns and row pointers, two loads.
+//   no `hops` (a static scratch did not hold them): from the columns and row pointers, two loads.
 // Cycles a step, one lane stepping with the tree test and the store in its chain -> this: rows from
 // L2 (160 x 160 grid) 589 -> 227, graph in LDS (32 x 32) 277 -> 161, rows past L2 with the GPU full
 // (hyperbolic, n = 200k) 1812 -> 1200.
 // Returns the walk's total step count.
-template <bool LDS, typename CT, bool WT, bool GL, typename Next>
+template <bool LDS, typename CT, bool WT, bool GL, bool BV, typename Next>
 __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, const int *rp, const CT *col,
                                const unsigned long long *hops, const uint32_t *lhops, const double *cw, const int *guide,
                                uint32_t wkey, int x0, long long k0, uint32_t tlo, uint32_t thi, uint32_t key0,
@@ -533,7 +533,7 @@ __device__ long long walk_next(const TreeState<LDS> &bits, const Next &next, con
                         r0 = rp[y];
                         deg = rp[y + 1] - r0;
                     });
-            } else if (hops) {
+            } else if ((!LDS && !BV) || hops) {  // past the bitmap always there, but for the block-split graph
                 chase([&](int slot) {
                     const unsigned long long h = scalar(hops)[(uint32_t)slot];
                     r0 = (int)(uint32_t)h;
@@ -1189,7 +1189,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                 }
                 uint32_t wk0 = (uint32_t)s0;  // the walk's Philox key
                 if constexpr (BV) wk0 = (uint32_t)a.skey[s0];
-                const long long kk = walk_next<LDS, CT, WT, GL>(bits, next, rp, col, g.hops, lhops, cw, guide, wk0,
+                const long long kk = walk_next<LDS, CT, WT, GL, BV>(bits, next, rp, col, g.hops, lhops, cw, guide, wk0,
                                                                 __builtin_amdgcn_readfirstlane(xs), k0, tlo, thi, g.key0,
                                                                 g.key1);
                 retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
