@@ -101,33 +101,27 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
     return block_sum_t<T>(v, sh, (int)blockDim.x);
 }
 
-// Walk steps and draws of a tree, counted by the lanes of its wave.  A lane's own counters have 32 bits:
-//   steps: of the walks it commits in batches, at most kBatchSteps a start, and a tree has fewer than
-//   2^30 starts;
-//   draws: at most kWalkDraws a start it walks, moved to the wave's counter once every kDrawWindow
-//   starts of the tree (another kDrawWindow bounds the starts then in flight).
-// What the whole wave commits (longer walks, any number of steps) goes to the wave's 64-bit counters.
-struct WalkCounts {
-    static constexpr unsigned kBatchSteps = 4, kWalkDraws = 250, kDrawWindow = 1u << 22;
-    static_assert((1ull << 30) * kBatchSteps <= 1ull << 32, "a lane's steps fit (fewer than 2^30 starts)");
-    static_assert(2ull * kDrawWindow * kWalkDraws < 1ull << 32, "a lane's draws between two moves fit");
-    uint32_t steps = 0u, draws = 0u;
-    long long wave_steps = 0, wave_draws = 0;  // uniform
-    __host__ __device__ __forceinline__ void batch_walk(int k) { steps += (uint32_t)k; }
-    __host__ __device__ __forceinline__ void draw() { ++draws; }
-    __host__ __device__ __forceinline__ void wave_walk(long long k, long long drawn = 0) {
-        wave_steps += k;
-        wave_draws += drawn;
-    }
-    __host__ __device__ __forceinline__ static bool move_due(int start) {
-        return start != 0 && (start & (int)(kDrawWindow - 1)) == 0;
-    }
-    // all: the sum of the lanes' draws
-    __host__ __device__ __forceinline__ void move_draws(long long all) {
-        wave_draws += all;
-        draws = 0u;
-    }
-};
+// Walk steps and draws of a tree: a lane of its wave counts in 32 bits, the wave (uniform) in 64.
+//   steps: the walks that a lane commits in batches, at most kBatchSteps a start, are the lane's, and a
+//   tree has fewer than 2^30 starts; what the wave commits together is the wave's, but for a tree
+//   within the LDS bitmap, where 2^17 starts of kWalkDraws steps fit lane 0's counter (the wave's costs
+//   the graph-in-LDS sampler 4% on long lone walks: six more scalar registers spilled);
+//   draws: at most kWalkDraws a start that the lane walks, moved to the wave's counter once every
+//   kDrawWindow starts of the tree (another kDrawWindow bounds the starts then in flight).
+constexpr unsigned kBatchSteps = 4, kWalkDraws = 250, kDrawWindow = 1u << 22;
+static_assert((1ull << 30) * kBatchSteps <= 1ull << 32, "a lane's batch commits fit");
+static_assert((1ull << 17) * (kWalkDraws + kBatchSteps) < 1ull << 32, "all commits within the bitmap fit a lane");
+static_assert(2ull * kDrawWindow * kWalkDraws < 1ull << 32, "a lane's draws between two moves fit");
+
+// of a walk of k steps that the wave committed: the lane's part, the wave's part
+template <bool LDS>
+__host__ __device__ __forceinline__ uint32_t long_walk_lane(int k, int lane) { return LDS && lane == 0 ? (uint32_t)k : 0u; }
+template <bool LDS>
+__host__ __device__ __forceinline__ long long long_walk_wave(int k) { return LDS ? 0 : k; }
+// whether the lanes' draws move before the window of starts at `start`
+__host__ __device__ __forceinline__ bool draws_move(int start) {
+    return start != 0 && (start & (int)(kDrawWindow - 1)) == 0;
+}
 
 // Threads at work in the one-workgroup solve.  Where the rows' lane groups fill less than the
 // workgroup, four waves do the work and the others leave at once (a barrier counts the waves that

@@ -248,7 +248,7 @@ template <bool LDS>
 constexpr int rob_cap() { return LDS ? kSamplerRobLds : kSamplerRobMax; }
 constexpr int kPathLds = 4;    // recorded steps kept in LDS per entry (x_1..x_4)
 constexpr int kPath = 250;     // recorded steps per speculative walk (x_1..x_250)
-static_assert(kPathLds <= (int)WalkCounts::kBatchSteps && kPath <= (int)WalkCounts::kWalkDraws, "the counters' bounds");
+static_assert(kPathLds <= (int)kBatchSteps && kPath <= (int)kWalkDraws, "the bounds of the counters");
 static_assert(kPath - kPathLds == kSamplerPathGlobal, "path split");
 // reorder-buffer entry states (a byte) besides a finished walk's step count (<= kPath; 0: the
 // start was absorbed, nothing to commit):
@@ -770,7 +770,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
     int my_e = 0, x = 0, s = 0, bkey = 0, k = 0, r0 = 0, r1 = 0, fx = 0, pbits = 0;
     uint4 ph = make_uint4(0, 0, 0, 0);
     int4 vx = make_int4(0, 0, 0, 0);  // tree state in the records: x's entry {row begin, row end, B_u flag, 0}
-    WalkCounts walked;
+    uint32_t steps = 0u, draws = 0u;      // walk steps and draws of this lane
+    long long wsteps = 0, wdraws = 0;     // and of the wave
 
     // whether a vertex's parent is written, given the edge bits of its tree edge in the low two
     // bits: always, or where Algorithm 2 may read it (marked by a backward edge)
@@ -811,8 +812,10 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                 if (wpos == wcnt) {
                     if (wend >= n) break;
                     if constexpr (!LDS) {  // never due on a graph within the bitmap
-                        if (WalkCounts::move_due(wend))
-                            walked.move_draws(uniform_ll((long long)wave_sum((unsigned long long)walked.draws)));
+                        if (draws_move(wend)) {
+                            wdraws += uniform_ll((long long)wave_sum((unsigned long long)draws));
+                            draws = 0u;
+                        }
                     }
                     uint32_t fb = bits.free4(wend, lane, n);
                     const int left = n - (wend + 4 * lane);
@@ -904,7 +907,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
             consume(fy, cvy, ny0, ny1);  // no load may stay in flight into the commit phase
             if (in) cvy = cv_of(y, cvy);
             ++k;
-            walked.draw();
+            ++draws;
             const int eb = edge_bits(x, fx, y, fy);
             if (k <= kPathLds) {
                 rob_p[sl].v[k - 1] = (CT)y;
@@ -960,7 +963,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                         vertex_at(nbw, s0) = carry | (int)((unsigned)pb << 30);
                         if (keeps_parent(pb)) vertex_at(par, s0) = x1;
                         bits.set(s0);
-                        walked.batch_walk(1);
+                        ++steps;
                     }
                     head += r;
                     wave_sync();
@@ -1062,7 +1065,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     if (any3) put(2, x2);
                     put(1, x1);
                     put(0, s0);
-                    walked.batch_walk(istar);
+                    steps += istar;
                 }
                 head += jstar;
                 wave_sync();
@@ -1139,7 +1142,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     bits.set(xv);
                     if constexpr (!LDS) stamps[stamp_slot(xv)] = (uint16_t)round;
                 }
-                walked.wave_walk(istar);
+                steps += long_walk_lane<LDS>(istar, lane);
+                wsteps += long_walk_wave<LDS>(istar);
                 ++head;
                 wave_sync();
                 if constexpr (!LDS) {
@@ -1194,7 +1198,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                                                                 g.key1);
                 retrace<LDS>(bits, next, nbw, par, bflag, u, s0, htab, stamps, round);
                 for (int i = lane; i < 2 * kHashSlots; i += kWave) htab[i] = kWave;
-                walked.wave_walk(kk, kk - k0);
+                wsteps += kk;
+                wdraws += kk - k0;
                 ++head;
                 wave_sync();
                 if constexpr (!LDS) remark();
@@ -1300,7 +1305,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
                     if (m) carry = __builtin_amdgcn_readlane(xv[c], __builtin_ctzll(m));
                 }
             }
-            walked.wave_walk(istar);
+            steps += long_walk_lane<LDS>(istar, lane);
+            wsteps += long_walk_wave<LDS>(istar);
             ++head;
             wave_sync();
             if constexpr (!LDS) {
@@ -1309,8 +1315,8 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
         }
     }
 
-    const long long sum_steps = walked.wave_steps + (long long)wave_sum((unsigned long long)walked.steps);
-    const long long sum_draws = walked.wave_draws + (long long)wave_sum((unsigned long long)walked.draws);
+    const long long sum_steps = wsteps + (long long)wave_sum((unsigned long long)steps);
+    const long long sum_draws = wdraws + (long long)wave_sum((unsigned long long)draws);
     if (lane == 0) {
         if (a.steps) a.steps[tile] = sum_steps;
         if (a.draws) a.draws[tile] = sum_draws;

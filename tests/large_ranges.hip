@@ -118,23 +118,31 @@ void row_searches() {
     }
 }
 
-// walk counts of a tree past 2^32 steps: long commits, batch commits of one lane, draws of one lane
-void walk_counts() {
-    WalkCounts c;
-    const long long longs = 20000000;
-    for (long long i = 0; i < longs; ++i) c.wave_walk(250);
-    check(c.wave_steps + c.steps == 250 * longs, "long commits", c.wave_steps, c.steps);
-    const long long starts = (1ll << 30) - 3;  // the largest tree, every batch walk by one lane
-    for (long long i = 0; i < starts; ++i) c.batch_walk(4);
-    check(c.wave_steps + c.steps == 250 * longs + 4 * starts, "batch commits", c.wave_steps, c.steps);
-    long long draws = 0;
-    for (int w = 0; w < 1 << 25; w += 256) {  // a window of starts, each walked to its last recorded step
-        if (WalkCounts::move_due(w)) c.move_draws(c.draws);
-        for (int k = 0; k < 256 * 250; ++k, ++draws) c.draw();
+// the walk counts of the largest trees: 2^30 - 3 starts past the bitmap, 2^17 within it
+template <bool LDS>
+void walk_counts_of(long long starts) {
+    uint32_t steps = 0, draws = 0;  // lane 0
+    long long wave_steps = 0, wave_draws = 0;
+    const long long longs = starts / 2;  // walks of 250 steps; the other starts are batch walks by lane 0
+    for (long long i = 0; i < longs; ++i) {
+        steps += long_walk_lane<LDS>(250, 0) + long_walk_lane<LDS>(250, 1);
+        wave_steps += long_walk_wave<LDS>(250);
     }
-    c.wave_walk(1ll << 33, (1ll << 33) - 250);
-    check(c.wave_draws + c.draws == draws + (1ll << 33) - 250, "draws", c.wave_draws, c.draws);
-    check(c.wave_steps + c.steps == 250 * longs + 4 * starts + (1ll << 33), "lone walk", c.wave_steps, c.steps);
+    for (long long i = longs; i < starts; ++i) steps += kBatchSteps;
+    check(wave_steps + steps == 250 * longs + 4 * (starts - longs), "steps", wave_steps, steps);
+    for (int w = 0; w < starts; w += 256) {  // a window of starts, each walked to its last recorded step
+        if (!LDS && draws_move(w)) {
+            wave_draws += draws;
+            draws = 0;
+        }
+        draws += 256 * kWalkDraws;
+    }
+    const long long want = (starts + 255) / 256 * 256 * kWalkDraws;
+    check(wave_draws + draws == want, "draws", wave_draws, draws);
+}
+void walk_counts() {
+    walk_counts_of<false>((1ll << 30) - 3);
+    walk_counts_of<true>(1ll << 17);
 }
 
 // the one-workgroup solve takes the whole workgroup from one workgroup of row lanes on, at any size
