@@ -61,8 +61,8 @@ enum {
                                   ustd_batch_diag_lpinv: WORKGROUP for every member */
     USTD_ENGINE_WORKGROUP = 1, /* the whole solve in one workgroup, no host round trip (batches run
                                   all members' solves side by side in one launch) */
-    USTD_ENGINE_MULTI = 2      /* eight kernels per iteration over the whole GPU, enqueued ahead of a
-                                  device-side done flag */
+    USTD_ENGINE_MULTI = 2      /* three kernels per iteration (and per reliable update) over the whole
+                                  GPU, enqueued ahead of a device-side done flag */
 };
 
 /* How each tree is sampled.  Both draw uniform spanning trees rooted at the pivot; they consume

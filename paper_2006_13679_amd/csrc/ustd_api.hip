@@ -436,7 +436,7 @@ long long graph_in_lds(const Plan &L, int blocks, bool *hops) {
     return 0;
 }
 
-// The rows per slot that the sampler's lone walks read (the columns have been validated).
+// The rows per slot that the sampler's lone walks read (after the validation, where it was asked for).
 int queue_hops(Ctx &c, hipStream_t st) {
     c.hops_ready = true;
     HIP_TRY(launch_hops(c.L.nnz, c.p->d_col, c.rp32, at<unsigned long long>(c.ws, c.L.off_hops), st));
@@ -753,7 +753,7 @@ int setup_blocks(Ctx &c) {
     HIP_TRY(launch_bc_top_flags(ns, sblk, stop, rflag, st));
     HIP_TRY(launch_scan_excl(rflag, rpos, ns, tiles, &c.misc->ntops, st));
     HIP_TRY(launch_bc_compact(ns, rflag, rpos, tops, st));
-    // the sampler's view of G*: no B_u flags (no marks), 16-bit columns or edge entries
+    // the sampler's view of G*: no B_u flags (no marks); 16-bit columns, vertex entries, rows per slot
     int *sbflag = at<int>(ws, L.off_sbflag);
     HIP_TRY(launch_fill_i32(ns, sbflag, 0, st));
     if (L.s_col16) HIP_TRY(launch_col_to_u16(nnz, scol, at<unsigned short>(ws, L.off_scol16), st));
@@ -1201,7 +1201,7 @@ int make_batch_plan(const ustd_problem *probs, int count, BatchPlan &B, const us
             return fail(USTD_EINVAL, "problem %d: a batch samples with the plain Wilson variant only", i);
         B.lds_bits = B.lds_bits && make_plan(&probs[i], false).lds_bits;
     }
-    // one sampler variant serves every member: without the LDS bitmap all need edge entries
+    // one sampler variant serves every member: without the LDS bitmap all need vertex entries
     for (int i = 0; i < count; ++i) {
         const Plan L = make_plan(&probs[i], false, !B.lds_bits);
         B.g.push_back(L);
@@ -1246,7 +1246,7 @@ int make_batch_plan(const ustd_problem *probs, int count, BatchPlan &B, const us
     return USTD_OK;
 }
 
-// the workspace of a batch: enough for every schedule (the records layout needs edge entries)
+// the workspace of a batch: enough for every schedule (the records layout needs vertex entries)
 int batch_workspace(const ustd_problem *probs, int count, long long *bytes) {
     BatchPlan a, b;
     ustd_batch_schedule s = schedule_of(nullptr);
@@ -1283,8 +1283,8 @@ struct BatchFill {
 
 // Re-enqueues a member's set-up with the pivot and eccentricity its plan found (no host round
 // trip): the CSR views and heavy-row list, the BFS tree B_u (ecc levels), its intervals and
-// marks, the sampler's edge entries, and a weighted graph's row sums, B-path resistances and
-// edge factors at the planned fixed-point shift.  The kernels are deterministic, so the
+// marks, the sampler's vertex entries and rows per slot, and a weighted graph's row sums, B-path
+// resistances and edge factors at the planned fixed-point shift.  The kernels are deterministic, so the
 // workspace ends as the plan's set-up left it.
 int setup_replay(Ctx &c) {
     const ustd_problem *p = c.p;

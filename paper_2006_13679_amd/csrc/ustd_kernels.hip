@@ -226,17 +226,18 @@ __global__ void count_unreached_kernel(int n, const int *__restrict__ dist, int 
 //     loop erasure by one ballot and one lane read per branch vertex.  A walk that filled its
 //     record without reaching the tree it saw takes this path too: the tree has usually
 //     grown since, so the record mostly does reach it;
-//   - if no recorded vertex is in the tree, one lane turns the record into Next pointers and
-//     continues the walk from its last vertex in a tight loop (the sequential algorithm for
-//     that start).
+//   - if no recorded vertex is in the tree, one lane turns the record into Next pointers and the
+//     wave continues the walk from its last vertex, 64 steps at a time (the sequential algorithm
+//     for that start; walk_next).
 //
 // What bounds it: the latency of a round (allocate, step, commit) times the rounds of a tree, and
 // on graphs within the bitmap instruction issue.  A commit round that planned every walk for
 // five recorded steps, with a tree test (a global load past the bitmap) per vertex, took half
-// of a tree's time; without those, with 128 entries and starts from the window's list, a pass went
-// from 1350 to 1036 ms (R-MAT scale 22, 8192 trees), 51.3 to 30.8 ms (R-MAT 19, 777 trees,
-// fewer trees than SIMDs), 8.58 to 5.36 ms (R-MAT 16 edge counts), 13.1 to 11.2 ms (R-MAT 16),
-// 316 to 243 ms (hyperbolic, 200k vertices) and 5.1 to 3.9 ms (32 x 32 grid).
+// of a tree's time.  Without those, with 128 entries, starts from the window's list, the records in
+// two arrays and the lone walks of walk_next, a pass went from 1350 to 834 ms (R-MAT scale 22, 8192
+// trees), 51.3 to 30.6 ms (R-MAT 19, 777 trees, fewer trees than SIMDs), 8.58 to 5.28 ms (R-MAT 16
+// edge counts), 13.1 to 9.06 ms (R-MAT 16), 316 to 198 ms (hyperbolic, 200k vertices) and 5.1 to
+// 2.85 ms (32 x 32 grid).
 //
 // Output per vertex x: the word nba(x) | flags and, where the caller or Algorithm 2 reads it,
 // parent_T(x) (see "Marked vertices").
