@@ -101,7 +101,7 @@ int next_pow2(int v) {
 
 int check_problem(const ustd_problem *p) {
     if (!p) return fail(USTD_EINVAL, "problem is NULL");
-    if (p->n < 2 || p->n >= (1ll << 30) - 1) return fail(USTD_EINVAL, "n = %lld out of range [2, 2^30 - 1)", (long long)p->n);
+    if (p->n < 2 || !ids_fit(p->n)) return fail(USTD_EINVAL, "n = %lld out of range [2, 2^30 - 1)", (long long)p->n);
     if (p->nnz < 2 || p->nnz >= (1ll << 31)) return fail(USTD_EINVAL, "nnz = %lld out of range [2, 2^31)", (long long)p->nnz);
     if (!p->d_row_ptr || !p->d_col) return fail(USTD_EINVAL, "row_ptr / col is NULL");
     if (p->pivot < -2 || p->pivot >= p->n) return fail(USTD_EINVAL, "pivot %d out of range", p->pivot);
@@ -745,6 +745,7 @@ int setup_blocks(Ctx &c) {
     HIP_TRY(hipMemcpyAsync(&ns, &c.misc->nslots, sizeof(int), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     if (ns < n || ns > L.s_nmax) return fail(USTD_EHIP, "block split: %d slots for %d vertices", ns, n);
+    if (!ids_fit(ns)) return fail(USTD_EINVAL, "the block-split graph has %d vertices (at most %d)", ns, kFree - 1);
     HIP_TRY(launch_scan_excl(sdeg, rps, ns, tiles, &c.misc->scan_total, st));
     HIP_TRY(launch_bc_columns(n, u, c.rp32, c.p->d_col, eblk, uf, spar, stop, rps, cur, scol, st));
     HIP_TRY(launch_bc_roots(ns, rps, vtx, sblk, at<unsigned long long>(ws, L.off_rkey), rflag, st));

@@ -101,6 +101,11 @@ __device__ __forceinline__ T block_sum_t(T v, T *sh) {
     return block_sum_t<T>(v, sh, (int)blockDim.x);
 }
 
+// A record's word holds a vertex in 30 bits, whose largest value marks a free vertex: the vertices of a
+// graph (the slots of a block-split graph) that the sampler takes.
+constexpr int kFree = 0x3FFFFFFF;
+__host__ __device__ __forceinline__ bool ids_fit(long long count) { return count < kFree; }
+
 // Walk steps and draws of a tree: a lane of its wave counts in 32 bits, the wave (uniform) in 64.
 //   steps: the walks that a lane commits in batches, at most kBatchSteps a start, are the lane's, and a
 //   tree has fewer than 2^30 starts; what the wave commits together is the wave's, but for a tree

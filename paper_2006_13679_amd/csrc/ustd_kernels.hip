@@ -269,7 +269,6 @@ static_assert(kWin == 4 * kWave, "four vertices of the window per lane");
 // test reads the line a walk that ends there needs anyway, and joining is the record write
 // itself (set() does nothing).  All accesses of a tree's records come from one wavefront,
 // whose loads and stores the vector L1 keeps in order.
-constexpr int kFree = 0x3FFFFFFF;  // nba of a vertex not in the tree; vertex IDs are below it
 
 // entry v of an array of 4-byte entries, one per vertex: a 32-bit offset from a uniform base (4 v <
 // 2^32) takes one register and no 64-bit address arithmetic

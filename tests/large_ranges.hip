@@ -171,6 +171,13 @@ void solve_chunks() {
         }
 }
 
+// the largest vertex of the largest graph (of the largest block-split graph) is no free mark, and keeps
+// clear of a word's flag bits
+void vertex_ids() {
+    for (long long count : {2ll, (1ll << 30) - 2}) check(ids_fit(count), "ids", count, 0);
+    for (long long count : {(1ll << 30) - 1, 1ll << 30, (1ll << 31) - 6}) check(!ids_fit(count), "ids", count, 1);
+}
+
 int main(int argc, char **argv) {
     const char *what = argc > 1 ? argv[1] : "";
     if (!strcmp(what, "row_sums")) row_sums();
@@ -180,6 +187,7 @@ int main(int argc, char **argv) {
     else if (!strcmp(what, "walk_counts")) walk_counts();
     else if (!strcmp(what, "solve_threads")) solve_threads();
     else if (!strcmp(what, "solve_chunks")) solve_chunks();
+    else if (!strcmp(what, "vertex_ids")) vertex_ids();
     else return 2;
     puts("ok");
     return 0;

@@ -20,7 +20,7 @@ def driver(tmp_path_factory):
 
 
 @pytest.mark.parametrize("what", ["row_sums", "row_loops", "running_sums", "row_searches", "walk_counts",
-                                  "solve_threads", "solve_chunks"])
+                                  "solve_threads", "solve_chunks", "vertex_ids"])
 def test_on_the_host(driver, what):
     r = subprocess.run([driver, what], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0 and r.stdout.strip() == "ok", (r.returncode, r.stdout, r.stderr)
