@@ -1947,8 +1947,9 @@ bool most_static_trees(ustd_problem *q, bool hops, Plan *L) {
         *L = make_plan(q, true, false, hops);
         return (size_t)L->total <= kStaticScratchBytes;
     };
+    if (fits(kMaxTreesPerBatch)) return true;  // a small graph, or few trees in all: no search
     if (!fits(1)) return false;
-    int lo = 1, hi = kMaxTreesPerBatch;
+    int lo = 1, hi = kMaxTreesPerBatch - 1;
     while (lo < hi) {
         const int mid = lo + (hi - lo + 1) / 2;
         if (fits(mid)) lo = mid;
