@@ -1327,7 +1327,7 @@ __global__ __launch_bounds__(64, 5) void wilson_kernel(WilsonArgs a) {
 // ======================================================================================
 // Records of caller-supplied trees.  The sampler writes each vertex's record as it commits; for
 // trees given as parent arrays the same records are built here by pointer jumping, a thread per
-// (vertex, tree): 100 trees of R-MAT scale 15 in 0.60 ms a call.  Two words per vertex are doubled
+// (vertex, tree): 100 trees of R-MAT scale 15 in 0.57 ms a call.  Two words per vertex are doubled
 // side by side: anc(v), an ancestor of v (u once reached), whose end tells whether v reaches the
 // pivot; and jw(v) = J | done << 31, where J is an ancestor of v such that every vertex
 // from parent(v) up to J is unmarked and not u (not done), or J = nba(v) (done).  A round follows
